@@ -68,8 +68,9 @@ struct FwdArgs {
     int32_t Dn;             // dwords that hold candidates: ceil(N / 32)
     int32_t DT;             // candidate dwords per block tile
     int32_t CPT;            // clauses per thread (<= 255)
-    uint32_t* H;            // [n_inst][Np][K1] accumulators
+    uint32_t* H;            // [n_inst][H_reps][Np][K1] accumulators
     int64_t H_stride;       // Np * K1
+    int32_t H_reps;         // replicas per instance, added up by the SmoothMin kernel
     const Ctrl* ctrl;       // may be null
     const InstCtrl* ictrl;  // may be null
     uint32_t* planes;       // null, or [clauses][plane_P][plane_stride]: R of every clause in binary
@@ -91,7 +92,8 @@ struct FwdArgs {
 };
 
 struct SminArgs {
-    uint32_t* H;            // [n_inst][Np][K1] accumulators (read, optionally zeroed)
+    uint32_t* H;            // [n_inst][H_reps][Np][K1] accumulators (read, optionally zeroed)
+    int32_t H_reps;
     uint32_t* H_last;       // [n_inst][N][K1] copy including empty clauses, may be null
     float* table;           // [n_inst][K1][Np] dL/dR, may be null
     float* S_out;           // [n_inst][N] SmoothMin, may be null

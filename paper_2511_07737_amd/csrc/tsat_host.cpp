@@ -73,7 +73,7 @@ struct tsat_solver {
     int cur = 0;
     int32_t bits_mode = TSAT_MODE_MEAN; // normalization mode the current bits were computed with
     DBuf theta, m, v;
-    DBuf H, H_last, table, S64, sat;
+    DBuf H, table, S64, sat;
     DBuf ctrl, ictrl, ctrl_scr, witness;
     // scratch for stateless evaluations and the device-pointer API
     DBuf lits_scr, mu_scr, H_scr, table_scr, S64_scr, sat_scr, tmp;
@@ -175,12 +175,17 @@ static FwdGeom fwd_geometry(int32_t N, int32_t K1, int64_t Cb, int32_t KW, int32
     const int bins = KW + 1;
     g.DT = std::min(g.Dn, 64);
     while (g.DT > 1 && (size_t)g.DT * 32 * bins * 4 > 64 * 1024) g.DT >>= 1;
-    g.S = 256 / g.DT;
+    g.S = 4 * (64 / g.DT);
     g.tiles = (g.Dn + g.DT - 1) / g.DT;
     target_blocks = std::max(1, target_blocks);
     const int64_t target_x = std::max<int64_t>(1, (target_blocks + g.tiles - 1) / g.tiles);
     int64_t cpt = (Cb + (int64_t)g.S * target_x - 1) / ((int64_t)g.S * target_x);
-    g.CPT = (int)std::max<int64_t>(16, std::min<int64_t>(255, cpt));
+    // at least 4 clauses per thread: below that the read-out of a block's
+    // counters outweighs its clauses (32 ragged instances, N = 32: forward
+    // 30.1 us at 16, 26.6 at 8 and 4; 32 instances of 800 clauses, N = 64:
+    // 11.6 at 16, 10.5 at 4, 9.9 at 2; 2e5 mixed clauses, N = 100, the three
+    // narrow buckets: 43.4 at 16, 31.9 at 4, 34.5 at 2)
+    g.CPT = (int)std::max<int64_t>(4, std::min<int64_t>(255, cpt));
     return g;
 }
 
@@ -245,7 +250,27 @@ static int32_t prepare_units(tsat_solver* s, int32_t N)
     return TSAT_OK;
 }
 
-// enqueue the forward histograms of every width bucket on literal rows `lits`
+// Histogram replicas per instance.  A forward's blocks close with one atomic
+// add per candidate and level; adds to one address from different XCDs pass
+// its line around, so each XCD (blockIdx mod 8) gets a replica while the
+// instances are few enough for their blocks to meet often, and the
+// candidates few enough for one block to add the replicas up (a brute-force
+// check's blocks spread over its many candidates).
+static int32_t hist_reps(const tsat_solver* s, int32_t Np)
+{
+    if (Np > TSAT_MAX_STEP_N) return 1;
+    int32_t r = 8;
+    while (r > 1 && r * s->st.n_inst > 64) r >>= 1;
+    return r;
+}
+
+// words of an accumulator for every candidate count up to Np
+static size_t hist_words(const tsat_solver* s, int32_t Np)
+{
+    const int32_t small = std::min<int32_t>(Np, TSAT_MAX_STEP_N);
+    return (size_t)s->st.n_inst * K1_of(s) * (size_t)std::max(Np, hist_reps(s, small) * small);
+}
+
 // Words per candidate row the update kernels use for W words (a power of two).
 static int32_t row_words(int32_t W) { return W <= 2 ? W : (W <= 4 ? 4 : (W <= 8 ? 8 : 16)); }
 
@@ -408,6 +433,7 @@ static int32_t enqueue_fwd(tsat_solver* s, const uint64_t* lits, int32_t N, uint
     base.W2 = 2 * W;
     base.H = H;
     base.H_stride = (int64_t)64 * W * base.K1;
+    base.H_reps = hist_reps(s, 64 * W);
     base.ctrl = ctrl;
     base.ictrl = ictrl;
     // narrow clauses (widths 1 .. 3): two planes each from the start of the
@@ -512,6 +538,7 @@ static SminArgs smin_args(tsat_solver* s, const tsat_params& p, int32_t N, int32
     a.N = N;
     a.Np = Np;
     a.K1 = K1_of(s);
+    a.H_reps = hist_reps(s, Np);
     a.zero_H = 1;
     a.every = p.decay_every;
     a.restart = p.restart_every;
@@ -625,8 +652,9 @@ static int32_t ensure_scratch(tsat_solver* s, int32_t N)
     RET(s->lits_scr.reserve(((size_t)2 * s->st.V * W + 16) * 8, "scratch literal rows"));
     RET(s->mu_scr.reserve((size_t)s->st.V * 8, "scratch row means"));
     if (Np > s->scr_Np) {
-        RET(s->H_scr.alloc(ni * Np * K1 * 4, "scratch histogram"));
-        HIPCHK(launch_fill_u32(s->H_scr.as<uint32_t>(), (int64_t)(ni * Np * K1), 0u, s->stream));
+        const size_t hw = hist_words(s, Np);
+        RET(s->H_scr.alloc(hw * 4, "scratch histogram"));
+        HIPCHK(launch_fill_u32(s->H_scr.as<uint32_t>(), (int64_t)hw, 0u, s->stream));
         // the device-pointer calls run on the caller's stream: finish the fill first
         HIPCHK(hipStreamSynchronize(s->stream));
         RET(s->table_scr.alloc(ni * Np * K1 * 4, "scratch table"));
@@ -956,13 +984,12 @@ static int32_t alloc_batch(tsat_solver* s, int32_t N)
     RET(s->theta.alloc(VN * 4, "theta"));
     RET(s->m.alloc(VN * 4, "m"));
     RET(s->v.alloc(VN * 4, "v"));
-    RET(s->H.alloc(ni * Np * K1 * 4, "histogram"));
-    RET(s->H_last.alloc(ni * Np * K1 * 4, "histogram"));
+    const size_t hw = hist_words(s, Np);
+    RET(s->H.alloc(hw * 4, "histogram"));
     RET(s->table.alloc(ni * Np * K1 * 4, "table"));
     RET(s->S64.alloc(ni * Np * 8, "S"));
     RET(s->sat.alloc(ni * Np * 8, "sat counts"));
-    HIPCHK(launch_fill_u32(s->H.as<uint32_t>(), (int64_t)(ni * Np * K1), 0u, s->stream));
-    HIPCHK(launch_fill_u32(s->H_last.as<uint32_t>(), (int64_t)(ni * Np * K1), 0u, s->stream));
+    HIPCHK(launch_fill_u32(s->H.as<uint32_t>(), (int64_t)hw, 0u, s->stream));
     HIPCHK(launch_fill_u32(s->m.as<uint32_t>(), (int64_t)VN, 0u, s->stream));
     HIPCHK(launch_fill_u32(s->v.as<uint32_t>(), (int64_t)VN, 0u, s->stream));
     if (plane_path(s, N)) RET(ensure_planes(s, s->planes, N, s->stream));
@@ -1153,7 +1180,6 @@ int32_t tsat_step(tsat_solver* s, int32_t max_steps, const tsat_params* params, 
 
     SminArgs sa = smin_args(s, p, s->N, s->Np);
     sa.H = s->H.as<uint32_t>();
-    sa.H_last = s->H_last.as<uint32_t>();
     sa.table = s->table.as<float>();
     sa.S64_out = s->S64.as<double>();
     sa.sat_out = s->sat.as<int64_t>();
@@ -1795,6 +1821,7 @@ int32_t tsat_fwd_dev_noalloc(tsat_solver* s, const uint64_t* bits, int32_t N, fl
         a.CPT = g.CPT;
         a.H = H;
         a.H_stride = (int64_t)Np * K1;
+        a.H_reps = 1; // the fixed scratch array holds one accumulator
         a.nunits = (int32_t)nunits;
         HIPCHK(launch_fwd(a, (int)nunits, g.tiles, st));
     }
@@ -1802,6 +1829,7 @@ int32_t tsat_fwd_dev_noalloc(tsat_solver* s, const uint64_t* bits, int32_t N, fl
     p.tau = tau;
     SminArgs a = smin_args(s, p, N, Np);
     a.H = H;
+    a.H_reps = 1;
     a.H_last = hist;
     a.S_out = S;
     a.update = 0;

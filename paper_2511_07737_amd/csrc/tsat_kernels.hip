@@ -173,30 +173,39 @@ __device__ __forceinline__ uint32_t lit_dword(const uint32_t* __restrict__ bits3
 // One work unit of a width-KW bucket: the block's clauses [u.c0, u.c1),
 // their literal codes in `codes` (KW per clause), planes of R written to
 // `planes` ([clause][plane_P][plane_stride] dwords from clause plane_base)
-// when non-null.  lh: the block's LDS bins, [DT*32][KW+1].
+// when non-null.  lh: the block's LDS counts, [KW][32][DT].
+//
+// A lane counts dword tid mod DT of the rows; the 64 / DT lanes of a wave
+// that share a dword are its slots.  The read-out adds the vertical counters
+// of a wave's slots with a bit-sliced adder over log2(slots) lane exchanges,
+// after which every lane of a dword holds the wave's totals and extracts its
+// share of the 32 candidates: consecutive LDS words, one add per candidate
+// and level.  (Every lane extracting all 32 of its candidates and adding
+// them to LDS bins shared by its slots took most of a small launch: all
+// lanes of a dword hit one bank at a time.)  With the histogram replicas:
+// large configuration 255 -> 212 us, 32 ragged instances (4.6e5 variables,
+// N = 32) 69 -> 27 us, V = 5e4 and N = 1000 76 -> 43 us, 32 instances of
+// V = 200 and N = 64 15.8 -> 10.5 us.
 template <int KW, int B, bool VR>
 __device__ __forceinline__ void fwd_hist_unit(const FwdArgs& a, const FwdUnit& u, const uint32_t* __restrict__ codes,
                                               uint32_t* planes, int plane_P, int64_t plane_base, uint32_t* lh)
 {
-    uint32_t* H = a.H + (size_t)u.inst * a.H_stride;
-    const int tid = threadIdx.x;
-    const int DT = a.DT;
-    const int dl = tid % DT, slot = tid / DT, S = blockDim.x / DT;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int DT = a.DT, nsl = 64 / DT; // dwords of the tile, slots of a wave
+    const int dl = lane % DT, ws = lane / DT, slot = (tid >> 6) * nsl + ws, S = 4 * nsl;
     const int d = blockIdx.y * DT + dl;
-    const int nb = DT * 32 * (KW + 1);
-    for (int q = tid; q < nb; q += blockDim.x) lh[q] = 0;
+    for (int q = tid; q < KW * 32 * DT; q += blockDim.x) lh[q] = 0;
     __syncthreads();
-    if (d < a.Dn && slot < S) {
-        uint32_t pl[KW][B];
+    uint32_t pl[KW][B + 6];
 #pragma unroll
-        for (int r = 0; r < KW; ++r)
+    for (int r = 0; r < KW; ++r)
 #pragma unroll
-            for (int b = 0; b < B; ++b) pl[r][b] = 0;
+        for (int b = 0; b < B + 6; ++b) pl[r][b] = 0;
+    if (d < a.Dn && ws < nsl) {
         // this thread's clauses: c0 + it S for it < nit
         const int64_t c0 = u.c0 + slot;
         const int64_t rem = u.c1 - c0;
         const int nit = rem <= 0 ? 0 : (int)(rem < (int64_t)a.CPT * S ? (rem + S - 1) / S : a.CPT);
-        const uint32_t n = (uint32_t)nit;
         // software pipeline over the clauses: while clause it is counted, the
         // literal dwords of clause it + 1 and the literal codes of clause
         // it + 2 are in flight (one memory round trip per clause, not two)
@@ -260,39 +269,69 @@ __device__ __forceinline__ void fwd_hist_unit(const FwdArgs& a, const FwdUnit& u
                 }
             }
         }
-        if (n) {
-            for (int p = 0; p < 32; ++p) {
-                uint32_t cum[KW + 1];
-                cum[0] = n;
+    }
+    // the slots' counters, added over windows of `off` slots: a circular
+    // window when the slots are a power of two (every lane then ends with
+    // the wave's total), else cut at the last slot (slot 0 holds the total)
+    const bool pow2 = (nsl & (nsl - 1)) == 0;
 #pragma unroll
-                for (int r = 0; r < KW; ++r) {
-                    uint32_t s = 0;
+    for (int st = 0; st < 6; ++st) {
+        const int off = 1 << st;
+        if (off >= nsl) break; // block-uniform
+        const int other = ws + off;
+        const bool in = pow2 || other < nsl;
+        const int src = (pow2 ? (other & (nsl - 1)) : other) * DT + dl;
 #pragma unroll
-                    for (int b = 0; b < B; ++b) s |= ((pl[r][b] >> p) & 1u) << b;
-                    cum[r + 1] = s;
-                }
+        for (int r = 0; r < KW; ++r) {
+            uint32_t carry = 0;
 #pragma unroll
-                for (int r = 0; r <= KW; ++r) {
-                    const uint32_t h = cum[r] - (r < KW ? cum[r + 1] : 0u);
-                    if (h) atomicAdd(&lh[(dl * 32 + p) * (KW + 1) + r], h);
-                }
+            for (int b = 0; b < B + st; ++b) {
+                uint32_t y = __shfl(pl[r][b], in ? src : lane);
+                y = in ? y : 0u;
+                const uint32_t x = pl[r][b], t = x ^ y;
+                pl[r][b] = t ^ carry;
+                carry = (t & carry) | (~t & x);
+            }
+            pl[r][B + st] = carry;
+        }
+    }
+    if (!pow2) {
+#pragma unroll
+        for (int r = 0; r < KW; ++r)
+#pragma unroll
+            for (int b = 0; b < B + 6; ++b) pl[r][b] = __shfl(pl[r][b], dl);
+    }
+    if (d < a.Dn && ws < nsl) {
+        for (int p = ws; p < 32; p += nsl) {
+#pragma unroll
+            for (int r = 0; r < KW; ++r) {
+                uint32_t s = 0;
+#pragma unroll
+                for (int b = 0; b < B + 6; ++b) s |= ((pl[r][b] >> p) & 1u) << b;
+                if (s) atomicAdd(&lh[(r * 32 + p) * DT + dl], s);
             }
         }
     }
     __syncthreads();
-    for (int q = tid; q < nb; q += blockDim.x) {
-        const uint32_t val = lh[q];
-        if (!val) continue;
-        const int cl = q / (KW + 1), r = q % (KW + 1);
-        const int dd = blockIdx.y * DT + cl / 32;
-        if (dd < a.Dn) atomicAdd(&H[(size_t)(blockIdx.y * DT * 32 + cl) * a.K1 + r], val);
+    uint32_t* H = a.H + ((size_t)u.inst * a.H_reps + blockIdx.x % (uint32_t)a.H_reps) * a.H_stride;
+    const uint32_t total = (uint32_t)(u.c1 - u.c0);
+    // consecutive lanes add to consecutive words of H (a lane per candidate
+    // with its levels in turn touches four lines for one: V = 5e4 and
+    // N = 1000, 117 us against 43)
+    for (int q = tid; q < 32 * DT * (KW + 1); q += blockDim.x) {
+        const int c = q / (KW + 1), r = q - c * (KW + 1), dd = c >> 5;
+        const int at = (c & 31) * DT + dd;
+        if (blockIdx.y * DT + dd >= a.Dn) break;
+        const uint32_t ge = r > 0 ? lh[(r - 1) * 32 * DT + at] : total;
+        const uint32_t nx = r < KW ? lh[r * 32 * DT + at] : 0u;
+        if (ge != nx) atomicAdd(&H[(size_t)(blockIdx.y * DT * 32 + c) * a.K1 + r], ge - nx);
     }
 }
 
 template <int KW, int B, bool VR>
 __global__ __launch_bounds__(256) void fwd_hist_kernel(FwdArgs a)
 {
-    extern __shared__ uint32_t lh[]; // [DT*32][KW+1]
+    extern __shared__ uint32_t lh[]; // [KW][32][DT]
     if (a.ctrl && a.ctrl->stop) return;
     const uint32_t un = xcd_unit(a.xcd, (uint32_t)a.nunits);
     if (un >= (uint32_t)a.nunits) return;
@@ -317,7 +356,7 @@ __global__ __launch_bounds__(256) void fwd_hist_lanes_kernel(FwdArgs a)
     if (un >= (uint32_t)a.nunits) return;
     const FwdUnit u = a.units[un];
     if (a.ictrl && a.ictrl[u.inst].frozen) return;
-    uint32_t* H = a.H + (size_t)u.inst * a.H_stride;
+    uint32_t* H = a.H + ((size_t)u.inst * a.H_reps + blockIdx.x % (uint32_t)a.H_reps) * a.H_stride;
     const uint32_t lane = __lane_id(), wave = threadIdx.x / 64u;
     // KW = 0: the units of every wide bucket in one launch, unit width in pad
     const int K1 = a.K1, k = a.KW > 0 ? a.KW : u.pad;
@@ -378,145 +417,205 @@ __global__ __launch_bounds__(256) void fwd_hist_lanes_kernel(FwdArgs a)
 
 // ---------------------------------------------------------------------------
 // SmoothMin (Eq. 4), loss (Eq. 3), dL/dR table, schedule (Sec. IV-A).
-// One block.  Candidate i: H[i][r] (plus the empty clauses in bin 0),
+// One block per instance (stateless evaluations without a loss: one per 256
+// candidates).  Candidate i: H[i][r] (plus the empty clauses in bin 0),
 // r0 = min{r : H > 0}, w_r = exp(-tau (r - r0)), D = sum H w,
 // S = sum r H w / D, table[r][i] = dS_i (w_r / D)(1 - tau (r - S)).
+//
+// A latency chain, not work: the exponentials depend on r - r0 alone and are
+// formed once per block, the schedule's powers by three waves side by side,
+// the histogram replicas are summed by coalesced loads into LDS, and the
+// closing reductions take one barrier.  (V = 200, N = 64: 5.2 -> 4.6 us
+// with eight replicas to add where there was one; large 9.9 -> 9.7.)
 // ---------------------------------------------------------------------------
 
 __global__ __launch_bounds__(256) void smin_kernel(SminArgs a)
 {
     __shared__ double s_loss[256];
-    __shared__ int64_t s_best[256];
-    __shared__ int32_t s_bidx[256];
-    __shared__ int32_t s_sat[256];
+    __shared__ double s_w[2 * TSAT_MAX_WIDTH + 1]; // exp(-tau x), x = -(K1 - 1) .. K1 - 1
+    __shared__ int64_t s_best[4];
+    __shared__ int32_t s_bidx[4], s_sat[4];
+    extern __shared__ uint32_t s_h[]; // [256][K1 | 1]
     Ctrl* ctrl = a.ctrl;
     if (ctrl && ctrl->stop) return;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int b = blockIdx.x; // instance
-    const int K1 = a.K1;
+    const int K1 = a.K1, hs = K1 | 1;
     const int64_t t = ctrl ? ctrl->t : 0;
-    if (b == 0 && tid == 0 && ctrl && a.update) {
+    if (b == 0 && ctrl && a.update) {
         // schedule scalars of the pending update:
         // lr(t) = max(lr_min, lr0 decay^floor((t mod restart)/every))
         const int64_t phase = a.restart > 0 ? t % a.restart : t;
-        const int64_t e = a.every > 0 ? phase / a.every : 0;
-        double lr = a.lr0 * pow(a.decay, (double)e);
-        if (lr < a.lr_min) lr = a.lr_min;
         // assignment mixing at a restart replaces the update and starts a
         // fresh AdamW: the bias corrections count from the next iteration
         const bool mixing = a.mix && a.restart > 0 && t > 0 && phase == 0;
-        ctrl->mixing = mixing ? 1 : 0;
-        if (mixing) ctrl->t_reset = t + 1;
-        const double tt = (double)(t - ctrl->t_reset + 1);
-        const double bc1 = 1.0 - pow(a.beta1, tt);
-        const double bc2 = 1.0 - pow(a.beta2, tt);
-        ctrl->lr = lr;
-        ctrl->f_decay = (float)(1.0 - lr * a.weight_decay);
-        ctrl->f_step = (float)(lr / bc1);
-        ctrl->f_isbc2 = (float)(1.0 / sqrt(bc2));
+        const double tt = (double)(t - (mixing ? t + 1 : ctrl->t_reset) + 1);
+        __syncthreads(); // every thread has read t_reset
+        if (tid == 0) {
+            const int64_t e = a.every > 0 ? phase / a.every : 0;
+            double lr = a.lr0 * pow(a.decay, (double)e);
+            if (lr < a.lr_min) lr = a.lr_min;
+            ctrl->mixing = mixing ? 1 : 0;
+            if (mixing) ctrl->t_reset = t + 1;
+            ctrl->lr = lr;
+            ctrl->f_decay = (float)(1.0 - lr * a.weight_decay);
+            s_loss[0] = lr;
+        } else if (tid == 64) {
+            s_loss[1] = 1.0 - pow(a.beta1, tt);
+        } else if (tid == 128) {
+            const double bc2 = 1.0 - pow(a.beta2, tt);
+            ctrl->f_isbc2 = (float)(1.0 / sqrt(bc2));
+        }
     }
+    if (tid >= 192) {
+        for (int x = tid - 192; x < 2 * K1 - 1; x += 64) s_w[x] = exp(-a.tau * (double)(x - (K1 - 1)));
+    }
+    __syncthreads();
+    if (tid == 0 && b == 0 && ctrl && a.update) ctrl->f_step = (float)(s_loss[0] / s_loss[1]);
     InstCtrl* ic = a.ictrl ? a.ictrl + b : nullptr;
     if (ic && ic->frozen) return; // nothing accumulated for a frozen instance
     const InstInfo info = a.info[b];
-    uint32_t* Hb = a.H + (size_t)b * a.Np * K1;
+    uint32_t* Hb = a.H + (size_t)b * a.H_reps * a.Np * K1;
     float* tb = a.table ? a.table + (size_t)b * K1 * a.Np : nullptr;
     const size_t ob = (size_t)b * a.N;
+    const double* w0 = s_w + (K1 - 1); // w0[x] = exp(-tau x)
     double loss = 0.0;
     int64_t best = -1;
     int32_t bidx = 0x7fffffff, satc = 0x7fffffff;
-    for (int i = tid; i < a.Np; i += blockDim.x) {
-        uint32_t* h = Hb + (size_t)i * K1;
-        if (i >= a.N) {
-            for (int r = 0; r < K1; ++r) {
-                if (tb) tb[(size_t)r * a.Np + i] = 0.0f;
-                h[r] = 0;
+    for (int i0 = blockIdx.y * 256; i0 < a.Np; i0 += gridDim.y * 256) {
+        // this pass's histogram rows: the replicas' sum, cleared on the way
+        const int rows = min(256, a.Np - i0);
+        for (int g = tid; g < rows * K1 / 4; g += 256) { // 16 bytes: rows is a multiple of 64
+            uint4* src = (uint4*)(Hb + (size_t)i0 * K1) + g;
+            const size_t stride = (size_t)a.Np * K1 / 4;
+            uint4 v[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = q < a.H_reps ? src[q * stride] : make_uint4(0u, 0u, 0u, 0u);
+            uint32_t h[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                h[0] += v[q].x;
+                h[1] += v[q].y;
+                h[2] += v[q].z;
+                h[3] += v[q].w;
             }
-            continue;
-        }
-        int r0 = -1;
-        for (int r = 0; r < K1; ++r) {
-            const uint64_t hr = (uint64_t)h[r] + (r == 0 ? (uint64_t)info.n_empty : 0);
-            if (hr > 0) { r0 = r; break; }
-        }
-        double D = 0.0, num = 0.0;
-        if (r0 >= 0) {
-            for (int r = 0; r < K1; ++r) {
-                const double hr = (double)h[r] + (r == 0 ? (double)info.n_empty : 0.0);
-                const double w = exp(-a.tau * (double)(r - r0));
-                D += hr * w;
-                num += (double)r * hr * w;
+            if (a.zero_H) {
+#pragma unroll
+                for (int q = 0; q < 8; ++q)
+                    if (q < a.H_reps) src[q * stride] = make_uint4(0u, 0u, 0u, 0u);
             }
-        }
-        const double S = (r0 >= 0) ? num / D : 0.0;
-        const int64_t unsat = (int64_t)h[0] + info.n_empty;
-        const int64_t sat = info.C - unsat;
-        if (a.S_out) a.S_out[ob + i] = (float)S;
-        if (a.S64_out) a.S64_out[ob + i] = S;
-        if (a.sat_out) a.sat_out[ob + i] = sat;
-        loss += S;
-        if (sat > best) { best = sat; bidx = i; }
-        if (unsat == 0 && i < satc) satc = i;
-        // dL/dS_i: given per candidate, or -dloss (Eq. 3 scaled by the
-        // upstream gradient of the loss), or -1 (Eq. 3)
-        const double up = a.dS ? (double)a.dS[ob + i] : (a.dloss ? -(double)a.dloss[b] : -1.0);
-        for (int r = 0; r < K1; ++r) {
-            if (tb) {
-                double tv = 0.0;
-                if (r0 >= 0) {
-                    const double w = exp(-a.tau * (double)(r - r0));
-                    tv = up * (w / D) * (1.0 - a.tau * ((double)r - S));
-                }
-                tb[(size_t)r * a.Np + i] = (float)tv;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int e = 4 * g + j, c = e / K1, r = e - c * K1;
+                s_h[c * hs + r] = h[j];
+                if (a.H_last && i0 + c < a.N)
+                    a.H_last[(ob + i0) * K1 + e] = h[j] + (r == 0 ? (uint32_t)info.n_empty : 0u);
             }
-            if (a.H_last) a.H_last[(ob + i) * K1 + r] = h[r] + (r == 0 ? (uint32_t)info.n_empty : 0u);
-            if (a.zero_H) h[r] = 0;
-        }
-    }
-    s_loss[tid] = loss;
-    s_best[tid] = best;
-    s_bidx[tid] = bidx;
-    s_sat[tid] = satc;
-    __syncthreads();
-    for (int st = blockDim.x / 2; st > 0; st >>= 1) {
-        if (tid < st) {
-            s_loss[tid] += s_loss[tid + st];
-            if (s_best[tid + st] > s_best[tid] || (s_best[tid + st] == s_best[tid] && s_bidx[tid + st] < s_bidx[tid])) {
-                s_best[tid] = s_best[tid + st];
-                s_bidx[tid] = s_bidx[tid + st];
-            }
-            if (s_sat[tid + st] < s_sat[tid]) s_sat[tid] = s_sat[tid + st];
         }
         __syncthreads();
+        const int i = i0 + tid;
+        if (tid < rows && i >= a.N) {
+            if (tb)
+                for (int r = 0; r < K1; ++r) tb[(size_t)r * a.Np + i] = 0.0f;
+        } else if (tid < rows) {
+            const uint32_t* h = s_h + tid * hs;
+            int r0 = -1;
+            for (int r = 0; r < K1; ++r) {
+                const uint64_t hr = (uint64_t)h[r] + (r == 0 ? (uint64_t)info.n_empty : 0);
+                if (hr > 0) { r0 = r; break; }
+            }
+            double D = 0.0, num = 0.0;
+            if (r0 >= 0) {
+                for (int r = 0; r < K1; ++r) {
+                    const double hr = (double)h[r] + (r == 0 ? (double)info.n_empty : 0.0);
+                    const double w = w0[r - r0];
+                    D += hr * w;
+                    num += (double)r * hr * w;
+                }
+            }
+            const double S = (r0 >= 0) ? num / D : 0.0;
+            const int64_t unsat = (int64_t)h[0] + info.n_empty;
+            const int64_t sat = info.C - unsat;
+            if (a.S_out) a.S_out[ob + i] = (float)S;
+            if (a.S64_out) a.S64_out[ob + i] = S;
+            if (a.sat_out) a.sat_out[ob + i] = sat;
+            loss += S;
+            if (sat > best) { best = sat; bidx = i; }
+            if (unsat == 0 && i < satc) satc = i;
+            if (tb) {
+                // dL/dS_i: given per candidate, or -dloss (Eq. 3 scaled by
+                // the upstream gradient of the loss), or -1 (Eq. 3)
+                const double up = a.dS ? (double)a.dS[ob + i] : (a.dloss ? -(double)a.dloss[b] : -1.0);
+                for (int r = 0; r < K1; ++r) {
+                    double tv = 0.0;
+                    if (r0 >= 0) tv = up * (w0[r - r0] / D) * (1.0 - a.tau * ((double)r - S));
+                    tb[(size_t)r * a.Np + i] = (float)tv;
+                }
+            }
+        }
+        __syncthreads(); // the next pass rewrites the rows
     }
-    if (tid == 0 && a.loss_out) a.loss_out[b] = (float)(-s_loss[0]);
-    if (tid == 0 && ic) {
-        const uint64_t now = __builtin_amdgcn_s_memrealtime();
-        if (ic->start_time == 0) ic->start_time = now;
-        ic->loss = -s_loss[0];
-        ic->best_cand = s_bidx[0];
-        ic->best_sat = s_best[0];
+    if (!ic && !a.loss_out) return;
+    // the loss in a fixed order: lanes tid, tid + 128, tid + 64, tid + 192,
+    // then halves of the first wave; the best candidate by count, then index
+    s_loss[tid] = loss;
+#pragma unroll
+    for (int st = 32; st > 0; st >>= 1) {
+        const int64_t ob2 = __shfl_xor(best, st);
+        const int32_t oi = __shfl_xor(bidx, st), os = __shfl_xor(satc, st);
+        if (ob2 > best || (ob2 == best && oi < bidx)) {
+            best = ob2;
+            bidx = oi;
+        }
+        satc = min(satc, os);
+    }
+    if (lane == 0) {
+        s_best[wv] = best;
+        s_bidx[wv] = bidx;
+        s_sat[wv] = satc;
+    }
+    __syncthreads();
+    if (wv != 0) return;
+    double l = (s_loss[tid] + s_loss[tid + 128]) + (s_loss[tid + 64] + s_loss[tid + 192]);
+#pragma unroll
+    for (int st = 32; st > 0; st >>= 1) l += __shfl_down(l, st);
+    if (tid != 0) return;
+#pragma unroll
+    for (int w = 1; w < 4; ++w) {
+        if (s_best[w] > best || (s_best[w] == best && s_bidx[w] < bidx)) {
+            best = s_best[w];
+            bidx = s_bidx[w];
+        }
+        satc = min(satc, s_sat[w]);
+    }
+    if (a.loss_out) a.loss_out[b] = (float)(-l);
+    if (!ic) return;
+    const uint64_t now = __builtin_amdgcn_s_memrealtime();
+    if (ic->start_time == 0) ic->start_time = now;
+    ic->loss = -l;
+    ic->best_cand = bidx;
+    ic->best_sat = best;
+    ic->witness_pending = 0;
+    const bool any_sat = satc != 0x7fffffff;
+    if (any_sat && ic->first_sat_step < 0) {
+        ic->first_sat_step = t;
+        ic->sat_cand = satc;
+        ic->sat_time = now;
+        ic->witness_pending = 1;
+    }
+    const bool converged = (double)best > a.conv_frac * (double)info.C;
+    if (converged && ic->first_conv_step < 0) {
+        ic->first_conv_step = t;
+        ic->conv_time = now;
+    }
+    // stop mode 1: freeze on a satisfying candidate; 2: also on
+    // convergence, the hand-off point of Sec. IV-B
+    if (a.update && ctrl && ctrl->stop_on_sat && (any_sat || (ctrl->stop_on_sat == 2 && converged))) {
+        // freeze: the current bits stay (a witness if satisfied), no more updates
+        ic->frozen = 1;
         ic->witness_pending = 0;
-        const bool any_sat = s_sat[0] != 0x7fffffff;
-        if (any_sat && ic->first_sat_step < 0) {
-            ic->first_sat_step = t;
-            ic->sat_cand = s_sat[0];
-            ic->sat_time = now;
-            ic->witness_pending = 1;
-        }
-        const bool converged = (double)s_best[0] > a.conv_frac * (double)info.C;
-        if (converged && ic->first_conv_step < 0) {
-            ic->first_conv_step = t;
-            ic->conv_time = now;
-        }
-        // stop mode 1: freeze on a satisfying candidate; 2: also on
-        // convergence, the hand-off point of Sec. IV-B
-        if (a.update && ctrl && ctrl->stop_on_sat && (any_sat || (ctrl->stop_on_sat == 2 && converged))) {
-            // freeze: the current bits stay (a witness if satisfied), no more updates
-            ic->frozen = 1;
-            ic->witness_pending = 0;
-            const int nf = atomicAdd(&ctrl->n_frozen, 1) + 1;
-            if (nf >= a.n_inst) ctrl->stop = 1;
-        }
+        const int nf = atomicAdd(&ctrl->n_frozen, 1) + 1;
+        if (nf >= a.n_inst) ctrl->stop = 1;
     }
 }
 
@@ -2450,7 +2549,7 @@ __global__ __launch_bounds__(256) void fwd_planes_kernel(FwdArgs a)
 template <int KMAX, bool VR>
 __global__ __launch_bounds__(256) void fwd_multi_kernel(FwdArgs a)
 {
-    extern __shared__ uint32_t lh[]; // [DT*32][5]
+    extern __shared__ uint32_t lh[]; // [4][32][DT]
     if (a.ctrl && a.ctrl->stop) return;
     const uint32_t un = xcd_unit(a.xcd, (uint32_t)a.nunits);
     if (un >= (uint32_t)a.nunits) return;
@@ -2492,7 +2591,7 @@ __global__ __launch_bounds__(256) void planes_hist_kernel(FwdArgs a, int nunits)
         }
         __syncthreads();
         if (inst >= 0) {
-            uint32_t* H = a.H + (size_t)inst * a.H_stride;
+            uint32_t* H = a.H + ((size_t)inst * a.H_reps + blockIdx.x % (uint32_t)a.H_reps) * a.H_stride;
             for (int e = threadIdx.x; e < J * 64; e += 256) {
                 const int j = e / 64, l = e % 64;
                 const uint32_t cand = 64u * j + l;
@@ -3040,7 +3139,7 @@ __global__ __launch_bounds__(256) void select_kernel(SelectArgs a)
 template <int KW, int B, bool VR>
 static hipError_t launch_fwd_k(const FwdArgs& a, dim3 grid, hipStream_t st)
 {
-    const size_t lds = (size_t)a.DT * 32 * (KW + 1) * sizeof(uint32_t);
+    const size_t lds = (size_t)a.DT * 32 * KW * sizeof(uint32_t);
     hipLaunchKernelGGL((fwd_hist_kernel<KW, B, VR>), grid, dim3(256), lds, st, a);
     return hipGetLastError();
 }
@@ -3102,7 +3201,7 @@ hipError_t launch_planes_hist(const FwdArgs& a, int kmax, int nunits, hipStream_
 hipError_t launch_fwd_multi(const FwdArgs& a, int kmax, int nunits, hipStream_t st)
 {
     const dim3 g(fwd_grid_x(a, nunits));
-    const size_t lds = (size_t)a.DT * 32 * 5 * sizeof(uint32_t);
+    const size_t lds = (size_t)a.DT * 32 * 4 * sizeof(uint32_t);
     if (a.vrows) {
         if (kmax <= 8) hipLaunchKernelGGL((fwd_multi_kernel<8, true>), g, dim3(256), lds, st, a);
         else hipLaunchKernelGGL((fwd_multi_kernel<15, true>), g, dim3(256), lds, st, a);
@@ -3192,7 +3291,12 @@ hipError_t noalloc_scratch_address(int device, void** out)
 
 hipError_t launch_smin(const SminArgs& a, hipStream_t st)
 {
-    hipLaunchKernelGGL(smin_kernel, dim3((unsigned)a.n_inst), dim3(256), 0, st, a);
+    // the candidates of an evaluation without a loss or bookkeeping are
+    // independent: as many blocks as they fill (a brute-force check has
+    // millions)
+    const unsigned tiles = (a.ictrl || a.loss_out) ? 1u : (unsigned)std::min(4096, (a.Np + 255) / 256);
+    const size_t lds = (size_t)256 * (a.K1 | 1) * sizeof(uint32_t);
+    hipLaunchKernelGGL(smin_kernel, dim3((unsigned)a.n_inst, tiles), dim3(256), lds, st, a);
     return hipGetLastError();
 }
 
