@@ -522,7 +522,8 @@ typedef struct {
                                   follows from it); default 1024 */
     int32_t var_blocks_per_cu; /* fused update: persistent blocks per CU, 0 = 4 x occupancy */
     int32_t pure_group;        /* uniform-width stores: occurrence records per load group, 1, 2 or 4 */
-    int32_t clause_planes;     /* uniform widths 2, 3 and N <= 256: 1 = the forward stores R of every
+    int32_t clause_planes;     /* uniform widths 2, 3 (other widths up to 15 at N <= 256, with the window
+                                  gather): 1 = the forward stores R of every
                                   clause in binary and the update gathers it (one record per
                                   occurrence), 0 = the update gathers the other literals' rows */
     int32_t window_gather;     /* with clause planes: 1 = the update loads the planes of 64 consecutive

@@ -271,8 +271,9 @@ static size_t hist_words(const tsat_solver* s, int32_t Np)
     return (size_t)s->st.n_inst * K1_of(s) * (size_t)std::max(Np, hist_reps(s, small) * small);
 }
 
-// Words per candidate row the update kernels use for W words (a power of two).
-static int32_t row_words(int32_t W) { return W <= 2 ? W : (W <= 4 ? 4 : (W <= 8 ? 8 : 16)); }
+// Words per plane row the update kernels use for W words: the words of one
+// wave's rows, or four per wave of a team.
+static int32_t row_words(int32_t W) { return W <= 2 ? W : (W + 3) / 4 * 4; }
 
 static bool uniform_plane_store(const tsat_solver* s) { return s->st.pure_k == 2 || s->st.pure_k == 3; }
 
@@ -287,14 +288,20 @@ static size_t levels_lds_bytes(const tsat_solver* s, int32_t J)
 }
 
 // The clause-plane update applies: clause-index records exist (widths up to
-// kMaxPlaneWidth), at most 256 candidates, and, beyond uniform widths 2 and
-// 3 (which also have a record-by-record plane gather), the window gather
-// with its 16-bit counts and LDS budget.
+// kMaxPlaneWidth) and, beyond uniform widths 2 and 3 at N <= 256 (which also
+// have a record-by-record plane gather), the window gather is on and its
+// 16-bit counts hold; mixed widths up to 256 candidates and within the
+// kernel's LDS budget, uniform widths 2 and 3 up to TSAT_MAX_STEP_N (the row
+// gather took 2.35 ms per launch at V = 5e4, C = 2.05e5, N = 1000 where the
+// teams of waves take 0.36).
 static bool plane_path(const tsat_solver* s, int32_t N)
 {
-    if (!s->clause_planes || !s->occ_cid.p || (N + 63) / 64 > 4) return false;
+    const int32_t W = (N + 63) / 64;
+    if (!s->clause_planes || !s->occ_cid.p || N > TSAT_MAX_STEP_N) return false;
+    if (uniform_plane_store(s) && W <= 4) return true;
+    if (!s->window_gather || s->st.max_sign_rec >= 65536) return false;
     if (uniform_plane_store(s)) return true;
-    return s->window_gather && s->st.max_sign_rec < 65536 && levels_lds_bytes(s, row_words((N + 63) / 64)) <= 65536;
+    return W <= 4 && levels_lds_bytes(s, row_words(W)) <= 65536;
 }
 
 // Uniform widths 2 and 3 with the window gather at N <= 32: the update takes
@@ -962,7 +969,7 @@ static int32_t alloc_batch(tsat_solver* s, int32_t N)
     if (s->lit_rows_req) {
         // independent literal rows run only on the window gather of the
         // forward's clause planes
-        if (!plane_path(s, N))
+        if (N > 256 || !plane_path(s, N))
             return fail(TSAT_E_ARG, "independent literal rows need the clause-plane window gather: N <= 256, "
                                     "clauses at most %d wide, clause planes and the window gather on", kMaxPlaneWidth);
     }
@@ -2039,7 +2046,14 @@ int32_t tsat_autotune(tsat_solver* s, int32_t iters, const tsat_params* p, tsat_
     // then take few chunks each, and the chip walks the variables in order)
     static const int kPerCu[] = {0, 8, 16, 32, 64, 128, 256, 512, 1024};
     const bool pure = s->st.pure_k != 0;
-    const bool planes_apply = s->occ_cid.p && (s->N + 63) / 64 <= 4;
+    bool planes_apply;
+    {
+        const int32_t cp = s->clause_planes, wg = s->window_gather;
+        s->clause_planes = s->window_gather = 1;
+        planes_apply = plane_path(s, s->N);
+        s->clause_planes = cp;
+        s->window_gather = wg;
+    }
     static const int kGroups[] = {1, 2, 4};
     double best_var = 1e30, best_sum = 1e30;
     tsat_launch_config pick = cur;
@@ -2048,7 +2062,7 @@ int32_t tsat_autotune(tsat_solver* s, int32_t iters, const tsat_params* p, tsat_
     // planes, so the shapes are compared on forward + update time
     for (int cp = planes_apply ? 1 : 0; cp >= (s->rows_per_var == 2 ? 1 : 0); --cp) {
         const int ngroups = (pure && !cp) ? 3 : 1;
-        const int nwin = (cp && uniform_plane_store(s) && s->rows_per_var == 1) ? 2 : 1;
+        const int nwin = (cp && uniform_plane_store(s) && s->rows_per_var == 1 && s->N <= 256) ? 2 : 1;
         for (int pc : kPerCu) {
             for (int gi = 0; gi < ngroups; ++gi) {
                 for (int wi = 0; wi < nwin; ++wi) {

@@ -99,6 +99,26 @@ __device__ __forceinline__ double wave_sum(double x)
     return (r0 + r1) + (r2 + r3);
 }
 
+// Sum of a row held by one wave (lane l: candidates 64 j + l), x[j] a lane's
+// terms.  Rows of more than four words are summed in groups of four words,
+// group after group: the order in which a team of waves, four words each,
+// adds its shares (var_window_team_kernel), so that every kernel forms the
+// same sums.
+template <int J, class F>
+__device__ __forceinline__ double row_sum(F x)
+{
+    double total = 0.0;
+#pragma unroll
+    for (int j0 = 0; j0 < J; j0 += 4) {
+        double s = 0.0;
+#pragma unroll
+        for (int j = j0; j < (J < j0 + 4 ? J : j0 + 4); ++j) s += x(j);
+        s = wave_sum(s);
+        total = j0 == 0 ? s : total + s;
+    }
+    return total;
+}
+
 // Sum over each half wave (lanes 0-31, 32-63), returned to the lanes of that
 // half.  A half holding a row of at most 32 values gets the wave_sum value
 // of that row alone (there, the other half adds only zeros).
@@ -713,10 +733,7 @@ __device__ __forceinline__ void norm_backward_row(const VarArgs& a, const float 
                                                   double mu, bool clamped, float (&g)[J])
 {
     if (a.mode == 1) {
-        double ut = 0.0;
-#pragma unroll
-        for (int j = 0; j < J; ++j) ut += U[j] * (double)th[j];
-        ut = wave_sum(ut);
+        const double ut = row_sum<J>([&](int j) { return U[j] * (double)th[j]; });
         const double inv_mu = 1.0 / mu;
         const double corr = clamped ? 0.0 : ut * inv_mu * inv_mu * a.inv_n;
 #pragma unroll
@@ -759,7 +776,6 @@ __device__ __forceinline__ void var_tail(const VarArgs& a, const StepScalars& c,
         return;
     }
     // AdamW (decoupled weight decay), FP32 with FP64-derived scalars
-    double s2 = 0.0;
 #pragma unroll
     for (int j = 0; j < J; ++j) {
         const size_t idx = (size_t)v * N + 64 * j + lane;
@@ -776,12 +792,11 @@ __device__ __forceinline__ void var_tail(const VarArgs& a, const StepScalars& c,
             __builtin_nontemporal_store(mm, a.m + idx);
             __builtin_nontemporal_store(vv, a.v + idx);
         }
-        s2 += (double)th[j];
     }
     if (witness && lane == 0 && !a.lit_rows) a.witness[v] = (uint8_t)((oP[wcand >> 6] >> (wcand & 63)) & 1u);
     bool pos = true;
     if (a.mode == 1) {
-        const double mu2 = wave_sum(s2) * a.inv_n;
+        const double mu2 = row_sum<J>([&](int j) { return (double)th[j]; }) * a.inv_n;
         if (lane == 0) a.mu_next[v] = mu2;
         pos = mu2 >= 0.0; // the clamp maps a zero mean to +1e-12
     }
@@ -873,9 +888,9 @@ __device__ __forceinline__ void advance_step(const VarArgs& a)
 template <int J>
 __device__ void mix_rows(const VarArgs& a)
 {
-    const uint32_t lane = __lane_id();
-    const uint32_t wave0 = uniform(blockIdx.x * 4u + threadIdx.x / 64u);
-    const uint32_t nwaves = uniform(gridDim.x * 4u);
+    const uint32_t lane = __lane_id(), wpb = blockDim.x / 64u;
+    const uint32_t wave0 = uniform(blockIdx.x * wpb + threadIdx.x / 64u);
+    const uint32_t nwaves = uniform(gridDim.x * wpb);
     const int N = a.N, W = a.W;
     for (uint32_t v = wave0; v < (uint32_t)a.V; v += nwaves) {
         const VarInst vi = var_instance<OP_STEP>(a, v);
@@ -888,7 +903,6 @@ __device__ void mix_rows(const VarArgs& a)
         const double star = (double)row[best]; // same address in every lane
         float th[J];
         bool valid[J];
-        double s = 0.0;
 #pragma unroll
         for (int j = 0; j < J; ++j) {
             const int i = 64 * j + (int)lane;
@@ -902,7 +916,6 @@ __device__ void mix_rows(const VarArgs& a)
                 __builtin_nontemporal_store(0.f, a.m + idx);
                 __builtin_nontemporal_store(0.f, a.v + idx);
             }
-            s += (double)x;
         }
         if (vi.witness && lane == 0 && !a.lit_rows) {
             const uint64_t w = a.lits_cur[(size_t)(2 * v) * W + (vi.wcand >> 6)];
@@ -910,7 +923,7 @@ __device__ void mix_rows(const VarArgs& a)
         }
         bool pos = true;
         if (a.mode == 1) {
-            const double mu2 = wave_sum(s) * a.inv_n;
+            const double mu2 = row_sum<J>([&](int j) { return (double)th[j]; }) * a.inv_n;
             if (lane == 0) a.mu_next[v] = mu2;
             pos = mu2 >= 0.0;
         }
@@ -929,19 +942,17 @@ __global__ __launch_bounds__(256) void binarize_kernel(VarArgs a)
     for (uint32_t v = wave0; v < (uint32_t)a.V; v += nwaves) {
         float th[J];
         bool valid[J];
-        double s = 0.0;
 #pragma unroll
         for (int j = 0; j < J; ++j) {
             const int i = 64 * j + (int)lane;
             valid[j] = i < a.N;
             th[j] = valid[j] ? a.theta[(size_t)v * a.N + i] : 0.f;
-            s += (double)th[j];
         }
         bool pos = true;
         if (a.mode == 1) {
             // the same arithmetic as the update's new row mean, so that a
             // state set from a checkpoint binarizes exactly as the run did
-            const double mu = wave_sum(s) * a.inv_n;
+            const double mu = row_sum<J>([&](int j) { return (double)th[j]; }) * a.inv_n;
             if (lane == 0) a.mu_next[v] = mu;
             pos = mu >= 0.0;
         } else if (lane == 0) {
@@ -973,17 +984,16 @@ __global__ __launch_bounds__(256) void norm_backward_kernel(VarArgs a)
         float th[J];
         double U[J];
         bool valid[J];
-        double s = 0.0;
 #pragma unroll
         for (int j = 0; j < J; ++j) {
             const int i = 64 * j + (int)lane;
             valid[j] = i < a.N;
             th[j] = valid[j] ? a.theta[(size_t)v * a.N + i] : 0.f;
             U[j] = valid[j] ? (double)a.dA_in[(size_t)v * a.N + i] : 0.0;
-            s += (double)th[j];
         }
         bool clamped = false;
-        const double mu = a.mode == 1 ? clamp_mu(wave_sum(s) * a.inv_n, clamped) : 1.0;
+        const double mu =
+            a.mode == 1 ? clamp_mu(row_sum<J>([&](int j) { return (double)th[j]; }) * a.inv_n, clamped) : 1.0;
         float g[J];
         norm_backward_row<J>(a, th, U, mu, clamped, g);
 #pragma unroll
@@ -1963,6 +1973,253 @@ __global__ __launch_bounds__(256) void var_window_kernel(VarArgs a)
             double U[J];
             plane_u<J, KW>(cnt, rm - r0, r1 - rm, my_gt, lane, U);
             var_tail<J, OP>(a, c, v, lane, th, mm, vv, valid, mu, clamped, U, oP, vi.witness, vi.wcand, bad);
+        }
+    }
+    if (OP == OP_STEP) {
+        if (ballot64(bad != 0) && lane == 0) atomicOr(&a.ctrl->nonfinite, 1);
+        advance_step(a);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Window gather for rows of more than four words (256 < N <= 1024): a block
+// is a team of ceil(W / 4) waves, each holding four words (256 candidates)
+// of the rows, so that a wave keeps the window, table and registers of
+// var_window_kernel<4>.  The team takes three consecutive variables at a
+// time: every wave requests its share of their rows, counts their records,
+// and the two row sums of each variable (Eq. 5 backward, new mean) are added
+// over the team in LDS, all three variables between the same two barriers
+// (two variables 376 us, four 381).
+//
+// What bounds it: the theta, m, v streams and a plane row per record (V =
+// 5e4, C = 2.05e5, N = 1000: 1.2 GB and 0.16 GB a launch, 358 us = 3.8 TB/s,
+// a copy of 5.1).  The row gather of var_pure_kernel, which these sizes took
+// before, reads two literal rows of 128 bytes per record through the scalar
+// cache, one wave per variable: 2346 us.
+// ---------------------------------------------------------------------------
+
+// Planes of records [w, w + 64) as load_window<4>, of the four words from
+// word0 of clauses holding `words` words per plane.
+__device__ __forceinline__ void load_window_part(const VarArgs& a, uint32_t w, uint32_t end, uint32_t lane,
+                                                 uint32_t words, uint32_t word0, uint64_t* win)
+{
+    const uint32_t rec = w + lane;
+    const bool ok = rec < end;
+    const uint32_t id = ok ? a.occ_cid[rec] : 0u;
+    const uint64_t* pl = (const uint64_t*)a.planes + (size_t)id * (2u * words) + word0;
+    uint64_t wd[8];
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const uint4 q = ok ? ((const uint4*)(pl + p * words))[k] : make_uint4(0u, 0u, 0u, 0u);
+            wd[4 * p + 2 * k] = ((uint64_t)q.y << 32) | q.x;
+            wd[4 * p + 2 * k + 1] = ((uint64_t)q.w << 32) | q.z;
+        }
+    transpose64_n<8>(wd, lane);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) win[e * 64 + lane] = wd[e];
+}
+
+template <int KW, int OP>
+__global__ __launch_bounds__(256) void var_window_team_kernel(VarArgs a)
+{
+    if (OP == OP_STEP && a.ctrl->stop) {
+        copy_bits_on_stop(a);
+        return;
+    }
+    if (OP == OP_STEP && a.ctrl->mixing) {
+        mix_rows<16>(a);
+        return;
+    }
+    constexpr int K1 = KW + 1, J = 4;
+    constexpr int C = 3; // variables per team pass
+    const uint32_t lane = __lane_id();
+    const uint32_t wv = uniform(threadIdx.x / 64u), G = blockDim.x / 64u;
+    const uint32_t word0 = wv * J; // first word of this wave's share
+    const uint32_t V = (uint32_t)a.V;
+    const int W = a.W, N = a.N, Np = a.Np;
+    const StepScalars c = load_scalars(a, OP);
+    __shared__ float s_gt[4][K1 * J * 64];
+    __shared__ uint64_t s_win[4][2 * J * 64];
+    __shared__ double s_ut[C][4], s_mu[C][4]; // the waves' shares of the row sums
+    float* my_gt = s_gt[wv];
+    uint64_t* my_win = s_win[wv];
+    uint32_t gt_inst = 0xffffffffu;
+    int bad = 0;
+    bool valid[J];
+#pragma unroll
+    for (int j = 0; j < J; ++j) valid[j] = (int)(64u * (word0 + j) + lane) < N;
+    const bool sums = OP != OP_ADJ && a.mode == 1;
+    const uint32_t nchunks = (V + C - 1) / C;
+    for (uint32_t ch = blockIdx.x; ch < nchunks; ch += gridDim.x) { // block-uniform
+        const uint32_t vb = ch * C, nv = V - vb < C ? V - vb : C;
+        const uint32_t rend = sload(a.occ_off + vb + nv);
+        float th[C][J], mm[C][J], vv[C][J], g[C][J];
+        VarInst vi[C];
+#pragma unroll
+        for (int i = 0; i < C; ++i) {
+            if ((uint32_t)i < nv) vi[i] = var_instance<OP>(a, vb + i);
+            else vi[i].frozen = true;
+            const size_t row = (size_t)(vb + i) * N + 64u * word0 + lane;
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                const bool ld = (uint32_t)i < nv && valid[j];
+                th[i][j] = (OP != OP_ADJ && ld) ? __builtin_nontemporal_load(a.theta + row + 64 * j) : 0.f;
+            }
+        }
+        uint32_t w = 0;
+        bool loaded = false;
+#pragma unroll
+        for (int i = 0; i < C; ++i) {
+            if ((uint32_t)i >= nv) break;
+            const uint32_t v = vb + i;
+            if (vi[i].frozen) {
+                if (wv == 0) keep_variable<16>(a, v, lane);
+                continue;
+            }
+            if (vi[i].inst != gt_inst) {
+                gt_inst = vi[i].inst;
+                const float* tg = a.tbl + (size_t)gt_inst * K1 * Np;
+#pragma unroll
+                for (int r = 0; r < K1; ++r)
+#pragma unroll
+                    for (int j = 0; j < J; ++j)
+                        my_gt[(r * J + j) * 64 + lane] =
+                            (int)word0 + j < W ? tg[(size_t)r * Np + 64u * (word0 + j) + lane] : 0.f;
+            }
+            const uint32_t r0 = sload(a.occ_off + v), rm = sload(a.occ_mid + v), r1 = sload(a.occ_off + v + 1);
+            uint32_t cnt[KW][J];
+#pragma unroll
+            for (int r = 0; r < KW; ++r)
+#pragma unroll
+                for (int j = 0; j < J; ++j) cnt[r][j] = 0;
+            for (uint32_t q = r0; q < r1;) { // wave-uniform
+                if (!loaded || q - w >= 64u) {
+                    w = q;
+                    loaded = true;
+                    load_window_part(a, w, rend, lane, 4u * G, word0, my_win);
+                }
+                const uint32_t hi = r1 < w + 64u ? r1 : w + 64u;
+                const uint64_t mp = q < rm ? bit_range(q - w, (hi < rm ? hi : rm) - w) : 0ull;
+                const uint64_t mn = hi > rm ? bit_range((q > rm ? q : rm) - w, hi - w) : 0ull;
+#pragma unroll
+                for (int j = 0; j < J; ++j) {
+                    const uint64_t b0 = my_win[j * 64 + lane], b1 = my_win[(J + j) * 64 + lane];
+                    const uint64_t b01 = b0 | b1; // R >= 1 (b1: R >= 2)
+                    cnt[0][j] += (uint32_t)__popcll(b01 & mp) + ((uint32_t)__popcll(b01 & mn) << 16);
+                    cnt[1][j] += (uint32_t)__popcll(b1 & mp) + ((uint32_t)__popcll(b1 & mn) << 16);
+                    if constexpr (KW == 3) { // R = 3
+                        const uint64_t b3 = b0 & b1;
+                        cnt[2][j] += (uint32_t)__popcll(b3 & mp) + ((uint32_t)__popcll(b3 & mn) << 16);
+                    }
+                }
+                q = hi;
+            }
+            double U[J];
+            plane_u<J, KW>(cnt, rm - r0, r1 - rm, my_gt, lane, U);
+#pragma unroll
+            for (int j = 0; j < J; ++j) g[i][j] = (float)U[j]; // U is a float's value
+            if (sums) {
+                const double ut = row_sum<J>([&](int j) { return U[j] * (double)th[i][j]; });
+                if (lane == 0) s_ut[i][wv] = ut;
+            }
+        }
+        // the moments are requested here, not with theta: held through the
+        // counting they cost registers (415 us; 358 this way)
+#pragma unroll
+        for (int i = 0; i < C; ++i) {
+            const size_t row = (size_t)(vb + i) * N + 64u * word0 + lane;
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                const bool ld = OP == OP_STEP && (uint32_t)i < nv && valid[j];
+                mm[i][j] = ld ? __builtin_nontemporal_load(a.m + row + 64 * j) : 0.f;
+                vv[i][j] = ld ? __builtin_nontemporal_load(a.v + row + 64 * j) : 0.f;
+            }
+        }
+        if (sums) __syncthreads();
+#pragma unroll
+        for (int i = 0; i < C; ++i) {
+            if (vi[i].frozen) continue;
+            const uint32_t v = vb + i;
+            const size_t row = (size_t)v * N + 64u * word0 + lane;
+            if ((OP == OP_ADJ || OP == OP_GRAD) && a.U_out) {
+#pragma unroll
+                for (int j = 0; j < J; ++j)
+                    if (valid[j]) a.U_out[row + 64 * j] = g[i][j];
+            }
+            if (OP == OP_ADJ) continue;
+            if (a.mode == 1) {
+                bool clamped;
+                const double mu = clamp_mu(sload(a.mu_cur + v), clamped);
+                double ut = s_ut[i][0];
+                for (uint32_t k = 1; k < G; ++k) ut = ut + s_ut[i][k];
+                const double inv_mu = 1.0 / mu;
+                const double corr = clamped ? 0.0 : ut * inv_mu * inv_mu * a.inv_n;
+#pragma unroll
+                for (int j = 0; j < J; ++j) g[i][j] = (float)((double)g[i][j] * inv_mu - corr);
+            }
+            if (OP == OP_GRAD) {
+                if (a.g_out) {
+#pragma unroll
+                    for (int j = 0; j < J; ++j) {
+                        if (!valid[j]) continue;
+                        if (a.g_transposed) a.g_out[(size_t)(64u * (word0 + j) + lane) * a.V + v] = g[i][j];
+                        else a.g_out[row + 64 * j] = g[i][j];
+                    }
+                }
+                continue;
+            }
+            // AdamW as in var_tail
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                float t = th[i][j] * c.f_decay;
+                const float m2 = c.b1 * mm[i][j] + c.omb1 * g[i][j];
+                const float v2 = c.b2 * vv[i][j] + c.omb2 * (g[i][j] * g[i][j]);
+                const float denom = __builtin_amdgcn_sqrtf(v2) * c.f_isbc2 + c.eps;
+                t = t - c.f_step * (m2 * __builtin_amdgcn_rcpf(denom));
+                th[i][j] = valid[j] ? t : 0.f;
+                if (valid[j]) {
+                    if (!(__builtin_isfinite(t) && __builtin_isfinite(m2) && __builtin_isfinite(v2))) bad = 1;
+                    __builtin_nontemporal_store(t, a.theta + row + 64 * j);
+                    __builtin_nontemporal_store(m2, a.m + row + 64 * j);
+                    __builtin_nontemporal_store(v2, a.v + row + 64 * j);
+                }
+            }
+            if (vi[i].witness && wv == 0 && lane == 0) {
+                const uint64_t own = a.lits_cur[(size_t)(2 * v) * W + (vi[i].wcand >> 6)];
+                a.witness[v] = (uint8_t)((own >> (vi[i].wcand & 63)) & 1u);
+            }
+            if (a.mode == 1) {
+                const double s2 = row_sum<J>([&](int j) { return (double)th[i][j]; });
+                if (lane == 0) s_mu[i][wv] = s2;
+            }
+        }
+        // the next pass writes s_ut only after every wave is past this
+        // barrier, and s_mu only after its own first one
+        if (sums) __syncthreads();
+        if (OP != OP_STEP) continue;
+#pragma unroll
+        for (int i = 0; i < C; ++i) {
+            if (vi[i].frozen) continue;
+            const uint32_t v = vb + i;
+            bool pos = true;
+            if (a.mode == 1) {
+                double mu2 = s_mu[i][0];
+                for (uint32_t k = 1; k < G; ++k) mu2 = mu2 + s_mu[i][k];
+                mu2 = mu2 * a.inv_n;
+                if (wv == 0 && lane == 0) a.mu_next[v] = mu2;
+                pos = mu2 >= 0.0; // the clamp maps a zero mean to +1e-12
+            }
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                const uint64_t bal = ballot64(valid[j] && (pos ? th[i][j] > 0.f : th[i][j] < 0.f));
+                const uint64_t vm = ballot64(valid[j]);
+                if (lane == 0 && (int)word0 + j < W) {
+                    a.lits_next[(size_t)(2 * v) * W + word0 + j] = bal;
+                    a.lits_next[(size_t)(2 * v + 1) * W + word0 + j] = ~bal & vm;
+                }
+            }
         }
     }
     if (OP == OP_STEP) {
@@ -3348,10 +3605,10 @@ static hipError_t launch_var_j(const VarArgs& a, int op, int blocks, hipStream_t
 
 // resident blocks per CU of the kernel a launch with these arguments would use
 template <class K>
-static int occupancy_of(K kernel, size_t lds)
+static int occupancy_of(K kernel, size_t lds, int threads = 256)
 {
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, 256, lds) != hipSuccess) {
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, threads, lds) != hipSuccess) {
         (void)hipGetLastError();
         return 0;
     }
@@ -3455,6 +3712,23 @@ static hipError_t launch_plane_j(const VarArgs& a, int op, int blocks, hipStream
     return full ? launch_plane_jkf<J, 3, true>(a, op, blocks, st) : launch_plane_jkf<J, 3, false>(a, op, blocks, st);
 }
 
+// rows of more than four words: a team of ceil(W / 4) waves per block
+template <int KW>
+static auto team_kernel_ptr(int op)
+{
+    return op == OP_STEP ? var_window_team_kernel<KW, OP_STEP>
+                         : (op == OP_GRAD ? var_window_team_kernel<KW, OP_GRAD> : var_window_team_kernel<KW, OP_ADJ>);
+}
+
+static int team_threads(const VarArgs& a) { return 64 * ((a.W + 3) / 4); }
+
+static hipError_t launch_team(const VarArgs& a, int op, int blocks, hipStream_t st)
+{
+    const auto k = a.pure_k == 2 ? team_kernel_ptr<2>(op) : team_kernel_ptr<3>(op);
+    hipLaunchKernelGGL(k, dim3(blocks), dim3(team_threads(a)), 0, st, a);
+    return hipGetLastError();
+}
+
 // mixed-width window gather: levels KT >= the widest clause (K1 - 1)
 static int levels_of(const VarArgs& a) { return levels_for_width(a.K1 - 1); }
 
@@ -3521,7 +3795,8 @@ static int occupancy_levels_j(const VarArgs& a)
 hipError_t launch_var(const VarArgs& a, int op, int blocks, hipStream_t st)
 {
     const bool rowwise = op == OP_BINARIZE || op == OP_NORMBWD; // no gather
-    if (a.occ_cid && a.planes && !rowwise && a.W <= 4) {
+    if (a.occ_cid && a.planes && !rowwise && a.W > 4) return launch_team(a, op, blocks, st);
+    if (a.occ_cid && a.planes && !rowwise) {
         if (a.pure_k == 2 || a.pure_k == 3) {
             switch (a.W) {
             case 1: return launch_plane_j<1>(a, op, blocks, st);
@@ -3572,14 +3847,16 @@ static int occupancy_j(const VarArgs& a, bool pure)
 int var_occupancy(const VarArgs& a, int op)
 {
     const bool rowwise = op == OP_BINARIZE || op == OP_NORMBWD; // no gather
-    if (a.occ_cid && a.planes && !rowwise && a.pure_k != 2 && a.pure_k != 3 && a.W <= 4) {
+    if (a.occ_cid && a.planes && !rowwise && a.W > 4)
+        return occupancy_of(a.pure_k == 2 ? team_kernel_ptr<2>(OP_STEP) : team_kernel_ptr<3>(OP_STEP), 0, team_threads(a));
+    if (a.occ_cid && a.planes && !rowwise && a.pure_k != 2 && a.pure_k != 3) {
         switch (a.W) {
         case 1: return occupancy_levels_j<1>(a);
         case 2: return occupancy_levels_j<2>(a);
         default: return occupancy_levels_j<4>(a);
         }
     }
-    if (a.occ_cid && a.planes && !rowwise && (a.pure_k == 2 || a.pure_k == 3) && a.W <= 4) {
+    if (a.occ_cid && a.planes && !rowwise) {
         const bool k2 = a.pure_k == 2, win = a.window != 0;
         if (pair_rows(a))
             return k2 ? occupancy_of(var_window_pair_kernel<2, OP_STEP>, 0) : occupancy_of(var_window_pair_kernel<3, OP_STEP>, 0);
