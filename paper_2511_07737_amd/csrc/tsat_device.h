@@ -144,11 +144,12 @@ struct VarArgs {
     float* m;
     float* v;
     float* U_out;             // [V][N], may be null
-    float* g_out;             // [V][N] or [N][V], may be null
+    float* g_out;             // [V][N], or [V][g_nsel] of the candidates with a slot, may be null
+    const int32_t* g_slot;    // null, or [N]: column of the candidate in g_out, -1: not stored
+    int32_t g_nsel;
     const float* dA_in;       // [V][N] dL/d(theta_norm) for the Eq. 5 backward op
     uint64_t* vbits_out;      // [V][W] value rows of the binarize op, may be null
     float* assign_out;        // [V][N] 0/1 values of the binarize op, may be null
-    int32_t g_transposed;
     float beta1, beta2, one_minus_beta1, one_minus_beta2, eps;
     double inv_n;             // 1 / N (row means and the Eq. 5 backward multiply by it)
     Ctrl* ctrl;
@@ -180,13 +181,20 @@ struct VarArgs {
 };
 
 struct SelectArgs {
-    const float* gT;        // [N][V]
+    const float* g;         // [V][S] gradient columns of the selected candidates
     const uint32_t* occ_off;
     const uint64_t* lits;   // [2V][W]
     const int32_t* order;   // candidates by priority
-    int32_t V, W, k, kpow2;
-    int32_t* lits_out;      // [nblocks][k]
-    int32_t* cand_out;      // [nblocks]
+    const int64_t* sat;     // [N] satisfied clauses
+    int32_t V, W, S, k, kpow2;
+    int32_t chunk, nchunks; // variables per block, blocks
+    uint32_t* hist;         // [4 passes][8 replicas][S][256], zero on entry
+    uint32_t* state;        // [5][S][3]
+    uint32_t* count;        // [nchunks][S][2]
+    uint64_t* sel;          // [S][k] (key << 32 | variable)
+    int64_t* sat_out;       // [S]
+    int32_t* cand_out;      // [S]
+    int32_t* lits_out;      // [S][k]
 };
 
 hipError_t launch_fwd(const FwdArgs& a, int nunits, int tiles, hipStream_t st);
@@ -211,8 +219,8 @@ hipError_t launch_stream(int kind, uint32_t* a, uint32_t* b, uint32_t* c, const 
                          hipStream_t st);
 hipError_t launch_strided_rows(const uint64_t* src, int64_t rows, int w, int64_t src_stride, uint64_t* dst,
                                hipStream_t st);
-hipError_t launch_rank(const int64_t* sat, int N, int32_t* order, hipStream_t st);
-hipError_t launch_select(const SelectArgs& a, int nblocks, hipStream_t st);
+hipError_t launch_rank(const int64_t* sat, int N, int nsel, int32_t* order, int32_t* slot, hipStream_t st);
+hipError_t launch_select(const SelectArgs& a, hipStream_t st);
 
 enum { VOP_STEP = 0, VOP_GRAD = 1, VOP_ADJ = 2, VOP_BINARIZE = 3, VOP_NORMBWD = 4 };
 

@@ -1629,7 +1629,6 @@ int32_t tsat_get_grad(tsat_solver* s, const tsat_params* params, float* U, float
     va.mu_cur = s->mu[s->cur].as<double>();
     va.U_out = s->tmp.as<float>();
     va.g_out = s->tmp.as<float>() + VN;
-    va.g_transposed = 0;
     batch_rows(s, va);
     HIPCHK(launch_var(va, VOP_GRAD, var_blocks(s, va.V), s->stream));
     if (U) HIPCHK(hipMemcpyAsync(U, va.U_out, VN * 4, hipMemcpyDeviceToHost, s->stream));
@@ -1652,44 +1651,70 @@ int32_t tsat_extract_partial(tsat_solver* s, int32_t max_cands, int32_t k, int32
     if (!cand_ids || !lits) return fail(TSAT_E_ARG, "NULL output");
     RET(ensure_mode(s, s->params.norm_mode));
     RET(ensure_scratch(s, s->N));
-    const size_t VN = (size_t)s->st.V * s->N;
-    DBuf gT, order, lout, cout;
-    RET(gT.alloc(VN * 4, "transposed gradient"));
-    RET(order.alloc((size_t)s->N * 4, "candidate order"));
-    RET(lout.alloc((size_t)max_cands * k * 4, "partial assignments"));
-    RET(cout.alloc((size_t)max_cands * 4, "candidate ids"));
+    // one scratch buffer: the selected gradient columns, the select's
+    // histograms (zeroed), states, counts and pairs, the candidate order, and
+    // the results, which leave in one copy
+    const size_t S = (size_t)max_cands, V = (size_t)s->st.V;
+    SelectArgs sa{};
+    sa.V = s->st.V;
+    sa.W = s->W;
+    sa.S = max_cands;
+    sa.k = k;
+    sa.kpow2 = 1;
+    while (sa.kpow2 < k) sa.kpow2 <<= 1;
+    sa.chunk = (int32_t)std::max<size_t>(256, (V + 511) / 512);
+    sa.nchunks = (int32_t)((V + sa.chunk - 1) / sa.chunk);
+    size_t need = 0;
+    auto part = [&](size_t bytes) {
+        const size_t at = need;
+        need += (bytes + 255) & ~(size_t)255;
+        return at;
+    };
+    const size_t o_g = part(V * S * 4), o_hist = part(4 * 8 * S * 256 * 4), o_state = part(5 * S * 12);
+    const size_t o_count = part((size_t)sa.nchunks * S * 8), o_sel = part(S * k * 8);
+    const size_t o_order = part((size_t)s->N * 4), o_slot = part((size_t)s->N * 4);
+    const size_t out_bytes = S * 8 + S * 4 + S * k * 4, o_out = part(out_bytes);
+    RET(s->tmp.reserve(need, "partial assignments"));
+    uint8_t* base = s->tmp.as<uint8_t>();
+    int32_t* order = reinterpret_cast<int32_t*>(base + o_order);
+    int32_t* slot = reinterpret_cast<int32_t*>(base + o_slot);
+    std::vector<uint8_t> out;
+    try {
+        out.resize(out_bytes);
+    } catch (const std::bad_alloc&) {
+        return fail(TSAT_E_OOM, "host allocation failed");
+    }
     RET(eval_rows(s, s->params, s->lits[s->cur].as<uint64_t>(), s->N, nullptr, nullptr, nullptr, nullptr,
                   s->sat_scr.as<int64_t>(), s->table_scr.as<float>(), s->stream));
+    HIPCHK(launch_rank(s->sat_scr.as<int64_t>(), s->N, max_cands, order, slot, s->stream));
     VarArgs va = var_args(s, s->params, s->N, s->W, s->Np);
     va.tbl = s->table_scr.as<float>();
     va.theta = s->theta.as<float>();
     va.lits_cur = s->lits[s->cur].as<uint64_t>();
     va.mu_cur = s->mu[s->cur].as<double>();
-    va.g_out = gT.as<float>();
-    va.g_transposed = 1;
+    va.g_out = reinterpret_cast<float*>(base + o_g);
+    va.g_slot = slot;
+    va.g_nsel = max_cands;
     HIPCHK(launch_var(va, VOP_GRAD, var_blocks(s, s->st.V), s->stream));
-    HIPCHK(launch_rank(s->sat_scr.as<int64_t>(), s->N, order.as<int32_t>(), s->stream));
-    SelectArgs sa{};
-    sa.gT = gT.as<float>();
+    HIPCHK(launch_fill_u32(reinterpret_cast<uint32_t*>(base + o_hist), (int64_t)(4 * 8 * S * 256), 0u, s->stream));
+    sa.g = va.g_out;
     sa.occ_off = s->occ_off.as<uint32_t>();
     sa.lits = s->lits[s->cur].as<uint64_t>();
-    sa.order = order.as<int32_t>();
-    sa.V = s->st.V;
-    sa.W = s->W;
-    sa.k = k;
-    int kp = 1;
-    while (kp < k) kp <<= 1;
-    sa.kpow2 = kp;
-    sa.lits_out = lout.as<int32_t>();
-    sa.cand_out = cout.as<int32_t>();
-    HIPCHK(launch_select(sa, max_cands, s->stream));
-    std::vector<int64_t> sat(s->N);
-    HIPCHK(hipMemcpyAsync(lits, lout.p, (size_t)max_cands * k * 4, hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(hipMemcpyAsync(cand_ids, cout.p, (size_t)max_cands * 4, hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(hipMemcpyAsync(sat.data(), s->sat_scr.p, (size_t)s->N * 8, hipMemcpyDeviceToHost, s->stream));
+    sa.order = order;
+    sa.sat = s->sat_scr.as<int64_t>();
+    sa.hist = reinterpret_cast<uint32_t*>(base + o_hist);
+    sa.state = reinterpret_cast<uint32_t*>(base + o_state);
+    sa.count = reinterpret_cast<uint32_t*>(base + o_count);
+    sa.sel = reinterpret_cast<uint64_t*>(base + o_sel);
+    sa.sat_out = reinterpret_cast<int64_t*>(base + o_out);
+    sa.cand_out = reinterpret_cast<int32_t*>(base + o_out + S * 8);
+    sa.lits_out = sa.cand_out + S;
+    HIPCHK(launch_select(sa, s->stream));
+    HIPCHK(hipMemcpyAsync(out.data(), base + o_out, out_bytes, hipMemcpyDeviceToHost, s->stream));
     HIPCHK(hipStreamSynchronize(s->stream));
-    if (sat_counts)
-        for (int32_t a = 0; a < max_cands; ++a) sat_counts[a] = sat[cand_ids[a]];
+    if (sat_counts) memcpy(sat_counts, out.data(), S * 8);
+    memcpy(cand_ids, out.data() + S * 8, S * 4);
+    memcpy(lits, out.data() + S * 12, S * k * 4);
     return TSAT_OK;
 }
 
@@ -1941,7 +1966,6 @@ int32_t tsat_loss_backward_dev(tsat_solver* s, const float* theta, int32_t N, fl
     va.mu_cur = s->mu_scr.as<double>();
     va.U_out = U;
     va.g_out = g;
-    va.g_transposed = 0;
     HIPCHK(launch_var(va, VOP_GRAD, var_blocks(s, s->st.V), st));
     return TSAT_OK;
 }

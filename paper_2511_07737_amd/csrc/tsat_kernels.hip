@@ -744,6 +744,18 @@ __device__ __forceinline__ void norm_backward_row(const VarArgs& a, const float 
     }
 }
 
+// Store of one gradient entry: the whole [V][N], or the selected candidates'
+// columns only, [V][g_nsel] in their order.
+__device__ __forceinline__ void store_g(const VarArgs& a, uint32_t v, uint32_t i, float g)
+{
+    if (!a.g_slot) {
+        a.g_out[(size_t)v * a.N + i] = g;
+        return;
+    }
+    const int32_t q = a.g_slot[i];
+    if (q >= 0) a.g_out[(size_t)v * a.g_nsel + q] = g;
+}
+
 // Everything after U: stores of U (adjoint op), Eq. 5 backward, stores of g
 // (gradient op), AdamW, witness, new row mean, re-binarization (step op).
 template <int J, int OP>
@@ -769,8 +781,7 @@ __device__ __forceinline__ void var_tail(const VarArgs& a, const StepScalars& c,
             for (int j = 0; j < J; ++j) {
                 if (!valid[j]) continue;
                 const int i = 64 * j + lane;
-                if (a.g_transposed) a.g_out[(size_t)i * a.V + v] = g[j];
-                else a.g_out[(size_t)v * N + i] = g[j];
+                store_g(a, v, (uint32_t)i, g[j]);
             }
         }
         return;
@@ -2164,8 +2175,7 @@ __global__ __launch_bounds__(256) void var_window_team_kernel(VarArgs a)
 #pragma unroll
                     for (int j = 0; j < J; ++j) {
                         if (!valid[j]) continue;
-                        if (a.g_transposed) a.g_out[(size_t)(64u * (word0 + j) + lane) * a.V + v] = g[i][j];
-                        else a.g_out[row + 64 * j] = g[i][j];
+                        store_g(a, v, 64u * (word0 + j) + lane, g[i][j]);
                     }
                 }
                 continue;
@@ -2267,8 +2277,7 @@ __device__ __forceinline__ void pair_tail(const VarArgs& a, const StepScalars& c
     }
     if (OP == OP_GRAD) {
         if (a.g_out && valid) {
-            if (a.g_transposed) a.g_out[(size_t)l * a.V + vl] = g;
-            else a.g_out[idx] = g;
+            store_g(a, vl, l, g);
         }
         return;
     }
@@ -3260,116 +3269,263 @@ __global__ void fill_u32_kernel(uint32_t* __restrict__ p, int64_t n, uint32_t va
 }
 
 // Candidate priority (Sec. IV-B): rank = #{j : sat_j > sat_i or (== and j < i)}.
-__global__ void rank_kernel(const int64_t* __restrict__ sat, int N, int32_t* __restrict__ order)
+// order[rank] = i, and slot[i] = rank for the first nsel candidates, else -1.
+__global__ __launch_bounds__(256) void rank_kernel(const int64_t* __restrict__ sat, int N, int nsel,
+                                                   int32_t* __restrict__ order, int32_t* __restrict__ slot)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= N) return;
-    const int64_t si = sat[i];
+    __shared__ int64_t s_sat[256];
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    const int64_t si = i < N ? sat[i] : 0;
     int rank = 0;
-    for (int j = 0; j < N; ++j) {
-        const int64_t sj = sat[j];
-        rank += (sj > si) || (sj == si && j < i);
+    for (int j0 = 0; j0 < N; j0 += 256) {
+        __syncthreads();
+        if (j0 + (int)threadIdx.x < N) s_sat[threadIdx.x] = sat[j0 + threadIdx.x];
+        __syncthreads();
+        const int n = min(256, N - j0);
+        for (int j = 0; j < n; ++j) rank += (s_sat[j] > si) || (s_sat[j] == si && j0 + j < i);
     }
+    if (i >= N) return;
     order[rank] = i;
+    slot[i] = rank < nsel ? rank : -1;
 }
 
-// Confident partial assignment of one candidate (Sec. IV-B): the k eligible
-// variables with the smallest |g| (ties: lower index), in that order.
-// One block per selected candidate; keys are the IEEE bits of |g|, which
-// order like the values for non-negative floats.
-__global__ __launch_bounds__(256) void select_kernel(SelectArgs a)
+// ---------------------------------------------------------------------------
+// Confident partial assignments (Sec. IV-B): per selected candidate (slot)
+// the k eligible variables with the smallest |g| (ties: lower index), in that
+// order.  Keys are the IEEE bits of |g|, which order like the values for
+// non-negative floats.
+//
+// A radix select of the k-th smallest key over [V][slots], every slot at
+// once and the variables split over the chip: four digit passes (a histogram
+// per slot and 8-bit digit), a counting pass (keys below and equal to the
+// k-th, per chunk), a collecting pass, and a sort of each slot's k keys.
+// The passes read the keys from the last-level cache (V = 2e5, 16 slots:
+// 12.8 MB); one block per candidate walking its column five times took
+// SEL_OLD.
+// ---------------------------------------------------------------------------
+
+constexpr int kSelTile = 32; // slots of a block
+
+struct SelDigit {
+    uint32_t prefix, rank, k; // key digits found so far, rank left among the keys sharing them, keys to take
+};
+
+// State of a slot before pass `pass` (0: nothing known): the previous
+// pass's histogram scanned for the digit that holds the rank.  Called by a
+// whole wave.
+__device__ __forceinline__ SelDigit select_state(const SelectArgs& a, int pass, int slot, uint32_t lane)
 {
-    __shared__ uint32_t hist[256];
-    __shared__ uint32_t s_pref, s_rank, s_cnt, s_taken_eq, s_elig;
-    __shared__ uint32_t s_scan[256];
-    extern __shared__ uint64_t sel[]; // [kpow2] (key << 32 | v)
-    const int tid = threadIdx.x;
-    const int cand = a.order[blockIdx.x];
-    const float* gi = a.gT + (size_t)cand * a.V;
-    auto eligible = [&](int v) { return a.occ_off[v + 1] > a.occ_off[v]; };
-    auto keyof = [&](int v) { return __float_as_uint(fabsf(gi[v])); };
-    if (tid == 0) s_elig = 0;
-    __syncthreads();
-    uint32_t cnt = 0;
-    for (int v = tid; v < a.V; v += blockDim.x) cnt += eligible(v);
-    atomicAdd(&s_elig, cnt);
-    __syncthreads();
-    const uint32_t k = min((uint32_t)a.k, s_elig);
-    uint32_t prefix = 0, pmask = 0;
-    uint32_t rank = k; // 1-based rank of the threshold among eligible keys
-    for (int pass = 0; pass < 4 && k > 0; ++pass) {
-        const int shift = 24 - 8 * pass;
-        hist[tid] = 0;
-        __syncthreads();
-        for (int v = tid; v < a.V; v += blockDim.x) {
-            if (!eligible(v)) continue;
-            const uint32_t key = keyof(v);
-            if ((key & pmask) == prefix) atomicAdd(&hist[(key >> shift) & 255u], 1u);
-        }
-        __syncthreads();
-        if (tid == 0) {
-            uint32_t acc = 0;
-            int dsel = 255;
-            for (int dgt = 0; dgt < 256; ++dgt) {
-                if (acc + hist[dgt] >= rank) { dsel = dgt; break; }
-                acc += hist[dgt];
-            }
-            s_pref = prefix | ((uint32_t)dsel << shift);
-            s_rank = rank - acc;
-        }
-        __syncthreads();
-        prefix = s_pref;
-        rank = s_rank;
-        pmask |= 255u << shift;
-        __syncthreads();
+    SelDigit d = {0u, 0u, 0u};
+    if (pass == 0) return d;
+    if (pass > 1) d = ((const SelDigit*)a.state)[(size_t)(pass - 1) * a.S + slot];
+    const uint4* h = (const uint4*)(a.hist + ((size_t)(pass - 1) * 8 * a.S + slot) * 256) + lane;
+    uint4 v = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const uint4 x = h[(size_t)q * a.S * 64];
+        v.x += x.x;
+        v.y += x.y;
+        v.z += x.z;
+        v.w += x.w;
     }
-    const uint32_t T = prefix;         // the k-th smallest eligible key
-    const uint32_t need_eq = rank;     // how many keys equal to T are taken
-    if (tid == 0) { s_cnt = 0; s_taken_eq = 0; }
-    __syncthreads();
-    if (k > 0) {
-        // keys below T (all taken), then keys equal to T in increasing v
-        for (int base = 0; base < a.V; base += blockDim.x) {
-            const int v = base + tid;
-            uint32_t key = 0xffffffffu;
-            bool el = v < a.V && eligible(v);
-            if (el) key = keyof(v);
-            const bool lt = el && key < T;
-            const bool eq = el && key == T;
-            if (lt) {
-                const uint32_t pos = atomicAdd(&s_cnt, 1u);
-                sel[pos] = ((uint64_t)key << 32) | (uint32_t)v;
-            }
-            s_scan[tid] = eq ? 1u : 0u;
-            __syncthreads();
-            for (int off = 1; off < (int)blockDim.x; off <<= 1) {
-                const uint32_t x = tid >= off ? s_scan[tid - off] : 0u;
-                __syncthreads();
-                s_scan[tid] += x;
-                __syncthreads();
-            }
-            const uint32_t before = s_taken_eq;
-            if (eq) {
-                const uint32_t idx = before + s_scan[tid] - 1u;
-                if (idx < need_eq) {
-                    const uint32_t pos = atomicAdd(&s_cnt, 1u);
-                    sel[pos] = ((uint64_t)key << 32) | (uint32_t)v;
-                }
-            }
-            __syncthreads();
-            if (tid == 0) s_taken_eq = before + s_scan[blockDim.x - 1];
-            __syncthreads();
+    const uint32_t own = v.x + v.y + v.z + v.w;
+    uint32_t incl = own;
+#pragma unroll
+    for (int st = 1; st < 64; st <<= 1) {
+        const uint32_t y = __shfl_up(incl, st);
+        if ((int)lane >= st) incl += y;
+    }
+    if (pass == 1) d.k = d.rank = min((uint32_t)a.k, (uint32_t)__shfl(incl, 63));
+    if (d.k == 0) return d;
+    // the lane whose four bins hold the rank, then the bin
+    const uint64_t m = ballot64(incl >= d.rank);
+    const int at = __ffsll((unsigned long long)m) - 1;
+    uint32_t before = incl - own, dig = 0;
+    const uint32_t c[3] = {v.x, v.y, v.z};
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+        if (dig == (uint32_t)j && before + c[j] < d.rank) {
+            before += c[j];
+            ++dig;
+        }
+    const uint32_t digit = 4u * (uint32_t)at + (uint32_t)__shfl(dig, at);
+    d.rank -= (uint32_t)__shfl(before, at);
+    d.prefix |= digit << (32 - 8 * pass);
+    return d;
+}
+
+// The slots of this block: [s0, s0 + n), one slot per lane group of a power
+// of two, threads striding the variables of chunk blockIdx.x.
+struct SelTile {
+    int s0, n, slot, row, rows, v0, v1;
+};
+
+__device__ __forceinline__ SelTile select_tile(const SelectArgs& a)
+{
+    SelTile t;
+    t.s0 = blockIdx.y * kSelTile;
+    t.n = min(kSelTile, a.S - t.s0);
+    int p = 1;
+    while (p < t.n) p <<= 1;
+    t.slot = threadIdx.x % p;
+    t.row = threadIdx.x / p;
+    t.rows = 256 / p;
+    t.v0 = blockIdx.x * a.chunk;
+    t.v1 = min(a.V, t.v0 + a.chunk);
+    return t;
+}
+
+// f(v, key) over the eligible variables of the tile's chunk for this
+// thread's slot, four keys in flight
+template <class F>
+__device__ __forceinline__ void select_keys(const SelectArgs& a, const SelTile& t, F f)
+{
+    if (t.slot >= t.n) return;
+    for (int v = t.v0 + t.row; v < t.v1; v += 4 * t.rows) {
+        uint32_t key[4], o0[4], o1[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int w = min(v + q * t.rows, t.v1 - 1);
+            key[q] = __float_as_uint(fabsf(a.g[(size_t)w * a.S + t.s0 + t.slot]));
+            o0[q] = a.occ_off[w];
+            o1[q] = a.occ_off[w + 1];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (v + q * t.rows < t.v1 && o1[q] > o0[q]) f(v + q * t.rows, key[q]);
+    }
+}
+
+__device__ __forceinline__ void select_states(const SelectArgs& a, const SelTile& t, int pass, SelDigit* s_d)
+{
+    const uint32_t lane = __lane_id();
+    for (int s = threadIdx.x / 64; s < t.n; s += 4) {
+        const SelDigit d = select_state(a, pass, t.s0 + s, lane);
+        if (lane == 0) {
+            s_d[s] = d;
+            if (blockIdx.x == 0 && pass > 0) ((SelDigit*)a.state)[(size_t)pass * a.S + t.s0 + s] = d;
         }
     }
+}
+
+__global__ __launch_bounds__(256) void select_hist_kernel(SelectArgs a, int pass)
+{
+    __shared__ uint32_t s_hist[kSelTile][256];
+    __shared__ SelDigit s_d[kSelTile];
+    const SelTile t = select_tile(a);
+    for (int e = threadIdx.x; e < t.n * 256; e += 256) (&s_hist[0][0])[e] = 0;
+    select_states(a, t, pass, s_d);
     __syncthreads();
-    // bitonic sort of the k selected (key, v) pairs, padded with max
-    const int kp = a.kpow2;
-    for (int q = tid; q < kp; q += blockDim.x)
-        if (q >= (int)k) sel[q] = ~0ull;
+    const SelDigit d = s_d[t.slot < t.n ? t.slot : 0];
+    const uint32_t mask = pass == 0 ? 0u : ~0u << (32 - 8 * pass);
+    const int shift = 24 - 8 * pass;
+    if (pass == 0 || d.k > 0)
+        select_keys(a, t, [&](int, uint32_t key) {
+            if ((key & mask) == d.prefix) atomicAdd(&s_hist[t.slot][(key >> shift) & 255u], 1u);
+        });
+    __syncthreads();
+    uint32_t* H = a.hist + (((size_t)pass * 8 + blockIdx.x % 8u) * a.S + t.s0) * 256;
+    for (int e = threadIdx.x; e < t.n * 256; e += 256) {
+        const uint32_t c = (&s_hist[0][0])[e];
+        if (c) atomicAdd(&H[e], c);
+    }
+}
+
+// keys below and equal to the k-th, per chunk and slot
+__global__ __launch_bounds__(256) void select_count_kernel(SelectArgs a)
+{
+    __shared__ uint32_t s_c[2][kSelTile];
+    __shared__ SelDigit s_d[kSelTile];
+    const SelTile t = select_tile(a);
+    if (threadIdx.x < 2 * kSelTile) (&s_c[0][0])[threadIdx.x] = 0;
+    select_states(a, t, 4, s_d);
+    __syncthreads();
+    const SelDigit d = s_d[t.slot < t.n ? t.slot : 0];
+    uint32_t lt = 0, eq = 0;
+    if (d.k > 0)
+        select_keys(a, t, [&](int, uint32_t key) {
+            lt += key < d.prefix;
+            eq += key == d.prefix;
+        });
+    if (t.slot < t.n) {
+        if (lt) atomicAdd(&s_c[0][t.slot], lt);
+        if (eq) atomicAdd(&s_c[1][t.slot], eq);
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < t.n) {
+        uint2* o = (uint2*)a.count + (size_t)blockIdx.x * a.S + t.s0;
+        o[threadIdx.x] = make_uint2(s_c[0][threadIdx.x], s_c[1][threadIdx.x]);
+    }
+}
+
+// Selected (key, variable) pairs: keys below the k-th take the slots' first
+// places (offset by the earlier chunks' counts), the ones equal to it follow
+// in the order of the variables until k are taken.
+__global__ __launch_bounds__(256) void select_collect_kernel(SelectArgs a)
+{
+    __shared__ uint32_t s_lt[kSelTile], s_eq[kSelTile]; // keys of earlier chunks
+    __shared__ int s_any;
+    const SelTile t = select_tile(a);
+    const uint2* cnt = (const uint2*)a.count;
+    if (threadIdx.x == 0) s_any = 0;
+    if (threadIdx.x < kSelTile) s_lt[threadIdx.x] = s_eq[threadIdx.x] = 0;
+    __syncthreads();
+    if ((int)threadIdx.x < t.n) {
+        const uint2 c = cnt[(size_t)blockIdx.x * a.S + t.s0 + threadIdx.x];
+        if (c.x | c.y) s_any = 1;
+    }
+    __syncthreads();
+    if (!s_any) return;
+    if (t.slot < t.n) {
+        uint32_t lt = 0, eq = 0;
+        for (int ch = t.row; ch < (int)blockIdx.x; ch += t.rows) {
+            const uint2 c = cnt[(size_t)ch * a.S + t.s0 + t.slot];
+            lt += c.x;
+            eq += c.y;
+        }
+        if (lt) atomicAdd(&s_lt[t.slot], lt);
+        if (eq) atomicAdd(&s_eq[t.slot], eq);
+    }
+    __syncthreads();
+    const SelDigit* state = (const SelDigit*)a.state + (size_t)4 * a.S + t.s0;
+    // keys equal to the k-th: a wave per slot, variables in order
+    const uint32_t lane = __lane_id();
+    for (int s = threadIdx.x / 64; s < t.n; s += 4) {
+        const SelDigit d = state[s];
+        uint64_t* out = a.sel + (size_t)(t.s0 + s) * a.k + (d.k - d.rank); // keys below the k-th come first
+        uint32_t eq = s_eq[s];
+        const uint32_t end = eq + cnt[(size_t)blockIdx.x * a.S + t.s0 + s].y;
+        if (d.k == 0) continue;
+        for (int v = t.v0; v < t.v1 && eq < d.rank && eq < end; v += 64) { // wave-uniform
+            const int w = v + (int)lane;
+            const bool hit = w < t.v1 && a.occ_off[w + 1] > a.occ_off[w] &&
+                             __float_as_uint(fabsf(a.g[(size_t)w * a.S + t.s0 + s])) == d.prefix;
+            const uint64_t m = ballot64(hit);
+            const uint32_t at = eq + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+            if (hit && at < d.rank) out[at] = ((uint64_t)d.prefix << 32) | (uint32_t)w;
+            eq += (uint32_t)__popcll(m);
+        }
+    }
+    const SelDigit d = state[t.slot < t.n ? t.slot : 0];
+    if (d.k > 0)
+        select_keys(a, t, [&](int v, uint32_t key) {
+            if (key < d.prefix)
+                a.sel[(size_t)(t.s0 + t.slot) * a.k + atomicAdd(&s_lt[t.slot], 1u)] = ((uint64_t)key << 32) | (uint32_t)v;
+        });
+}
+
+// bitonic sort of a slot's (key, variable) pairs, padded with max, and the
+// literals of the candidate's current values
+__global__ __launch_bounds__(256) void select_sort_kernel(SelectArgs a)
+{
+    extern __shared__ uint64_t sel[]; // [kpow2]
+    const int tid = threadIdx.x, kp = a.kpow2, cand = a.order[blockIdx.x];
+    const uint32_t k = ((const SelDigit*)a.state)[(size_t)4 * a.S + blockIdx.x].k;
+    for (int q = tid; q < kp; q += 256) sel[q] = q < (int)k ? a.sel[(size_t)blockIdx.x * a.k + q] : ~0ull;
     __syncthreads();
     for (int size = 2; size <= kp; size <<= 1)
         for (int stride = size / 2; stride > 0; stride >>= 1) {
-            for (int q = tid; q < kp; q += blockDim.x) {
+            for (int q = tid; q < kp; q += 256) {
                 const int p = q ^ stride;
                 if (p > q) {
                     const bool up = (q & size) == 0;
@@ -3380,13 +3536,16 @@ __global__ __launch_bounds__(256) void select_kernel(SelectArgs a)
             __syncthreads();
         }
     int32_t* out = a.lits_out + (size_t)blockIdx.x * a.k;
-    for (int q = tid; q < a.k; q += blockDim.x) {
+    for (int q = tid; q < a.k; q += 256) {
         if (q >= (int)k) { out[q] = 0; continue; }
         const uint32_t v = (uint32_t)(sel[q] & 0xffffffffu);
         const uint64_t w = a.lits[(size_t)(2 * v) * a.W + (cand >> 6)];
         out[q] = ((w >> (cand & 63)) & 1u) ? (int32_t)(v + 1) : -(int32_t)(v + 1);
     }
-    if (tid == 0) a.cand_out[blockIdx.x] = cand;
+    if (tid == 0) {
+        a.cand_out[blockIdx.x] = cand;
+        a.sat_out[blockIdx.x] = a.sat[cand];
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -3930,16 +4089,27 @@ hipError_t launch_fill_u32(uint32_t* p, int64_t n, uint32_t val, hipStream_t st)
     return hipGetLastError();
 }
 
-hipError_t launch_rank(const int64_t* sat, int N, int32_t* order, hipStream_t st)
+hipError_t launch_rank(const int64_t* sat, int N, int nsel, int32_t* order, int32_t* slot, hipStream_t st)
 {
-    hipLaunchKernelGGL(rank_kernel, dim3((N + 255) / 256), dim3(256), 0, st, sat, N, order);
+    hipLaunchKernelGGL(rank_kernel, dim3((N + 255) / 256), dim3(256), 0, st, sat, N, nsel, order, slot);
     return hipGetLastError();
 }
 
-hipError_t launch_select(const SelectArgs& a, int nblocks, hipStream_t st)
+hipError_t launch_select(const SelectArgs& a, hipStream_t st)
 {
-    const size_t lds = (size_t)a.kpow2 * sizeof(uint64_t);
-    hipLaunchKernelGGL(select_kernel, dim3(nblocks), dim3(256), lds, st, a);
+    const dim3 grid((unsigned)a.nchunks, (unsigned)((a.S + kSelTile - 1) / kSelTile));
+    for (int pass = 0; pass < 4; ++pass) {
+        hipLaunchKernelGGL(select_hist_kernel, grid, dim3(256), 0, st, a, pass);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(select_count_kernel, grid, dim3(256), 0, st, a);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(select_collect_kernel, grid, dim3(256), 0, st, a);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(select_sort_kernel, dim3((unsigned)a.S), dim3(256), (size_t)a.kpow2 * sizeof(uint64_t), st, a);
     return hipGetLastError();
 }
 
