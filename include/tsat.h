@@ -407,6 +407,28 @@ int32_t tsat_loss_dev(tsat_solver* s, const float* theta, int32_t N, float tau, 
 int32_t tsat_loss_backward_dev(tsat_solver* s, const float* theta, int32_t N, float tau, int32_t mode,
                                const float* dloss, float* g, float* U, void* stream);
 
+/* Forward and backward of one evaluation without forming the forward twice:
+ * the save forms of tsat_fwd_dev and tsat_loss_dev leave what their backward
+ * needs (the histogram of R, the row means, and the clause planes or literal
+ * rows) in caller device memory `saved` (256-byte aligned, at least
+ * tsat_saved_bytes(s, N) bytes), and a nonzero *key naming the loaded CNF and
+ * the layout; the saved forms of tsat_bwd_dev and tsat_loss_backward_dev read
+ * it (it is not modified, so a forward may be followed by several
+ * backwards).  Arguments, results (bitwise) and errors are those of the plain
+ * calls.  N, tau, mode and the inputs must be the forward's; if the key does
+ * not match, because another CNF was loaded or the launch shapes changed
+ * since, the plain call runs instead and `saved` is not read. */
+int32_t tsat_saved_bytes(tsat_solver* s, int32_t N, int64_t* bytes);
+int32_t tsat_fwd_save_dev(tsat_solver* s, const uint64_t* bits, int32_t N, float tau, float* S, void* saved,
+                          int64_t bytes, uint64_t* key, void* stream);
+int32_t tsat_bwd_saved_dev(tsat_solver* s, const uint64_t* bits, int32_t N, float tau, const float* dS, float* U,
+                           void* saved, int64_t bytes, uint64_t key, void* stream);
+int32_t tsat_loss_save_dev(tsat_solver* s, const float* theta, int32_t N, float tau, int32_t mode, float* loss,
+                           void* saved, int64_t bytes, uint64_t* key, void* stream);
+int32_t tsat_loss_backward_saved_dev(tsat_solver* s, const float* theta, int32_t N, float tau, int32_t mode,
+                                     const float* dloss, float* g, float* U, void* saved, int64_t bytes, uint64_t key,
+                                     void* stream);
+
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the
  * forward of tsat_fwd_dev with the same arguments, outputs and results

@@ -13,6 +13,10 @@ passes their pointers and torch's current stream, and wires the backward.
   the Eq. 5 backward of the gradient the STE passes through Eq. 2.
 * ``loss_of(theta)``: the whole chain to the scalar loss in one call, its
   backward in one fused pass (adjoint, Eq. 5 backward).
+
+The layer and the loss keep the forward's histogram, row means and clause
+planes in a saved tensor, so that the backward does not form the forward
+again; without a gradient to compute nothing is kept.
 """
 from __future__ import annotations
 
@@ -33,6 +37,17 @@ def _logits(theta: torch.Tensor, solver: tsat.Solver) -> torch.Tensor:
     return theta.contiguous()
 
 
+def _saved_buffer(solver: tsat.Solver, n: int, device) -> torch.Tensor | None:
+    """Memory for a forward's saved state, or None where it does not fit or the
+    candidates are too many for a backward (which then says so)."""
+    if n > tsat.MAX_STEP_N:
+        return None
+    try:
+        return torch.empty(solver.saved_bytes(n), dtype=torch.uint8, device=device)
+    except torch.cuda.OutOfMemoryError:
+        return None
+
+
 def _upstream(t: torch.Tensor) -> torch.Tensor:
     if t.dtype != torch.float32:
         raise ValueError(f"upstream gradient must be float32 (got {t.dtype})")
@@ -49,8 +64,14 @@ class SmoothMinSat(torch.autograd.Function):
         bits = torch.empty((V, W), dtype=torch.int64, device=assign.device)
         solver.pack_dev(assign.data_ptr(), N, bits.data_ptr(), stream)
         S = torch.empty(N, dtype=torch.float32, device=assign.device)
-        solver.fwd_dev(bits.data_ptr(), N, tau, S.data_ptr(), None, stream)
-        ctx.save_for_backward(bits)
+        saved = _saved_buffer(solver, N, assign.device) if ctx.needs_input_grad[0] else None
+        if saved is None:
+            solver.fwd_dev(bits.data_ptr(), N, tau, S.data_ptr(), None, stream)
+            ctx.save_for_backward(bits)
+        else:
+            ctx.key = solver.fwd_save_dev(bits.data_ptr(), N, tau, S.data_ptr(), saved.data_ptr(), saved.numel(),
+                                          stream)
+            ctx.save_for_backward(bits, saved)
         ctx.solver = solver
         ctx.tau = tau
         ctx.shape = (V, N)
@@ -58,11 +79,15 @@ class SmoothMinSat(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, dS: torch.Tensor):
-        (bits,) = ctx.saved_tensors
+        bits, *saved = ctx.saved_tensors
         V, N = ctx.shape
         dS = _upstream(dS)
         U = torch.empty((V, N), dtype=torch.float32, device=bits.device)
-        ctx.solver.bwd_dev(bits.data_ptr(), N, ctx.tau, dS.data_ptr(), U.data_ptr(), _stream(bits))
+        if saved:
+            ctx.solver.bwd_saved_dev(bits.data_ptr(), N, ctx.tau, dS.data_ptr(), U.data_ptr(), saved[0].data_ptr(),
+                                     saved[0].numel(), ctx.key, _stream(bits))
+        else:
+            ctx.solver.bwd_dev(bits.data_ptr(), N, ctx.tau, dS.data_ptr(), U.data_ptr(), _stream(bits))
         return U, None, None
 
 
@@ -103,8 +128,15 @@ class LogitLoss(torch.autograd.Function):
     def forward(ctx, theta: torch.Tensor, solver: tsat.Solver, tau: float, mode: int):
         theta = _logits(theta, solver)
         loss = torch.empty((), dtype=torch.float32, device=theta.device)
-        solver.loss_dev(theta.data_ptr(), theta.shape[1], tau, mode, loss.data_ptr(), None, None, _stream(theta))
-        ctx.save_for_backward(theta)
+        N, stream = theta.shape[1], _stream(theta)
+        saved = _saved_buffer(solver, N, theta.device) if ctx.needs_input_grad[0] else None
+        if saved is None:
+            solver.loss_dev(theta.data_ptr(), N, tau, mode, loss.data_ptr(), None, None, stream)
+            ctx.save_for_backward(theta)
+        else:
+            ctx.key = solver.loss_save_dev(theta.data_ptr(), N, tau, mode, loss.data_ptr(), saved.data_ptr(),
+                                           saved.numel(), stream)
+            ctx.save_for_backward(theta, saved)
         ctx.solver = solver
         ctx.tau = tau
         ctx.mode = mode
@@ -112,11 +144,14 @@ class LogitLoss(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, dloss: torch.Tensor):
-        (theta,) = ctx.saved_tensors
+        theta, *saved = ctx.saved_tensors
         dloss = _upstream(dloss)
         g = torch.empty_like(theta)
-        ctx.solver.loss_backward_dev(theta.data_ptr(), theta.shape[1], ctx.tau, ctx.mode, dloss.data_ptr(),
-                                     g.data_ptr(), None, _stream(theta))
+        args = (theta.data_ptr(), theta.shape[1], ctx.tau, ctx.mode, dloss.data_ptr(), g.data_ptr(), None)
+        if saved:
+            ctx.solver.loss_backward_saved_dev(*args, saved[0].data_ptr(), saved[0].numel(), ctx.key, _stream(theta))
+        else:
+            ctx.solver.loss_backward_dev(*args, _stream(theta))
         return g, None, None, None
 
 

@@ -95,6 +95,7 @@ struct SminArgs {
     uint32_t* H;            // [n_inst][H_reps][Np][K1] accumulators (read, optionally zeroed)
     int32_t H_reps;
     uint32_t* H_last;       // [n_inst][N][K1] copy including empty clauses, may be null
+    uint32_t* H_save;       // [Np][K1] the accumulators' sum (one instance), may be null
     float* table;           // [n_inst][K1][Np] dL/dR, may be null
     float* S_out;           // [n_inst][N] SmoothMin, may be null
     double* S64_out;        // [n_inst][N] SmoothMin in FP64, may be null

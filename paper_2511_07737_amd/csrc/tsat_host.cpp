@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -48,6 +49,7 @@ struct tsat_solver {
     int32_t cus = 256;
 
     bool loaded = false;
+    uint64_t load_id = 0; // number of the last load, over all solvers of the process
     Store st;
     std::vector<Bucket*> buckets;
     DBuf occ_off, occ_mid, occ_data, var_inst, info;
@@ -322,11 +324,16 @@ static int64_t narrow_end(const tsat_solver* s)
     return s->st.K >= 4 ? s->st.plane_base[4] : s->st.plane_clauses;
 }
 
-static int32_t ensure_planes(tsat_solver* s, DBuf& buf, int32_t N, hipStream_t st)
+static size_t planes_bytes(const tsat_solver* s, int32_t N)
 {
     const size_t G3 = (size_t)narrow_end(s);
     const size_t words = G3 * 2 + ((size_t)s->st.plane_clauses - G3) * 4; // plane rows
-    const size_t bytes = std::max<size_t>(16, words * 8 * (size_t)row_words((N + 63) / 64));
+    return std::max<size_t>(16, words * 8 * (size_t)row_words((N + 63) / 64));
+}
+
+static int32_t ensure_planes(tsat_solver* s, DBuf& buf, int32_t N, hipStream_t st)
+{
+    const size_t bytes = planes_bytes(s, N);
     if (buf.p && buf.bytes >= bytes) return TSAT_OK;
     RET(buf.alloc(bytes, "clause planes"));
     HIPCHK(launch_fill_u32(buf.as<uint32_t>(), (int64_t)(bytes / 4), 0u, st));
@@ -563,10 +570,13 @@ static SminArgs smin_args(tsat_solver* s, const tsat_params& p, int32_t N, int32
 
 // Persistent variable-major kernels: by default as many blocks as the CUs
 // hold at the kernel's occupancy, times 4 (measured faster than exactly one
-// resident round: waves that finish early pick up the remaining blocks).
+// resident round: waves that finish early pick up the remaining blocks); 16
+// per CU for the gradient and adjoint passes (V = 4e5, N = 256 gradient
+// 311 us, 328 at 32; V = 1e5 mixed adjoint 110 and 113; V = 2e5, N = 128
+// adjoint 64 and 63).
 static int var_blocks(const tsat_solver* s, int32_t V, int occ = 0)
 {
-    const int per_cu = s->var_per_cu > 0 ? s->var_per_cu : (occ > 0 ? 4 * occ : 32);
+    const int per_cu = s->var_per_cu > 0 ? s->var_per_cu : (occ > 0 ? 4 * occ : 16);
     const int64_t want = ((int64_t)V + 3) / 4;
     return (int)std::max<int64_t>(1, std::min<int64_t>(want, (int64_t)s->cus * per_cu));
 }
@@ -838,6 +848,10 @@ static int32_t load_store(tsat_solver* s, Store&& st)
     s->scr_Np = 0;
     s->prop_valid = false;
     s->st = std::move(st);
+    {
+        static std::atomic<uint64_t> loads{0};
+        s->load_id = ++loads;
+    }
     for (int k = 0; k <= s->st.K; ++k) {
         const auto& codes = s->st.buckets[k];
         const int64_t cnt = s->st.width_count[k];
@@ -1354,22 +1368,37 @@ int32_t tsat_device_clock_hz(tsat_solver* s, double* hz)
     return TSAT_OK;
 }
 
-// stateless forward + SmoothMin of literal rows `lits` (N candidates)
+// Where a forward leaves what its backward needs (caller memory).
+struct SavedView {
+    uint32_t* H = nullptr;      // [Np][K1] histogram
+    double* mu = nullptr;       // [V] row means (loss only)
+    uint32_t* planes = nullptr; // clause planes, when the update gathers them
+    uint64_t* lits = nullptr;   // else the literal rows
+};
+
+// stateless forward + SmoothMin of literal rows `lits` (N candidates).  The
+// clause planes are written for a backward (table, saved) and where several
+// buckets share a launch (the histogram of the wide clauses is taken from
+// them); a lone forward of one narrow width leaves them out (large
+// configuration: 262 MB).
 static int32_t eval_rows(tsat_solver* s, const tsat_params& p, const uint64_t* lits, int32_t N, const float* dS,
                          uint32_t* H_out, float* S32, double* S64, int64_t* sat, float* table, hipStream_t st,
-                         float* loss_out = nullptr, const float* dloss = nullptr)
+                         float* loss_out = nullptr, const float* dloss = nullptr, const SavedView* saved = nullptr)
 {
     const int32_t W = (N + 63) / 64, Np = 64 * W;
     uint32_t* planes = nullptr;
-    if (plane_path(s, N)) {
+    if (saved) {
+        planes = saved->planes;
+    } else if (plane_path(s, N) && (table || s->st.K > 4 || multi_path(s, N))) {
         RET(ensure_planes(s, s->planes_scr, N, st));
         planes = s->planes_scr.as<uint32_t>();
     }
-    RET(ensure_partial(s, s->partial_scr, N));
+    if (table) RET(ensure_partial(s, s->partial_scr, N));
     RET(enqueue_fwd(s, lits, N, s->H_scr.as<uint32_t>(), nullptr, nullptr, st, planes));
     SminArgs a = smin_args(s, p, N, Np);
     a.H = s->H_scr.as<uint32_t>();
     a.H_last = H_out;
+    a.H_save = saved ? saved->H : nullptr;
     a.table = table;
     a.S_out = S32;
     a.S64_out = S64;
@@ -1872,7 +1901,7 @@ int32_t tsat_fwd_dev_noalloc(tsat_solver* s, const uint64_t* bits, int32_t N, fl
 // Eq. 5 + Eq. 2 of caller logits into the scratch literal rows (and row
 // means), optionally also the value rows and 0/1 floats for the caller.
 static int32_t dev_binarize(tsat_solver* s, const float* theta, int32_t N, int32_t mode, uint64_t* vbits, float* assign,
-                            double* mu, hipStream_t st)
+                            double* mu, hipStream_t st, uint64_t* lits = nullptr)
 {
     RET(need_single(s));
     RET(ensure_scratch(s, N));
@@ -1882,7 +1911,7 @@ static int32_t dev_binarize(tsat_solver* s, const float* theta, int32_t N, int32
     p.norm_mode = mode;
     VarArgs a = var_args(s, p, N, W, 64 * W);
     a.theta = const_cast<float*>(theta); // read only by the binarize op
-    a.lits_next = s->lits_scr.as<uint64_t>();
+    a.lits_next = lits ? lits : s->lits_scr.as<uint64_t>();
     a.mu_next = mu ? mu : s->mu_scr.as<double>();
     a.vbits_out = vbits;
     a.assign_out = assign;
@@ -1968,6 +1997,161 @@ int32_t tsat_loss_backward_dev(tsat_solver* s, const float* theta, int32_t N, fl
     va.g_out = g;
     HIPCHK(launch_var(va, VOP_GRAD, var_blocks(s, s->st.V), st));
     return TSAT_OK;
+}
+
+// ------------------------------------------- forwards saved for a backward
+
+// Parts of the caller's buffer, each at a multiple of 256 bytes.
+static size_t saved_layout(const tsat_solver* s, int32_t N, uint8_t* base, SavedView* v)
+{
+    const size_t W = (size_t)(N + 63) / 64, V = (size_t)s->st.V;
+    size_t need = 0;
+    auto part = [&](size_t bytes) {
+        uint8_t* p = base ? base + need : nullptr;
+        need += (bytes + 255) & ~(size_t)255;
+        return p;
+    };
+    v->H = reinterpret_cast<uint32_t*>(part(64 * W * K1_of(s) * 4));
+    v->mu = reinterpret_cast<double*>(part(V * 8));
+    if (plane_path(s, N)) v->planes = reinterpret_cast<uint32_t*>(part(planes_bytes(s, N)));
+    else v->lits = reinterpret_cast<uint64_t*>(part((2 * V * W + 16) * 8));
+    return need;
+}
+
+// What the layout and contents depend on besides N: the CNF (each load has
+// its own number, over all solvers), and which planes the forward writes.
+static uint64_t saved_key(const tsat_solver* s, int32_t N)
+{
+    return (s->load_id << 2) | (plane_path(s, N) ? 1u : 0u) | (packed_planes(s, N) ? 2u : 0u);
+}
+
+static int32_t check_saved(tsat_solver* s, int32_t N, void* saved, int64_t bytes, SavedView* v)
+{
+    if (!saved || reinterpret_cast<uintptr_t>(saved) % 256) return fail(TSAT_E_ARG, "saved must be 256-byte aligned device memory");
+    const size_t need = saved_layout(s, N, static_cast<uint8_t*>(saved), v);
+    if (bytes < 0 || (size_t)bytes < need) return fail(TSAT_E_ARG, "saved holds %lld bytes, %zu needed", (long long)bytes, need);
+    return TSAT_OK;
+}
+
+// the backward of a saved forward: the table from its histogram, the gather
+// over its planes (or literal rows)
+static int32_t saved_backward(tsat_solver* s, const tsat_params& p, int32_t N, const SavedView& v, const float* theta,
+                              const float* dS, const float* dloss, float* U, float* g, int op, hipStream_t st)
+{
+    const int32_t W = (N + 63) / 64, Np = 64 * W;
+    RET(ensure_scratch(s, N));
+    RET(ensure_partial(s, s->partial_scr, N));
+    SminArgs a = smin_args(s, p, N, Np);
+    a.H = v.H;
+    a.H_reps = 1;
+    a.zero_H = 0;
+    a.table = s->table_scr.as<float>();
+    a.dS = dS;
+    a.dloss = dloss;
+    a.update = 0;
+    HIPCHK(launch_smin(a, st));
+    VarArgs va = var_args(s, p, N, W, Np);
+    va.tbl = s->table_scr.as<float>();
+    va.theta = const_cast<float*>(theta); // read only by the gradient op
+    va.planes = v.planes;
+    va.lits_cur = v.lits ? v.lits : s->lits_scr.as<uint64_t>(); // the plane gathers of these ops use no rows
+    va.mu_cur = v.mu;
+    va.U_out = U;
+    va.g_out = g;
+    HIPCHK(launch_var(va, op, var_blocks(s, s->st.V), st));
+    return TSAT_OK;
+}
+
+int32_t tsat_saved_bytes(tsat_solver* s, int32_t N, int64_t* bytes)
+{
+    g_err.clear();
+    RET(need_loaded(s));
+    RET(need_single(s));
+    if (!bytes) return fail(TSAT_E_ARG, "bytes is NULL");
+    if (N < 1 || N > TSAT_MAX_STEP_N) return fail(TSAT_E_ARG, "N must be in [1, %d]", TSAT_MAX_STEP_N);
+    SavedView v;
+    *bytes = (int64_t)saved_layout(s, N, nullptr, &v);
+    return TSAT_OK;
+}
+
+int32_t tsat_fwd_save_dev(tsat_solver* s, const uint64_t* bits, int32_t N, float tau, float* S, void* saved,
+                          int64_t bytes, uint64_t* key, void* stream)
+{
+    g_err.clear();
+    RET(need_loaded(s));
+    if (N < 1 || N > TSAT_MAX_STEP_N || !bits || !key || !(tau >= 0.f)) return fail(TSAT_E_ARG, "invalid arguments");
+    RET(need_single(s));
+    SavedView v;
+    RET(check_saved(s, N, saved, bytes, &v));
+    hipStream_t st = (hipStream_t)stream;
+    RET(ensure_scratch(s, N));
+    RET(prepare_units(s, N));
+    uint64_t* lits = v.lits ? v.lits : s->lits_scr.as<uint64_t>();
+    HIPCHK(launch_expand(bits, s->st.V, (N + 63) / 64, N, lits, st));
+    tsat_params p = s->params;
+    p.tau = tau;
+    RET(eval_rows(s, p, lits, N, nullptr, nullptr, S, nullptr, nullptr, nullptr, st, nullptr, nullptr, &v));
+    *key = saved_key(s, N);
+    return TSAT_OK;
+}
+
+int32_t tsat_bwd_saved_dev(tsat_solver* s, const uint64_t* bits, int32_t N, float tau, const float* dS, float* U,
+                           void* saved, int64_t bytes, uint64_t key, void* stream)
+{
+    g_err.clear();
+    RET(need_loaded(s));
+    if (N < 1 || N > TSAT_MAX_STEP_N || !bits || !dS || !U || !(tau >= 0.f)) return fail(TSAT_E_ARG, "invalid arguments");
+    RET(need_single(s));
+    const int32_t W = (N + 63) / 64;
+    if (key != saved_key(s, N)) return tsat_bwd_dev(s, bits, N, tau, dS, U, stream);
+    SavedView v;
+    RET(check_saved(s, N, saved, bytes, &v));
+    if ((size_t)K1_of(s) * 64 * W * 4 > 64 * 1024) return fail(TSAT_E_ARG, "table exceeds 64 KiB");
+    RET(check_row_offsets(s, W));
+    tsat_params p = s->params;
+    p.tau = tau;
+    return saved_backward(s, p, N, v, nullptr, dS, nullptr, U, nullptr, VOP_ADJ, (hipStream_t)stream);
+}
+
+int32_t tsat_loss_save_dev(tsat_solver* s, const float* theta, int32_t N, float tau, int32_t mode, float* loss,
+                           void* saved, int64_t bytes, uint64_t* key, void* stream)
+{
+    g_err.clear();
+    RET(dev_args(s, N, mode, theta, tau));
+    if (!loss || !key) return fail(TSAT_E_ARG, "NULL output");
+    RET(need_single(s));
+    RET(check_row_offsets(s, (N + 63) / 64));
+    SavedView v;
+    RET(check_saved(s, N, saved, bytes, &v));
+    hipStream_t st = (hipStream_t)stream;
+    RET(dev_binarize(s, theta, N, mode, nullptr, nullptr, v.mu, st, v.lits));
+    tsat_params p = s->params;
+    p.tau = tau;
+    p.norm_mode = mode;
+    RET(eval_rows(s, p, v.lits ? v.lits : s->lits_scr.as<uint64_t>(), N, nullptr, nullptr, nullptr, nullptr, nullptr,
+                  nullptr, st, loss, nullptr, &v));
+    *key = saved_key(s, N);
+    return TSAT_OK;
+}
+
+int32_t tsat_loss_backward_saved_dev(tsat_solver* s, const float* theta, int32_t N, float tau, int32_t mode,
+                                     const float* dloss, float* g, float* U, void* saved, int64_t bytes, uint64_t key,
+                                     void* stream)
+{
+    g_err.clear();
+    RET(dev_args(s, N, mode, theta, tau));
+    if (!g) return fail(TSAT_E_ARG, "g is NULL");
+    RET(need_single(s));
+    if (key != saved_key(s, N)) return tsat_loss_backward_dev(s, theta, N, tau, mode, dloss, g, U, stream);
+    const int32_t W = (N + 63) / 64;
+    SavedView v;
+    RET(check_saved(s, N, saved, bytes, &v));
+    if ((size_t)K1_of(s) * 64 * W * 4 > 64 * 1024) return fail(TSAT_E_ARG, "table exceeds 64 KiB");
+    RET(check_row_offsets(s, W));
+    tsat_params p = s->params;
+    p.tau = tau;
+    p.norm_mode = mode;
+    return saved_backward(s, p, N, v, theta, nullptr, dloss, U, g, VOP_GRAD, (hipStream_t)stream);
 }
 
 // ------------------------------------------------------------------ timing

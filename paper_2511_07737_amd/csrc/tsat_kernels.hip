@@ -528,6 +528,7 @@ __global__ __launch_bounds__(256) void smin_kernel(SminArgs a)
             for (int j = 0; j < 4; ++j) {
                 const int e = 4 * g + j, c = e / K1, r = e - c * K1;
                 s_h[c * hs + r] = h[j];
+                if (a.H_save) a.H_save[(size_t)i0 * K1 + e] = h[j];
                 if (a.H_last && i0 + c < a.N)
                     a.H_last[(ob + i0) * K1 + e] = h[j] + (r == 0 ? (uint32_t)info.n_empty : 0u);
             }
@@ -683,26 +684,28 @@ __device__ __forceinline__ double clamp_mu(double mu, bool& clamped)
     return clamped ? ((mu >= 0.0) ? 1e-12 : -1e-12) : mu;
 }
 
-// Pack B(theta_norm) of one variable row into its two literal rows.
+// Pack B(theta_norm) of one variable row into its two literal rows: their
+// 2 W words are consecutive, lane j < W stores word j of the value row and
+// lane W + j of the complement (one store instruction per variable, not 2 W).
 template <int J>
 __device__ __forceinline__ void write_bits(const VarArgs& a, uint32_t v, uint32_t lane, const float (&th)[J],
                                           const bool (&valid)[J], bool pos)
 {
     const int W = a.W;
+    uint64_t word = 0;
 #pragma unroll
     for (int j = 0; j < J; ++j) {
         if (j >= W) break;
         const bool p = valid[j] && (pos ? th[j] > 0.f : th[j] < 0.f);
         const uint64_t bal = ballot64(p);
         const uint64_t vm = ballot64(valid[j]);
-        if (lane == 0) {
-            if (a.lit_rows) { // row v is a literal of its own
-                a.lits_next[(size_t)v * W + j] = bal;
-            } else {
-                a.lits_next[(size_t)(2 * v) * W + j] = bal;
-                a.lits_next[(size_t)(2 * v + 1) * W + j] = ~bal & vm;
-            }
-        }
+        word = (int)lane == j ? bal : word;
+        word = (int)lane == W + j ? ~bal & vm : word;
+    }
+    if (a.lit_rows) { // row v is a literal of its own
+        if ((int)lane < W) a.lits_next[(size_t)v * W + lane] = word;
+    } else if ((int)lane < 2 * W) {
+        a.lits_next[(size_t)(2 * v) * W + lane] = word;
     }
 }
 
@@ -771,7 +774,14 @@ __device__ __forceinline__ void var_tail(const VarArgs& a, const StepScalars& c,
             for (int j = 0; j < J; ++j)
                 if (valid[j]) a.U_out[(size_t)v * N + 64 * j + lane] = (float)U[j];
         }
-        if (OP == OP_ADJ) return;
+        if (OP == OP_ADJ) { // without the Eq. 5 normalization the gradient is U
+            if (a.g_out) {
+#pragma unroll
+                for (int j = 0; j < J; ++j)
+                    if (valid[j]) store_g(a, v, 64u * j + lane, (float)U[j]);
+            }
+            return;
+        }
     }
     float g[J];
     norm_backward_row<J>(a, th, U, mu, clamped, g);
@@ -944,39 +954,50 @@ __device__ void mix_rows(const VarArgs& a)
 }
 
 // theta -> row means and literal rows (initialization, set_logits/state).
-template <int J>
+// A wave takes R consecutive variables, all their loads in flight before the
+// first row sum: one row at a time leaves a wave waiting for memory and then
+// for the sum's lane exchanges in turn (V = 4e5, N = 256, 410 MB: 207 us at
+// R = 1, 136 at R = 4, 3.4 TB/s with the rows written; 8 the same).
+template <int J, int R>
 __global__ __launch_bounds__(256) void binarize_kernel(VarArgs a)
 {
     const uint32_t lane = __lane_id();
     const uint32_t wave0 = uniform(blockIdx.x * 4u + threadIdx.x / 64u);
     const uint32_t nwaves = uniform(gridDim.x * 4u);
-    for (uint32_t v = wave0; v < (uint32_t)a.V; v += nwaves) {
-        float th[J];
+    for (uint32_t v0 = wave0 * R; v0 < (uint32_t)a.V; v0 += nwaves * R) {
+        float th[R][J];
         bool valid[J];
 #pragma unroll
-        for (int j = 0; j < J; ++j) {
-            const int i = 64 * j + (int)lane;
-            valid[j] = i < a.N;
-            th[j] = valid[j] ? a.theta[(size_t)v * a.N + i] : 0.f;
-        }
-        bool pos = true;
-        if (a.mode == 1) {
-            // the same arithmetic as the update's new row mean, so that a
-            // state set from a checkpoint binarizes exactly as the run did
-            const double mu = row_sum<J>([&](int j) { return (double)th[j]; }) * a.inv_n;
-            if (lane == 0) a.mu_next[v] = mu;
-            pos = mu >= 0.0;
-        } else if (lane == 0) {
-            a.mu_next[v] = 1.0;
-        }
-        write_bits<J>(a, v, lane, th, valid, pos);
-        if (a.vbits_out || a.assign_out) {
+        for (int q = 0; q < R; ++q)
 #pragma unroll
             for (int j = 0; j < J; ++j) {
-                const bool b = valid[j] && (pos ? th[j] > 0.f : th[j] < 0.f);
-                const uint64_t bal = ballot64(b);
-                if (a.vbits_out && j < a.W && lane == 0) a.vbits_out[(size_t)v * a.W + j] = bal;
-                if (a.assign_out && valid[j]) a.assign_out[(size_t)v * a.N + 64 * j + lane] = b ? 1.f : 0.f;
+                const int i = 64 * j + (int)lane;
+                valid[j] = i < a.N;
+                th[q][j] = valid[j] && v0 + q < (uint32_t)a.V ? a.theta[(size_t)(v0 + q) * a.N + i] : 0.f;
+            }
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            const uint32_t v = v0 + q;
+            if (R > 1 && v >= (uint32_t)a.V) break; // wave-uniform
+            bool pos = true;
+            if (a.mode == 1) {
+                // the same arithmetic as the update's new row mean, so that a
+                // state set from a checkpoint binarizes exactly as the run did
+                const double mu = row_sum<J>([&](int j) { return (double)th[q][j]; }) * a.inv_n;
+                if (lane == 0) a.mu_next[v] = mu;
+                pos = mu >= 0.0;
+            } else if (lane == 0) {
+                a.mu_next[v] = 1.0;
+            }
+            write_bits<J>(a, v, lane, th[q], valid, pos);
+            if (a.vbits_out || a.assign_out) {
+#pragma unroll
+                for (int j = 0; j < J; ++j) {
+                    const bool b = valid[j] && (pos ? th[q][j] > 0.f : th[q][j] < 0.f);
+                    const uint64_t bal = ballot64(b);
+                    if (a.vbits_out && j < a.W && lane == 0) a.vbits_out[(size_t)v * a.W + j] = bal;
+                    if (a.assign_out && valid[j]) a.assign_out[(size_t)v * a.N + 64 * j + lane] = b ? 1.f : 0.f;
+                }
             }
         }
     }
@@ -1569,27 +1590,75 @@ __device__ __forceinline__ void var_pure_body(const VarArgs& a)
     }
 }
 
-// U of one variable row from packed plane counts: cnt[r - 1][j] holds, for
-// candidate 64 j + lane, the positive records whose clause has R >= r in its
-// low 16 bits and the negative ones in its high 16 bits (r = 3: R = 3); dp /
-// dn are the record counts and my_gt the lane-private dL/dR table
-// ([r][j][lane]).  U = sum over r of (positive - negative records with R = r)
-// dL/dR[r], in the order of r as in the other uniform-width gathers, so that
-// every gather gives identical results.
+// Counts of the window gathers.  cnt[r - 1][j] collects, for candidate
+// 64 j + lane and level r, (positive - negative records whose clause has
+// R >= r) + (negative records): with the positive records' window bits in mp
+// and the negative ones' in mn, popc((G & (mp | mn)) ^ mn) = popc(G & mp) +
+// |mn| - popc(G & mn), one bitwise operation and one popcount per level and
+// dword.  (A popcount per sign, packed in 16-bit halves, took ten
+// instructions per level and word; the instruction stream is a large share
+// of these kernels' time: V = 4e5, N = 256 gradient 359 -> 326 us, large
+// update 1320 -> 1302, N = 1000 update 358 -> 345.)
+// T: the window's words, or the dwords of one half of them.
+template <int J, int KW, typename T>
+__device__ __forceinline__ void count_planes(const T (&b0)[J], const T (&b1)[J], T mp, T mn, uint32_t (&cnt)[KW][J])
+{
+    const T m = mp | mn;
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const T ge[3] = {b0[j] | b1[j], b1[j], b0[j] & b1[j]}; // R >= 1, R >= 2, R = 3
+#pragma unroll
+        for (int r = 0; r < KW; ++r) {
+            const T x = (ge[r] & m) ^ mn;
+            if constexpr (sizeof(T) == 8) cnt[r][j] += (uint32_t)__popcll(x);
+            else cnt[r][j] += (uint32_t)__popc(x);
+        }
+    }
+}
+
+// the records of one variable in the wave's window (win[(p J + j) 64 + lane])
+template <int J, int KW>
+__device__ __forceinline__ void count_window(const uint64_t* win, uint32_t lane, uint64_t mp, uint64_t mn,
+                                             uint32_t (&cnt)[KW][J])
+{
+    const uint64_t m = mp | mn;
+    if ((uint32_t)(m >> 32) == 0u || (uint32_t)m == 0u) { // wave-uniform
+        // they lie in one 32-bit half (most do): count on its dwords only
+        const uint32_t hf = (uint32_t)m == 0u ? 1u : 0u;
+        const uint32_t* win32 = reinterpret_cast<const uint32_t*>(win);
+        uint32_t b0[J], b1[J];
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            b0[j] = win32[2 * (j * 64 + lane) + hf];
+            b1[j] = win32[2 * ((J + j) * 64 + lane) + hf];
+        }
+        count_planes<J, KW, uint32_t>(b0, b1, (uint32_t)(mp >> (32u * hf)), (uint32_t)(mn >> (32u * hf)), cnt);
+    } else {
+        uint64_t b0[J], b1[J];
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            b0[j] = win[j * 64 + lane];
+            b1[j] = win[(J + j) * 64 + lane];
+        }
+        count_planes<J, KW, uint64_t>(b0, b1, mp, mn, cnt);
+    }
+}
+
+// U of one variable row from these counts: dp / dn are the record counts and
+// my_gt the lane-private dL/dR table ([r][j][lane]).  U = sum over r of
+// (positive - negative records with R = r) dL/dR[r], in the order of r as in
+// the other uniform-width gathers, so that every gather gives identical
+// results.
 template <int J, int KW>
 __device__ __forceinline__ void plane_u(const uint32_t (&cnt)[KW][J], uint32_t dp, uint32_t dn, const float* my_gt,
                                         uint32_t lane, double (&U)[J])
 {
-    const uint32_t total = dp | (dn << 16);
 #pragma unroll
     for (int j = 0; j < J; ++j) {
         float u = 0.f;
 #pragma unroll
         for (int r = 0; r <= KW; ++r) {
-            // records with R = r, both signs at once (no borrow: each half of
-            // the minuend is at least that of the subtrahend)
-            const uint32_t e = (r == 0 ? total : cnt[r - 1][j]) - (r < KW ? cnt[r][j] : 0u);
-            const int32_t d = (int32_t)(e & 0xffffu) - (int32_t)(e >> 16);
+            const int32_t d = (int32_t)(r == 0 ? dp : cnt[r - 1][j]) - (int32_t)(r < KW ? cnt[r][j] : dn);
             u = fmaf((float)d, my_gt[(r * J + j) * 64 + lane], u);
         }
         U[j] = (double)u;
@@ -1942,9 +2011,6 @@ __global__ __launch_bounds__(256) void var_window_kernel(VarArgs a)
                 load_gt<J, K1>(a, vi.inst, my_gt, lane);
             }
             const uint32_t r0 = sload(a.occ_off + v), rm = sload(a.occ_mid + v), r1 = sload(a.occ_off + v + 1);
-            // counts per level r and word j: positive records in the low
-            // 16 bits, negative in the high (the host keeps every variable
-            // below 2^16 records per sign on this path)
             uint32_t cnt[KW][J];
 #pragma unroll
             for (int r = 0; r < KW; ++r)
@@ -1959,17 +2025,7 @@ __global__ __launch_bounds__(256) void var_window_kernel(VarArgs a)
                 const uint32_t hi = r1 < w + 64u ? r1 : w + 64u;
                 const uint64_t mp = q < rm ? bit_range(q - w, (hi < rm ? hi : rm) - w) : 0ull;
                 const uint64_t mn = hi > rm ? bit_range((q > rm ? q : rm) - w, hi - w) : 0ull;
-#pragma unroll
-                for (int j = 0; j < J; ++j) {
-                    const uint64_t b0 = my_win[j * 64 + lane], b1 = my_win[(J + j) * 64 + lane];
-                    const uint64_t b01 = b0 | b1; // R >= 1 (b1: R >= 2)
-                    cnt[0][j] += (uint32_t)__popcll(b01 & mp) + ((uint32_t)__popcll(b01 & mn) << 16);
-                    cnt[1][j] += (uint32_t)__popcll(b1 & mp) + ((uint32_t)__popcll(b1 & mn) << 16);
-                    if constexpr (KW == 3) { // R = 3
-                        const uint64_t b3 = b0 & b1;
-                        cnt[2][j] += (uint32_t)__popcll(b3 & mp) + ((uint32_t)__popcll(b3 & mn) << 16);
-                    }
-                }
+                count_window<J, KW>(my_win, lane, mp, mn, cnt);
                 q = hi;
             }
             float th[J], mm[J], vv[J];
@@ -2000,10 +2056,10 @@ __global__ __launch_bounds__(256) void var_window_kernel(VarArgs a)
 // time: every wave requests its share of their rows, counts their records,
 // and the two row sums of each variable (Eq. 5 backward, new mean) are added
 // over the team in LDS, all three variables between the same two barriers
-// (two variables 376 us, four 381).
+// (three 358 us, two 376, four 381 before the one-popcount counts).
 //
 // What bounds it: the theta, m, v streams and a plane row per record (V =
-// 5e4, C = 2.05e5, N = 1000: 1.2 GB and 0.16 GB a launch, 358 us = 3.8 TB/s,
+// 5e4, C = 2.05e5, N = 1000: 1.2 GB and 0.16 GB a launch, 345 us = 3.9 TB/s,
 // a copy of 5.1).  The row gather of var_pure_kernel, which these sizes took
 // before, reads two literal rows of 128 bytes per record through the scalar
 // cache, one wave per variable: 2346 us.
@@ -2114,17 +2170,7 @@ __global__ __launch_bounds__(256) void var_window_team_kernel(VarArgs a)
                 const uint32_t hi = r1 < w + 64u ? r1 : w + 64u;
                 const uint64_t mp = q < rm ? bit_range(q - w, (hi < rm ? hi : rm) - w) : 0ull;
                 const uint64_t mn = hi > rm ? bit_range((q > rm ? q : rm) - w, hi - w) : 0ull;
-#pragma unroll
-                for (int j = 0; j < J; ++j) {
-                    const uint64_t b0 = my_win[j * 64 + lane], b1 = my_win[(J + j) * 64 + lane];
-                    const uint64_t b01 = b0 | b1; // R >= 1 (b1: R >= 2)
-                    cnt[0][j] += (uint32_t)__popcll(b01 & mp) + ((uint32_t)__popcll(b01 & mn) << 16);
-                    cnt[1][j] += (uint32_t)__popcll(b1 & mp) + ((uint32_t)__popcll(b1 & mn) << 16);
-                    if constexpr (KW == 3) { // R = 3
-                        const uint64_t b3 = b0 & b1;
-                        cnt[2][j] += (uint32_t)__popcll(b3 & mp) + ((uint32_t)__popcll(b3 & mn) << 16);
-                    }
-                }
+                count_window<J, KW>(my_win, lane, mp, mn, cnt);
                 q = hi;
             }
             double U[J];
@@ -2159,7 +2205,14 @@ __global__ __launch_bounds__(256) void var_window_team_kernel(VarArgs a)
                 for (int j = 0; j < J; ++j)
                     if (valid[j]) a.U_out[row + 64 * j] = g[i][j];
             }
-            if (OP == OP_ADJ) continue;
+            if (OP == OP_ADJ) {
+                if (a.g_out) {
+#pragma unroll
+                    for (int j = 0; j < J; ++j)
+                        if (valid[j]) store_g(a, v, 64u * (word0 + j) + lane, g[i][j]);
+                }
+                continue;
+            }
             if (a.mode == 1) {
                 bool clamped;
                 const double mu = clamp_mu(sload(a.mu_cur + v), clamped);
@@ -2262,7 +2315,10 @@ __device__ __forceinline__ void pair_tail(const VarArgs& a, const StepScalars& c
     const size_t idx = (size_t)vl * a.N + l;
     if (OP == OP_ADJ || OP == OP_GRAD) {
         if (a.U_out && valid) a.U_out[idx] = (float)U;
-        if (OP == OP_ADJ) return;
+        if (OP == OP_ADJ) {
+            if (a.g_out && valid) store_g(a, vl, l, (float)U);
+            return;
+        }
     }
     float g;
     if (a.mode == 1) {
@@ -2419,14 +2475,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void v
                 const uint64_t mpa = window_bits(pa0, pam, q, qe, w), mna = window_bits(pam, pa1, q, qe, w);
                 const uint64_t mpb = window_bits(pb0, pbm, q, qe, w), mnb = window_bits(pbm, pb1, q, qe, w);
                 const uint64_t mp = h ? mpb : mpa, mn = h ? mnb : mna;
-                const uint64_t b0 = my_win[l], bb1 = my_win[32 + l];
-                const uint64_t b01 = b0 | bb1; // R >= 1 (bb1: R >= 2)
-                cnt[0][0] += (uint32_t)__popcll(b01 & mp) + ((uint32_t)__popcll(b01 & mn) << 16);
-                cnt[1][0] += (uint32_t)__popcll(bb1 & mp) + ((uint32_t)__popcll(bb1 & mn) << 16);
-                if constexpr (KW == 3) {
-                    const uint64_t b3 = b0 & bb1;
-                    cnt[2][0] += (uint32_t)__popcll(b3 & mp) + ((uint32_t)__popcll(b3 & mn) << 16);
-                }
+                const uint64_t b0[1] = {my_win[l]}, b1[1] = {my_win[32 + l]};
+                count_planes<1, KW, uint64_t>(b0, b1, mp, mn, cnt);
                 q = qe;
             }
             const bool valid = live && (int)l < N;
@@ -3299,9 +3349,13 @@ __global__ __launch_bounds__(256) void rank_kernel(const int64_t* __restrict__ s
 // once and the variables split over the chip: four digit passes (a histogram
 // per slot and 8-bit digit), a counting pass (keys below and equal to the
 // k-th, per chunk), a collecting pass, and a sort of each slot's k keys.
-// The passes read the keys from the last-level cache (V = 2e5, 16 slots:
-// 12.8 MB); one block per candidate walking its column five times took
-// SEL_OLD.
+// The passes read the keys from the last-level cache; what bounds them is
+// each launch's latency and its closing adds (eight histogram replicas, one
+// per XCD).  V = 2e5, 16 slots, k = 20: four digit passes of 9.9 us, count
+// 9.4, collect 14.2, sort 5.8; one block per candidate, walking its column
+// of a transposed gradient five times, took 2.2 ms, and the transposed
+// store of every candidate's gradient 0.19 ms of the 0.28 ms gradient pass
+// (0.09 ms now, storing the selected columns row by row).
 // ---------------------------------------------------------------------------
 
 constexpr int kSelTile = 32; // slots of a block
@@ -3725,7 +3779,19 @@ static hipError_t launch_var_jm(const VarArgs& a, int op, int blocks, hipStream_
     case OP_GRAD: hipLaunchKernelGGL((var_kernel<J, OP_GRAD, MULTI>), dim3(blocks), dim3(256), lds, st, a); break;
     case OP_ADJ: hipLaunchKernelGGL((var_kernel<J, OP_ADJ, MULTI>), dim3(blocks), dim3(256), lds, st, a); break;
     case OP_NORMBWD: hipLaunchKernelGGL((norm_backward_kernel<J>), dim3(blocks), dim3(256), 0, st, a); break;
-    default: hipLaunchKernelGGL((binarize_kernel<J>), dim3(blocks), dim3(256), 0, st, a); break;
+    default: {
+        // several rows per wave once the variables fill the chip's waves
+        // without it (256 CUs of 32); below that the rows run side by side
+        constexpr int R = J <= 2 ? 8 : (J == 4 ? 4 : (J == 8 ? 2 : 1));
+        const bool many = R > 1 && a.V >= 8192 * R;
+        if (many) {
+            const unsigned want = (unsigned)((a.V + 4 * R - 1) / (4 * R));
+            hipLaunchKernelGGL((binarize_kernel<J, R>), dim3(want), dim3(256), 0, st, a);
+        } else {
+            hipLaunchKernelGGL((binarize_kernel<J, 1>), dim3(blocks), dim3(256), 0, st, a);
+        }
+        break;
+    }
     }
     return hipGetLastError();
 }
@@ -3953,6 +4019,9 @@ static int occupancy_levels_j(const VarArgs& a)
 
 hipError_t launch_var(const VarArgs& a, int op, int blocks, hipStream_t st)
 {
+    // without the Eq. 5 normalization a gradient is the adjoint itself: no
+    // theta to read
+    if (op == OP_GRAD && a.mode != 1) op = OP_ADJ;
     const bool rowwise = op == OP_BINARIZE || op == OP_NORMBWD; // no gather
     if (a.occ_cid && a.planes && !rowwise && a.W > 4) return launch_team(a, op, blocks, st);
     if (a.occ_cid && a.planes && !rowwise) {

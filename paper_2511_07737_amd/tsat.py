@@ -138,6 +138,11 @@ _SIGS = [
     ("tsat_norm_backward_dev", _i32, [_P, _P, _P, _i32, _i32, _P, _P]),
     ("tsat_loss_dev", _i32, [_P, _P, _i32, _f32, _i32, _P, _P, _P, _P]),
     ("tsat_loss_backward_dev", _i32, [_P, _P, _i32, _f32, _i32, _P, _P, _P, _P]),
+    ("tsat_saved_bytes", _i32, [_P, _i32, ct.POINTER(_i64)]),
+    ("tsat_fwd_save_dev", _i32, [_P, _P, _i32, _f32, _P, _P, _i64, ct.POINTER(_u64), _P]),
+    ("tsat_bwd_saved_dev", _i32, [_P, _P, _i32, _f32, _P, _P, _P, _i64, _u64, _P]),
+    ("tsat_loss_save_dev", _i32, [_P, _P, _i32, _f32, _i32, _P, _P, _i64, ct.POINTER(_u64), _P]),
+    ("tsat_loss_backward_saved_dev", _i32, [_P, _P, _i32, _f32, _i32, _P, _P, _P, _P, _i64, _u64, _P]),
     ("tsat_set_timing", _i32, [_P, _i32]),
     ("tsat_get_timing", _i32, [_P, ct.POINTER(_f64), ct.POINTER(_i32)]),
     ("tsat_copy_calibrate", _i32, [_P, _i64, ct.POINTER(_f64)]),
@@ -541,6 +546,37 @@ class Solver:
                           U_ptr: int | None, stream: int | None = None) -> None:
         _check(lib().tsat_loss_backward_dev(self._h, theta_ptr, int(n), float(tau), int(mode), dloss_ptr, g_ptr,
                                             U_ptr, stream))
+
+    # forwards saved for a backward (the saved forms take the forward's key)
+    def saved_bytes(self, n: int) -> int:
+        b = _i64()
+        _check(lib().tsat_saved_bytes(self._h, int(n), ct.byref(b)))
+        return int(b.value)
+
+    def fwd_save_dev(self, bits_ptr: int, n: int, tau: float, S_ptr: int | None, saved_ptr: int, nbytes: int,
+                     stream: int | None = None) -> int:
+        key = _u64()
+        _check(lib().tsat_fwd_save_dev(self._h, bits_ptr, int(n), float(tau), S_ptr, saved_ptr, int(nbytes),
+                                       ct.byref(key), stream))
+        return int(key.value)
+
+    def bwd_saved_dev(self, bits_ptr: int, n: int, tau: float, dS_ptr: int, U_ptr: int, saved_ptr: int, nbytes: int,
+                      key: int, stream: int | None = None) -> None:
+        _check(lib().tsat_bwd_saved_dev(self._h, bits_ptr, int(n), float(tau), dS_ptr, U_ptr, saved_ptr, int(nbytes),
+                                        int(key), stream))
+
+    def loss_save_dev(self, theta_ptr: int, n: int, tau: float, mode: int, loss_ptr: int, saved_ptr: int, nbytes: int,
+                      stream: int | None = None) -> int:
+        key = _u64()
+        _check(lib().tsat_loss_save_dev(self._h, theta_ptr, int(n), float(tau), int(mode), loss_ptr, saved_ptr,
+                                        int(nbytes), ct.byref(key), stream))
+        return int(key.value)
+
+    def loss_backward_saved_dev(self, theta_ptr: int, n: int, tau: float, mode: int, dloss_ptr: int | None,
+                                g_ptr: int, U_ptr: int | None, saved_ptr: int, nbytes: int, key: int,
+                                stream: int | None = None) -> None:
+        _check(lib().tsat_loss_backward_saved_dev(self._h, theta_ptr, int(n), float(tau), int(mode), dloss_ptr, g_ptr,
+                                                  U_ptr, saved_ptr, int(nbytes), int(key), stream))
 
     # timing ---------------------------------------------------------------
     def set_timing(self, enable: bool) -> None:
