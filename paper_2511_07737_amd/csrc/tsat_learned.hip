@@ -20,89 +20,128 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 // features
 // ---------------------------------------------------------------------------
 
-// One thread per variable walks its occurrence records (positive occurrences
+// Four lanes per variable walk its occurrence records (positive occurrences
 // first, then negative ones; each record lists the other literals of the
 // clause in clause order).  Clauses holding a variable and its negation are
 // skipped.  Round 0 counts and writes the base features and the channels h0;
-// round r (1..3) sums sgn(l_v) sgn(l_u) h_{r-1}[u] over co-literals.
+// round r (1..3) sums sgn(l_v) sgn(l_u) h_{r-1}[u] over co-literals, lane c
+// of a variable in channel c, in record order.
+//
+// A chain of dependent loads (record, then channels) per record: the four
+// lanes read one 16-byte channel group together and quadruple the waves that
+// hide it, and records of known width (uniform stores) are taken kBatch at a
+// time, all their loads in flight before the first sum.  V = 1e5, C = 4.1e5,
+// 3-SAT: 36 us per round with a thread per variable and a record at a
+// time, 17 us.
+constexpr int kBatch = 4;
+
+// sum over one record's co-literals of the signed channel value; false for a
+// tautology.  K1: co-literals (code[0 .. K1)).
+template <int K1>
+__device__ __forceinline__ bool feature_taut(const uint32_t (&code)[K1], uint32_t v)
+{
+    bool taut = false;
+#pragma unroll
+    for (int j = 0; j < K1; ++j) taut |= (code[j] >> 1) == v || (j > 0 && (code[j] >> 1) == (code[j - 1] >> 1));
+    return taut;
+}
+
+template <int K1>
+__device__ __forceinline__ void feature_records(const FeatArgs& a, uint32_t v, uint32_t ch, uint32_t beg, uint32_t mid,
+                                                uint32_t end, int32_t (&cnt)[2], float& acc)
+{
+    const float* h = (const float*)a.h_prev;
+    for (uint32_t w = beg; w < end; w += kBatch) {
+        uint32_t code[kBatch][K1];
+        float x[kBatch][K1];
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) {
+            const size_t rec = w + q < end ? w + q : end - 1;
+#pragma unroll
+            for (int j = 0; j < K1; ++j) code[q][j] = a.occ_data[rec * K1 + j];
+        }
+        if (a.round > 0) {
+#pragma unroll
+            for (int q = 0; q < kBatch; ++q)
+#pragma unroll
+                for (int j = 0; j < K1; ++j) x[q][j] = h[(size_t)(code[q][j] >> 1) * 4 + ch];
+        }
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) {
+            if (w + q >= end || feature_taut<K1>(code[q], v)) continue;
+            const int neg = w + q >= mid;
+            cnt[neg] += 1;
+            if (a.round == 0) continue;
+            float s = 0.f;
+#pragma unroll
+            for (int j = 0; j < K1; ++j) s = (code[q][j] & 1u) ? s - x[q][j] : s + x[q][j];
+            acc = neg ? acc - s : acc + s;
+        }
+    }
+}
+
 __global__ __launch_bounds__(256) void features_kernel(FeatArgs a)
 {
-    const int32_t v = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (v >= a.V) return;
-    const uint32_t end = a.occ_off[v + 1], mid = a.occ_mid[v];
-    const uint32_t pk1 = (uint32_t)(a.pure_k - 1);
-    int32_t pos = 0, neg = 0, wsum = 0, z = 0;
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    uint32_t w = a.occ_off[v];
-    while (w < end) {
-        const bool negv = w >= mid;
-        uint32_t km1, base;
-        if (a.pure_k) {
-            km1 = pk1;
-            base = w * pk1;
-            w += 1;
-        } else {
-            km1 = a.occ_data[w];
-            base = w + 1;
+    const uint32_t v = blockIdx.x * 64u + threadIdx.x / 4u, ch = threadIdx.x & 3u;
+    if (v >= (uint32_t)a.V) return;
+    const uint32_t beg = a.occ_off[v], end = a.occ_off[v + 1], mid = a.occ_mid[v];
+    int32_t cnt[2] = {0, 0}, wsum = 0, z = 0; // occurrences by sign, their widths, co-literals
+    float acc = 0.f;
+    if (a.pure_k) {
+        switch (a.pure_k) {
+        case 2: feature_records<1>(a, v, ch, beg, mid, end, cnt, acc); break;
+        case 3: feature_records<2>(a, v, ch, beg, mid, end, cnt, acc); break;
+        default: feature_records<3>(a, v, ch, beg, mid, end, cnt, acc); break;
+        }
+        wsum = (cnt[0] + cnt[1]) * a.pure_k;
+        z = (cnt[0] + cnt[1]) * (a.pure_k - 1);
+    } else {
+        const float* hp = (const float*)a.h_prev;
+        uint32_t w = beg;
+        while (w < end) {
+            const bool negv = w >= mid;
+            const uint32_t km1 = a.occ_data[w], base = w + 1;
             w += 1 + km1;
-        }
-        bool taut = false;
-        uint32_t prev_var = 0xffffffffu;
-        for (uint32_t j = 0; j < km1; ++j) {
-            const uint32_t u = a.occ_data[base + j] >> 1;
-            taut |= (u == (uint32_t)v) | (u == prev_var);
-            prev_var = u;
-        }
-        if (taut) continue;
-        if (a.round == 0) {
-            pos += negv ? 0 : 1;
-            neg += negv ? 1 : 0;
-            wsum += (int32_t)km1 + 1;
-            z += (int32_t)km1;
-        } else {
-            float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+            bool taut = false;
+            uint32_t prev_var = 0xffffffffu;
+            float s = 0.f;
             for (uint32_t j = 0; j < km1; ++j) {
-                const uint32_t c = a.occ_data[base + j];
-                const float4 h = a.h_prev[c >> 1];
-                if (c & 1u) {
-                    s.x -= h.x; s.y -= h.y; s.z -= h.z; s.w -= h.w;
-                } else {
-                    s.x += h.x; s.y += h.y; s.z += h.z; s.w += h.w;
+                const uint32_t c = a.occ_data[base + j], u = c >> 1;
+                taut |= (u == v) | (u == prev_var);
+                prev_var = u;
+                if (a.round > 0) {
+                    const float h = hp[(size_t)u * 4 + ch];
+                    s = (c & 1u) ? s - h : s + h;
                 }
             }
-            if (negv) {
-                acc.x -= s.x; acc.y -= s.y; acc.z -= s.z; acc.w -= s.w;
-            } else {
-                acc.x += s.x; acc.y += s.y; acc.z += s.z; acc.w += s.w;
-            }
+            if (taut) continue;
+            cnt[negv] += 1;
+            wsum += (int32_t)km1 + 1;
+            z += (int32_t)km1;
+            acc = negv ? acc - s : acc + s;
         }
     }
     float* x = a.X + (int64_t)v * kFeat;
     if (a.round == 0) {
-        const int32_t deg = pos + neg;
+        const int32_t pos = cnt[0], neg = cnt[1], deg = pos + neg;
         const float f0 = log1pf((float)pos), f1 = log1pf((float)neg);
         const float bias = (float)(pos - neg) / (float)(deg > 1 ? deg : 1);
-        x[0] = f0;
-        x[1] = f1;
-        x[2] = bias;
-        x[3] = deg > 0 ? (float)wsum / (float)deg * 0.25f : 0.f;
-        a.h_next[v] = make_float4(bias, (float)(pos - neg) / sqrtf((float)(deg > 1 ? deg : 1)), f0 - f1, 1.f);
-        a.zinv[v] = 1.f / (float)(z > 1 ? z : 1);
+        const float width = deg > 0 ? (float)wsum / (float)deg * 0.25f : 0.f;
+        const float norm = (float)(pos - neg) / sqrtf((float)(deg > 1 ? deg : 1));
+        x[ch] = ch == 0 ? f0 : (ch == 1 ? f1 : (ch == 2 ? bias : width));
+        ((float*)a.h_next)[(size_t)v * 4 + ch] = ch == 0 ? bias : (ch == 1 ? norm : (ch == 2 ? f0 - f1 : 1.f));
+        if (ch == 0) a.zinv[v] = 1.f / (float)(z > 1 ? z : 1);
     } else {
-        const float zi = a.zinv[v];
-        const float4 h = make_float4(acc.x * zi, acc.y * zi, acc.z * zi, acc.w * zi);
-        a.h_next[v] = h;
-        x[4 * a.round + 0] = h.x;
-        x[4 * a.round + 1] = h.y;
-        x[4 * a.round + 2] = h.z;
-        x[4 * a.round + 3] = h.w;
+        const float h = acc * a.zinv[v];
+        ((float*)a.h_next)[(size_t)v * 4 + ch] = h;
+        x[4 * a.round + ch] = h;
     }
 }
 
 hipError_t launch_features(const FeatArgs& a, hipStream_t st)
 {
     if (a.V <= 0) return hipSuccess;
-    hipLaunchKernelGGL(features_kernel, dim3((unsigned)((a.V + 255) / 256)), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(features_kernel, dim3((unsigned)((a.V + 63) / 64)), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 
@@ -393,13 +432,38 @@ __global__ __launch_bounds__(256) void mlp_kernel(MlpDev d, const float* __restr
     }
 }
 
-__global__ void mlp_reduce_kernel(MlpDev d, int blocks, int adam, float lr, float beta1, float beta2, float eps,
-                                  float bc1, float bc2)
+// Sum of the blocks' partial gradients in a fixed order, then Adam.  A block
+// takes kRedCols parameters: its kRedSegs thread groups each add a run of
+// consecutive blocks, eight loads in flight, and the runs are added in order.
+// (One thread per parameter adding all blocks one after the other waits for
+// memory 256 times: 61 us for 256 blocks; 7.7 us this way, 19 MB.)
+constexpr int kRedCols = 32, kRedSegs = 8;
+
+__global__ __launch_bounds__(256) void mlp_reduce_kernel(MlpDev d, int blocks, int adam, float lr, float beta1,
+                                                         float beta2, float eps, float bc1, float bc2)
 {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e > kNumParams) return;
+    __shared__ float s_sum[kRedSegs][kRedCols];
+    const int col = threadIdx.x % kRedCols, seg = threadIdx.x / kRedCols;
+    const int e = blockIdx.x * kRedCols + col;
+    const int run = (blocks + kRedSegs - 1) / kRedSegs;
+    const int b0 = seg * run, b1 = min(blocks, b0 + run);
+    float sum = 0.f;
+    if (e <= kNumParams) {
+        const float* p = d.partial + e;
+        for (int b = b0; b < b1; b += 8) {
+            float x[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) x[q] = b + q < b1 ? p[(int64_t)(b + q) * kPartialStride] : 0.f;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) sum += x[q];
+        }
+    }
+    s_sum[seg][col] = sum;
+    __syncthreads();
+    if (seg != 0 || e > kNumParams) return;
     float g = 0.f;
-    for (int b = 0; b < blocks; ++b) g += d.partial[(int64_t)b * kPartialStride + e];
+#pragma unroll
+    for (int q = 0; q < kRedSegs; ++q) g += s_sum[q][col];
     if (e == kNumParams) {
         *d.loss = g;
         return;
@@ -443,7 +507,7 @@ hipError_t launch_mlp_backward(const MlpDev& d, const float* X, const float* y, 
 hipError_t launch_mlp_reduce(const MlpDev& d, int blocks, int adam, float lr, float beta1, float beta2, float eps,
                              float bc1, float bc2, hipStream_t st)
 {
-    hipLaunchKernelGGL(mlp_reduce_kernel, dim3((kNumParams + 1 + 255) / 256), dim3(256), 0, st, d, blocks, adam, lr,
+    hipLaunchKernelGGL(mlp_reduce_kernel, dim3((kNumParams + kRedCols) / kRedCols), dim3(256), 0, st, d, blocks, adam, lr,
                        beta1, beta2, eps, bc1, bc2);
     return hipGetLastError();
 }
