@@ -547,7 +547,9 @@ typedef struct {
     int32_t clause_planes;     /* uniform widths 2, 3 (other widths up to 15 at N <= 256, with the window
                                   gather): 1 = the forward stores R of every
                                   clause in binary and the update gathers it (one record per
-                                  occurrence), 0 = the update gathers the other literals' rows */
+                                  occurrence), 0 = the update gathers the other literals' rows.
+                                  Other stores of mixed or wide clauses: 1 = the forward stores R
+                                  in bytes (up to 8 GiB) */
     int32_t window_gather;     /* with clause planes: 1 = the update loads the planes of 64 consecutive
                                   occurrence records per vector load and transposes their bits across
                                   the wavefront (up to 32 candidates: two variables per wavefront),

@@ -78,6 +78,8 @@ struct FwdArgs {
                             // 1 when a clause's two planes share one 8-byte word, N <= 32)
     int32_t plane_P;        // planes per clause (2 or 4)
     int64_t plane_base;     // global index of the bucket's first clause
+    uint8_t* rbytes;        // null, or [clauses][rb_stride]: R of every clause and candidate
+    int32_t rb_stride;      // bytes per clause, 64 ceil(N / 64)
     int32_t vrows;          // bits32 holds value rows only ([V][W2]); not-x is the complement
     int32_t nunits;         // work units of the launch
     int32_t xcd;            // XCD-aware unit order (grid rounded up to a multiple of 8)
@@ -161,6 +163,8 @@ struct VarArgs {
     // occ_mid), and the forward pass's planes of R for these bits
     const uint32_t* occ_cid;  // null: gather the other literals' rows instead
     const uint32_t* planes;   // [clauses][P][2 J] dwords
+    const uint8_t* rb;        // null, or the forward's bytes of R, [clauses][64 W]: generic
+                              // records gather these (occ_cid, cid_off, cid_mid)
     uint32_t narrow_end;      // clauses below this global index hold 2 planes, the rest 4 (after them)
     const uint32_t* cid_off;  // [V+1] record offsets of occ_cid
     const uint32_t* cid_mid;  // [V] first record of negative occurrences
@@ -178,6 +182,8 @@ struct VarArgs {
     const uint32_t* ch_var;   // [n_chunks]
     const uint32_t* ch_beg;   // [n_chunks] word range of the chunk's records
     const uint32_t* ch_end;   // [n_chunks]
+    const uint32_t* ch_rbeg;  // [n_chunks] its range of clause-index records
+    const uint32_t* ch_rend;  // [n_chunks]
     double* partial;          // [n_chunks][Np]
 };
 
@@ -200,7 +206,7 @@ struct SelectArgs {
 
 hipError_t launch_fwd(const FwdArgs& a, int nunits, int tiles, hipStream_t st);
 hipError_t launch_fwd_wide(const FwdArgs& a, int kmax, int nunits, int tiles, hipStream_t st);
-hipError_t launch_fwd_multi(const FwdArgs& a, int kmax, int nunits, hipStream_t st);
+hipError_t launch_fwd_multi(const FwdArgs& a, int kmax, int nunits, int tiles, hipStream_t st);
 hipError_t launch_planes_hist(const FwdArgs& a, int kmax, int nunits, hipStream_t st);
 hipError_t launch_smin(const SminArgs& a, hipStream_t st);
 hipError_t launch_adj_scatter(const uint32_t* codes, int64_t Cb, int k, int N, int K1, const uint32_t* bits32,

@@ -55,10 +55,12 @@ struct tsat_solver {
     DBuf occ_off, occ_mid, occ_data, var_inst, info;
     DBuf occ_cid;            // clause-index records (widths up to kMaxPlaneWidth)
     DBuf cid_off, cid_mid;   // their record offsets (stores with generic occurrence records)
+    DBuf wide_cid, wide_off, wide_mid; // the same of a store with clauses past kMaxPlaneWidth
+    bool bytes_off = false;  // the forward's bytes of R did not fit: row gather
     DBuf vchunk;             // work items of the mixed-width window gather: first variables
     int32_t n_vchunk = 0;
     DBuf planes, planes_scr; // R of every clause in binary, for the step / for evaluations
-    DBuf heavy, hv_var, hv_chunk, ch_var, ch_beg, ch_end; // chunked heavy variables (generic stores)
+    DBuf heavy, hv_var, hv_chunk, ch_var, ch_beg, ch_end, ch_rbeg, ch_rend; // chunked heavy variables (generic stores)
     DBuf partial, partial_scr; // FP64 partial sums of the chunks, for the step / for evaluations
 
     // independent literal rows (one logit row per literal, 2V rows): requested
@@ -102,7 +104,7 @@ struct tsat_solver {
     // forward work units of all wide buckets (widths > 4) in one launch, per clauses-per-wave
     std::map<int, std::pair<DBuf*, int>> wide_units;
     // forward work units of every bucket in one launch (mixed widths with
-    // clause planes), per clauses-per-thread
+    // clause planes), or of those up to width 4, per range of clauses
     std::map<int, std::pair<DBuf*, int>> multi_units;
 
     // learned proposal: features and aggregation channels, kept proposal
@@ -228,10 +230,13 @@ static int32_t bucket_units(tsat_solver* s, Bucket* b, const FwdGeom& g, const F
 // Make every bucket's unit table for N candidates resident (before a graph
 // capture, which must not allocate or copy).
 static int32_t wide_geometry(const tsat_solver* s, int32_t N, FwdGeom* g, int* kmax);
-static int32_t wide_units(tsat_solver* s, const FwdGeom& g, const FwdUnit** out, int* count);
+static int32_t wide_units(tsat_solver* s, const FwdGeom& g, bool lanes, const FwdUnit** out, int* count);
+static bool plane_path(const tsat_solver* s, int32_t N);
 static bool multi_path(const tsat_solver* s, int32_t N);
 static FwdGeom multi_geometry(const tsat_solver* s, int32_t N, int* kmax);
-static int32_t multi_units(tsat_solver* s, const FwdGeom& g, const FwdUnit** out, int* count);
+static int32_t multi_units(tsat_solver* s, const FwdGeom& g, int32_t kmax, const FwdUnit** out, int* count);
+static bool narrow_multi(const tsat_solver* s);
+static FwdGeom narrow_geometry(const tsat_solver* s, int32_t N);
 
 static int32_t prepare_units(tsat_solver* s, int32_t N)
 {
@@ -240,10 +245,15 @@ static int32_t prepare_units(tsat_solver* s, int32_t N)
         const FwdGeom g = multi_geometry(s, N, &kmax);
         const FwdUnit* u;
         int n;
-        RET(multi_units(s, g, &u, &n));
+        RET(multi_units(s, g, TSAT_MAX_WIDTH, &u, &n));
+    }
+    if (narrow_multi(s)) {
+        const FwdUnit* u;
+        int n;
+        RET(multi_units(s, narrow_geometry(s, N), 4, &u, &n));
     }
     for (auto* b : s->buckets) {
-        if (b->count == 0 || b->k == 0 || b->k > 4) continue;
+        if (b->count == 0 || b->k == 0 || b->k > 4 || narrow_multi(s)) continue;
         const FwdGeom g = fwd_geometry(N, K1_of(s), b->count, b->k, s->fwd_target_blocks);
         const FwdUnit* u;
         int n;
@@ -254,7 +264,7 @@ static int32_t prepare_units(tsat_solver* s, int32_t N)
     if (wide_geometry(s, N, &g, &kmax)) {
         const FwdUnit* u;
         int n;
-        RET(wide_units(s, g, &u, &n));
+        RET(wide_units(s, g, !plane_path(s, N), &u, &n));
     }
     return TSAT_OK;
 }
@@ -313,6 +323,23 @@ static bool plane_path(const tsat_solver* s, int32_t N)
     return W <= 4 && levels_lds_bytes(s, row_words(W)) <= 65536;
 }
 
+// R of every clause and candidate in bytes, for the stores and candidate
+// counts past the planes (clauses wider than kMaxPlaneWidth; mixed widths at
+// N > 256) with generic records: an update then loads one byte per record
+// and candidate where the row gather loads k - 1 literal rows and counts.
+// Held to 8 GiB, and to the clause planes' switch.
+static size_t rbytes_bytes(const tsat_solver* s, int32_t N)
+{
+    return std::max<size_t>(16, (size_t)s->st.plane_clauses * 64 * (size_t)((N + 63) / 64));
+}
+
+static bool bytes_path(const tsat_solver* s, int32_t N)
+{
+    return s->clause_planes && !s->bytes_off && s->st.pure_k == 0 && (s->wide_cid.p || s->occ_cid.p) &&
+           s->rows_per_var == 1 && N <= TSAT_MAX_STEP_N && !plane_path(s, N) &&
+           rbytes_bytes(s, N) <= ((size_t)8 << 30);
+}
+
 // Uniform widths 2 and 3 with the window gather at N <= 32: the update takes
 // two variables per wave and reads a clause's two planes as one 8-byte word,
 // so the forward writes them packed (plane stride of one dword).  The one
@@ -333,6 +360,7 @@ static int64_t narrow_end(const tsat_solver* s)
 
 static size_t planes_bytes(const tsat_solver* s, int32_t N)
 {
+    if (bytes_path(s, N)) return rbytes_bytes(s, N);
     const size_t G3 = (size_t)narrow_end(s);
     const size_t words = G3 * 2 + ((size_t)s->st.plane_clauses - G3) * 4; // plane rows
     return std::max<size_t>(16, words * 8 * (size_t)row_words((N + 63) / 64));
@@ -342,6 +370,12 @@ static int32_t ensure_planes(tsat_solver* s, DBuf& buf, int32_t N, hipStream_t s
 {
     const size_t bytes = planes_bytes(s, N);
     if (buf.p && buf.bytes >= bytes) return TSAT_OK;
+    if (bytes_path(s, N)) {
+        // a convenience: without the memory the row gather stays
+        s->bytes_off = buf.alloc(bytes, "bytes of R") != TSAT_OK;
+        if (s->bytes_off) g_err.clear();
+        return TSAT_OK;
+    }
     RET(buf.alloc(bytes, "clause planes"));
     HIPCHK(launch_fill_u32(buf.as<uint32_t>(), (int64_t)(bytes / 4), 0u, st));
     return TSAT_OK;
@@ -363,18 +397,23 @@ static int32_t wide_geometry(const tsat_solver* s, int32_t N, FwdGeom* g, int* k
     return Cw > 0;
 }
 
-static int32_t wide_units(tsat_solver* s, const FwdGeom& g, const FwdUnit** out, int* count)
+// `lanes`: for the lane-per-candidate kernel, which takes fewer clauses at a
+// time the wider they are; its units shrink with the clauses in flight, so
+// that those of one launch (and the XCDs' shares of them) cost alike.
+static int32_t wide_units(tsat_solver* s, const FwdGeom& g, bool lanes, const FwdUnit** out, int* count)
 {
-    auto it = s->wide_units.find(g.CPT);
+    const int key = g.CPT * 2 + (lanes ? 1 : 0);
+    auto it = s->wide_units.find(key);
     if (it == s->wide_units.end()) {
         std::vector<FwdUnit> u;
         const int64_t per = (int64_t)g.S * g.CPT;
         for (auto* b : s->buckets) {
             if (b->k <= 4 || b->count == 0) continue;
             const auto& off = s->st.inst_off[b->k];
+            const int64_t step = lanes ? std::max<int64_t>(16, per / (b->k > 16 ? 4 : (b->k > 8 ? 2 : 1))) : per;
             for (int32_t j = 0; j < s->st.n_inst; ++j)
-                for (int64_t c = off[j]; c < off[j + 1]; c += per)
-                    u.push_back(FwdUnit{j, b->k, c, std::min(c + per, off[j + 1])});
+                for (int64_t c = off[j]; c < off[j + 1]; c += step)
+                    u.push_back(FwdUnit{j, b->k, c, std::min(c + step, off[j + 1])});
         }
         DBuf* d = new (std::nothrow) DBuf();
         if (!d) return fail(TSAT_E_OOM, "host allocation failed");
@@ -384,7 +423,7 @@ static int32_t wide_units(tsat_solver* s, const FwdGeom& g, const FwdUnit** out,
             hipError_t e = hipMemcpy(d->p, u.data(), u.size() * sizeof(FwdUnit), hipMemcpyHostToDevice);
             if (e != hipSuccess) { delete d; return fail(TSAT_E_HIP, "unit upload: %s", hipGetErrorString(e)); }
         }
-        it = s->wide_units.emplace(g.CPT, std::make_pair(d, (int)u.size())).first;
+        it = s->wide_units.emplace(key, std::make_pair(d, (int)u.size())).first;
     }
     *out = it->second.first->as<FwdUnit>();
     *count = it->second.second;
@@ -414,15 +453,35 @@ static FwdGeom multi_geometry(const tsat_solver* s, int32_t N, int* kmax)
     return fwd_geometry(N, K1_of(s), C, 4, s->fwd_target_blocks);
 }
 
-// per bucket (width in pad) and instance, ranges of S CPT clauses
-static int32_t multi_units(tsat_solver* s, const FwdGeom& g, const FwdUnit** out, int* count)
+// Two or more non-empty widths up to 4: without planes these share a launch
+// (the wider clauses take the lane-per-candidate kernel)
+static bool narrow_multi(const tsat_solver* s)
 {
-    auto it = s->multi_units.find(g.CPT);
+    int nb = 0;
+    for (auto* b : s->buckets)
+        if (b->k > 0 && b->k <= 4 && b->count > 0) ++nb;
+    return nb >= 2;
+}
+
+static FwdGeom narrow_geometry(const tsat_solver* s, int32_t N)
+{
+    int64_t C = 0;
+    for (auto* b : s->buckets)
+        if (b->k > 0 && b->k <= 4) C += b->count;
+    return fwd_geometry(N, K1_of(s), C, 4, s->fwd_target_blocks);
+}
+
+// per bucket up to kmax (width in pad) and instance, ranges of S CPT clauses
+static int32_t multi_units(tsat_solver* s, const FwdGeom& g, int32_t kmax, const FwdUnit** out, int* count)
+{
+    // what the ranges follow from, and which buckets
+    const int key = (g.S * 256 + g.CPT) * 2 + (kmax <= 4 ? 1 : 0);
+    auto it = s->multi_units.find(key);
     if (it == s->multi_units.end()) {
         std::vector<FwdUnit> u;
         const int64_t per = (int64_t)g.S * g.CPT;
         for (auto* b : s->buckets) {
-            if (b->k == 0 || b->count == 0) continue;
+            if (b->k == 0 || b->k > kmax || b->count == 0) continue;
             const auto& off = s->st.inst_off[b->k];
             for (int32_t j = 0; j < s->st.n_inst; ++j)
                 for (int64_t c = off[j]; c < off[j + 1]; c += per)
@@ -436,7 +495,7 @@ static int32_t multi_units(tsat_solver* s, const FwdGeom& g, const FwdUnit** out
             hipError_t e = hipMemcpy(d->p, u.data(), u.size() * sizeof(FwdUnit), hipMemcpyHostToDevice);
             if (e != hipSuccess) { delete d; return fail(TSAT_E_HIP, "unit upload: %s", hipGetErrorString(e)); }
         }
-        it = s->multi_units.emplace(g.CPT, std::make_pair(d, (int)u.size())).first;
+        it = s->multi_units.emplace(key, std::make_pair(d, (int)u.size())).first;
     }
     *out = it->second.first->as<FwdUnit>();
     *count = it->second.second;
@@ -472,7 +531,7 @@ static int32_t enqueue_fwd(tsat_solver* s, const uint64_t* lits, int32_t N, uint
         const FwdGeom g = multi_geometry(s, N, &kmax);
         FwdArgs a = base;
         int nunits = 0;
-        RET(multi_units(s, g, &a.units, &nunits));
+        RET(multi_units(s, g, TSAT_MAX_WIDTH, &a.units, &nunits));
         a.KW = 0;
         a.Dn = g.Dn;
         a.DT = g.DT;
@@ -486,13 +545,13 @@ static int32_t enqueue_fwd(tsat_solver* s, const uint64_t* lits, int32_t N, uint
         }
         a.nunits = nunits;
         a.xcd = s->xcd_order;
-        if (nunits > 0) HIPCHK(launch_fwd_multi(a, kmax, nunits, st));
+        if (nunits > 0) HIPCHK(launch_fwd_multi(a, kmax, nunits, g.tiles, st));
         FwdGeom gw;
         int kw = 0;
         if (wide_geometry(s, N, &gw, &kw)) {
             FwdArgs w = a;
             int nw = 0;
-            RET(wide_units(s, gw, &w.units, &nw));
+            RET(wide_units(s, gw, false, &w.units, &nw));
             w.CPT = gw.CPT;
             w.planes = wide_planes;
             w.plane_P = 4;
@@ -501,9 +560,35 @@ static int32_t enqueue_fwd(tsat_solver* s, const uint64_t* lits, int32_t N, uint
         }
         return TSAT_OK;
     }
-    // widths 1 .. 4: one launch per bucket
+    if (planes && !with_planes && bytes_path(s, N)) {
+        base.rbytes = reinterpret_cast<uint8_t*>(planes);
+        base.rb_stride = 64 * W;
+    }
+    // global index of a bucket's first clause
+    int64_t base_of[TSAT_MAX_WIDTH + 2] = {0};
+    for (int k = 1; k <= TSAT_MAX_WIDTH; ++k) base_of[k + 1] = base_of[k] + s->st.width_count[k];
+    // widths 1 .. 4: several buckets in one launch, or one bucket
+    const bool together = narrow_multi(s);
+    if (together) {
+        const FwdGeom g = narrow_geometry(s, N);
+        FwdArgs a = base;
+        int nunits = 0;
+        RET(multi_units(s, g, 4, &a.units, &nunits));
+        a.Dn = g.Dn;
+        a.DT = g.DT;
+        a.CPT = g.CPT;
+        a.plane_P = 2;
+        a.nunits = nunits;
+        a.xcd = s->xcd_order;
+        for (auto* b : s->buckets) {
+            if (b->k == 0 || b->k > 4 || b->count == 0) continue;
+            a.wide_codes[b->k] = b->codes.as<uint32_t>();
+            a.wide_base[b->k] = base_of[b->k];
+        }
+        if (nunits > 0) HIPCHK(launch_fwd_multi(a, 4, nunits, g.tiles, st));
+    }
     for (auto* b : s->buckets) {
-        if (b->count == 0 || b->k == 0 || b->k > 4) continue;
+        if (b->count == 0 || b->k == 0 || b->k > 4 || together) continue;
         const FwdGeom g = fwd_geometry(N, K1_of(s), b->count, b->k, s->fwd_target_blocks);
         FwdArgs a = base;
         int nunits = 0;
@@ -519,6 +604,8 @@ static int32_t enqueue_fwd(tsat_solver* s, const uint64_t* lits, int32_t N, uint
             a.planes = narrow ? planes : wide_planes;
             a.plane_P = narrow ? 2 : 4;
             a.plane_base = s->st.plane_base[b->k] - (narrow ? 0 : G3);
+        } else {
+            a.plane_base = base_of[b->k];
         }
         a.nunits = nunits;
         a.xcd = s->xcd_order;
@@ -530,7 +617,7 @@ static int32_t enqueue_fwd(tsat_solver* s, const uint64_t* lits, int32_t N, uint
     if (wide_geometry(s, N, &g, &kmax)) {
         FwdArgs a = base;
         int nunits = 0;
-        RET(wide_units(s, g, &a.units, &nunits));
+        RET(wide_units(s, g, !with_planes, &a.units, &nunits));
         a.KW = 0;
         a.Dn = g.Dn;
         a.DT = g.DT;
@@ -542,7 +629,7 @@ static int32_t enqueue_fwd(tsat_solver* s, const uint64_t* lits, int32_t N, uint
         for (auto* b : s->buckets) {
             if (b->k <= 4 || b->count == 0) continue;
             a.wide_codes[b->k] = b->codes.as<uint32_t>();
-            if (with_planes) a.wide_base[b->k] = s->st.plane_base[b->k] - G3;
+            a.wide_base[b->k] = base_of[b->k] - G3;
         }
         a.nunits = nunits;
         a.xcd = s->xcd_order;
@@ -622,6 +709,14 @@ static VarArgs var_args(tsat_solver* s, const tsat_params& p, int32_t N, int32_t
     a.vchunk = s->vchunk.p ? s->vchunk.as<uint32_t>() : nullptr;
     a.n_vchunk = s->n_vchunk;
     a.planes = s->planes_scr.as<uint32_t>();
+    if (bytes_path(s, N)) { // likewise
+        a.rb = s->planes_scr.as<uint8_t>();
+        a.occ_cid = s->wide_cid.p ? s->wide_cid.as<uint32_t>() : s->occ_cid.as<uint32_t>();
+        if (s->wide_cid.p) {
+            a.cid_off = s->wide_off.as<uint32_t>();
+            a.cid_mid = s->wide_mid.as<uint32_t>();
+        }
+    }
     if (s->heavy.p) {
         a.heavy = s->heavy.as<uint32_t>();
         a.n_heavy = (int32_t)s->st.hv_var.size();
@@ -631,6 +726,8 @@ static VarArgs var_args(tsat_solver* s, const tsat_params& p, int32_t N, int32_t
         a.ch_var = s->ch_var.as<uint32_t>();
         a.ch_beg = s->ch_beg.as<uint32_t>();
         a.ch_end = s->ch_end.as<uint32_t>();
+        a.ch_rbeg = s->ch_rbeg.as<uint32_t>();
+        a.ch_rend = s->ch_rend.as<uint32_t>();
         a.partial = s->partial_scr.as<double>(); // evaluations; the step uses its own buffer
     }
     return a;
@@ -869,7 +966,9 @@ static int32_t load_store(tsat_solver* s, Store&& st)
         b->count = cnt;
         s->buckets.push_back(b);
         if (k == 0) continue;
-        RET(b->codes.alloc(codes.size() * 4, "clause store"));
+        // padded by a clause's width: the wide forward reads codes in fixed runs
+        RET(b->codes.alloc((codes.size() + TSAT_MAX_WIDTH) * 4, "clause store"));
+        HIPCHK(launch_fill_u32(b->codes.as<uint32_t>() + codes.size(), TSAT_MAX_WIDTH, 0u, s->stream));
         HIPCHK(hipMemcpy(b->codes.p, codes.data(), codes.size() * 4, hipMemcpyHostToDevice));
     }
     const size_t V = (size_t)s->st.V;
@@ -888,6 +987,21 @@ static int32_t load_store(tsat_solver* s, Store&& st)
         RET(s->occ_cid.alloc((nr + 64) * 4, "clause-index records"));
         HIPCHK(launch_fill_u32(s->occ_cid.as<uint32_t>() + nr, 64, 0u, s->stream));
         HIPCHK(hipMemcpy(s->occ_cid.p, s->st.occ_cid.data(), nr * 4, hipMemcpyHostToDevice));
+    }
+    s->wide_cid.release();
+    s->wide_off.release();
+    s->wide_mid.release();
+    s->bytes_off = false;
+    if (!s->st.wide_cid.empty()) {
+        // 64 words of padding, as above
+        const size_t nr = s->st.wide_cid.size();
+        RET(s->wide_cid.alloc((nr + 64) * 4, "clause-index records"));
+        RET(s->wide_off.alloc((V + 1) * 4, "clause-index record offsets"));
+        RET(s->wide_mid.alloc(V * 4, "clause-index record offsets"));
+        HIPCHK(launch_fill_u32(s->wide_cid.as<uint32_t>() + nr, 64, 0u, s->stream));
+        HIPCHK(hipMemcpy(s->wide_cid.p, s->st.wide_cid.data(), nr * 4, hipMemcpyHostToDevice));
+        HIPCHK(hipMemcpy(s->wide_off.p, s->st.wide_off.data(), (V + 1) * 4, hipMemcpyHostToDevice));
+        HIPCHK(hipMemcpy(s->wide_mid.p, s->st.wide_mid.data(), V * 4, hipMemcpyHostToDevice));
     }
     s->cid_off.release();
     s->cid_mid.release();
@@ -914,9 +1028,11 @@ static int32_t load_store(tsat_solver* s, Store&& st)
     s->partial_scr.release();
     {
         const Store& t = s->st;
-        DBuf* bufs[] = {&s->heavy, &s->hv_var, &s->hv_chunk, &s->ch_var, &s->ch_beg, &s->ch_end};
-        const std::vector<uint32_t>* src[] = {&t.heavy, &t.hv_var, &t.hv_chunk, &t.ch_var, &t.ch_beg, &t.ch_end};
-        for (int i = 0; i < 6; ++i) {
+        DBuf* bufs[] = {&s->heavy,  &s->hv_var, &s->hv_chunk, &s->ch_var,
+                        &s->ch_beg, &s->ch_end, &s->ch_rbeg,  &s->ch_rend};
+        const std::vector<uint32_t>* src[] = {&t.heavy,  &t.hv_var, &t.hv_chunk, &t.ch_var,
+                                              &t.ch_beg, &t.ch_end, &t.ch_rbeg,  &t.ch_rend};
+        for (int i = 0; i < 8; ++i) {
             bufs[i]->release();
             if (src[i]->empty()) continue;
             RET(bufs[i]->alloc(src[i]->size() * 4, "heavy-variable chunks"));
@@ -1019,7 +1135,8 @@ static int32_t alloc_batch(tsat_solver* s, int32_t N)
     HIPCHK(launch_fill_u32(s->H.as<uint32_t>(), (int64_t)hw, 0u, s->stream));
     HIPCHK(launch_fill_u32(s->m.as<uint32_t>(), (int64_t)VN, 0u, s->stream));
     HIPCHK(launch_fill_u32(s->v.as<uint32_t>(), (int64_t)VN, 0u, s->stream));
-    if (plane_path(s, N)) RET(ensure_planes(s, s->planes, N, s->stream));
+    s->bytes_off = false;
+    if (plane_path(s, N) || bytes_path(s, N)) RET(ensure_planes(s, s->planes, N, s->stream));
     RET(ensure_partial(s, s->partial, N));
     s->N = N;
     s->W = W;
@@ -1174,7 +1291,7 @@ static int32_t enqueue_iteration(tsat_solver* s, const SminArgs& sa, VarArgs va,
     Ctrl* ctrl = s->ctrl.as<Ctrl>();
     InstCtrl* ictrl = s->ictrl.as<InstCtrl>();
     RET(enqueue_fwd(s, s->lits[cur].as<uint64_t>(), s->N, s->H.as<uint32_t>(), ctrl, ictrl, s->stream,
-                    plane_path(s, s->N) ? s->planes.as<uint32_t>() : nullptr));
+                    plane_path(s, s->N) || bytes_path(s, s->N) ? s->planes.as<uint32_t>() : nullptr));
     if (timing) HIPCHK(hipEventRecord(s->events[3 * it + 1], s->stream));
     HIPCHK(launch_smin(sa, s->stream));
     if (timing) HIPCHK(hipEventRecord(s->events[3 * it + 2], s->stream));
@@ -1251,6 +1368,7 @@ int32_t tsat_step(tsat_solver* s, int32_t max_steps, const tsat_params* params, 
     sa.update = 1;
     VarArgs va = var_args(s, p, s->N, s->W, s->Np);
     va.planes = s->planes.as<uint32_t>();
+    if (bytes_path(s, s->N)) va.rb = s->planes.as<uint8_t>();
     if (va.heavy) va.partial = s->partial.as<double>();
     va.tbl = s->table.as<float>();
     va.theta = s->theta.as<float>();
@@ -1441,7 +1559,7 @@ static int32_t eval_rows(tsat_solver* s, const tsat_params& p, const uint64_t* l
     uint32_t* planes = nullptr;
     if (saved) {
         planes = saved->planes;
-    } else if (plane_path(s, N) && (table || s->st.K > 4 || multi_path(s, N))) {
+    } else if ((plane_path(s, N) && (table || s->st.K > 4 || multi_path(s, N))) || (table && bytes_path(s, N))) {
         RET(ensure_planes(s, s->planes_scr, N, st));
         planes = s->planes_scr.as<uint32_t>();
     }
@@ -2065,7 +2183,7 @@ static size_t saved_layout(const tsat_solver* s, int32_t N, uint8_t* base, Saved
     };
     v->H = reinterpret_cast<uint32_t*>(part(64 * W * K1_of(s) * 4));
     v->mu = reinterpret_cast<double*>(part(V * 8));
-    if (plane_path(s, N)) v->planes = reinterpret_cast<uint32_t*>(part(planes_bytes(s, N)));
+    if (plane_path(s, N) || bytes_path(s, N)) v->planes = reinterpret_cast<uint32_t*>(part(planes_bytes(s, N)));
     else v->lits = reinterpret_cast<uint64_t*>(part((2 * V * W + 16) * 8));
     return need;
 }
@@ -2074,7 +2192,8 @@ static size_t saved_layout(const tsat_solver* s, int32_t N, uint8_t* base, Saved
 // its own number, over all solvers), and which planes the forward writes.
 static uint64_t saved_key(const tsat_solver* s, int32_t N)
 {
-    return (s->load_id << 2) | (plane_path(s, N) ? 1u : 0u) | (packed_planes(s, N) ? 2u : 0u);
+    const unsigned form = bytes_path(s, N) ? 3u : (packed_planes(s, N) ? 2u : (plane_path(s, N) ? 1u : 0u));
+    return (s->load_id << 2) | form;
 }
 
 static int32_t check_saved(tsat_solver* s, int32_t N, void* saved, int64_t bytes, SavedView* v)
@@ -2106,6 +2225,7 @@ static int32_t saved_backward(tsat_solver* s, const tsat_params& p, int32_t N, c
     va.tbl = s->table_scr.as<float>();
     va.theta = const_cast<float*>(theta); // read only by the gradient op
     va.planes = v.planes;
+    if (bytes_path(s, N)) va.rb = reinterpret_cast<const uint8_t*>(v.planes);
     va.lits_cur = v.lits ? v.lits : s->lits_scr.as<uint64_t>(); // the plane gathers of these ops use no rows
     va.mu_cur = v.mu;
     va.U_out = U;
@@ -2249,7 +2369,7 @@ int32_t tsat_set_launch_config(tsat_solver* s, const tsat_launch_config* cfg)
     s->pure_group = cfg->pure_group;
     s->clause_planes = cfg->clause_planes;
     s->window_gather = cfg->window_gather;
-    if (s->N > 0 && plane_path(s, s->N)) RET(ensure_planes(s, s->planes, s->N, s->stream));
+    if (s->N > 0 && (plane_path(s, s->N) || bytes_path(s, s->N))) RET(ensure_planes(s, s->planes, s->N, s->stream));
     return TSAT_OK;
 }
 

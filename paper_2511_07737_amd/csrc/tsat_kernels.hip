@@ -265,7 +265,28 @@ __device__ __forceinline__ void fwd_hist_unit(const FwdArgs& a, const FwdUnit& u
                 for (int r = KW - 1; r >= 1; --r) ge[r] |= ge[r - 1] & x[q];
                 ge[0] |= x[q];
             }
-            if (planes) {
+            if (a.rbytes) {
+                // R of the 32 candidates in bytes, four at a time: the four
+                // bits of a plane spread to four bytes by a multiplication
+                uint32_t bp[3];
+#pragma unroll
+                for (int p = 0; p < 3; ++p) {
+                    bp[p] = 0;
+#pragma unroll
+                    for (int r = 1 << p; r <= KW; r += 1 << p) bp[p] ^= ge[r - 1];
+                }
+                uint32_t w[8];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    w[q] = 0;
+#pragma unroll
+                    for (int p = 0; p < 3; ++p)
+                        if ((1 << p) <= KW) w[q] |= (__umul24((bp[p] >> (4 * q)) & 15u, 0x204081u) & 0x01010101u) << p;
+                }
+                uint4* out = (uint4*)(a.rbytes + (size_t)(plane_base + c) * a.rb_stride + 32u * (uint32_t)d);
+                out[0] = make_uint4(w[0], w[1], w[2], w[3]);
+                out[1] = make_uint4(w[4], w[5], w[6], w[7]);
+            } else if (planes) {
                 // R in binary for the backward, plane_P planes: bit p of R is
                 // the parity of the masks [R >= m 2^p], m >= 1
                 uint32_t* P = planes + (size_t)(plane_base + c) * (size_t)(plane_P * a.plane_stride) + d;
@@ -368,6 +389,43 @@ __global__ __launch_bounds__(256) void fwd_hist_kernel(FwdArgs a)
 // block then adds its four waves' bins into the global histogram.  Clauses
 // are taken G at a time, all their row loads issued before the first wait.
 template <int KMAX, int G, bool VR>
+__device__ __forceinline__ void fwd_lanes_run(const FwdArgs& a, int k, const uint32_t* codes, int64_t cb, int64_t ce,
+                                              int64_t pbase, uint32_t cand, bool live, uint32_t* my)
+{
+    const uint32_t d = live ? cand >> 5 : 0u, bit = cand & 31u;
+    for (int64_t c = cb; c < ce; c += G) { // wave-uniform
+        // the codes past a clause's width belong to the next one (the bucket
+        // is padded): all loads without a condition between them, the rows
+        // past the width replaced by the clause's first
+        uint32_t code[G][KMAX], x[G][KMAX];
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const uint32_t* cl = (const uint32_t*)uniform64((uint64_t)(codes + (c + g < ce ? c + g : c) * k));
+#pragma unroll
+            for (int q = 0; q < KMAX; ++q) code[g][q] = sload(cl + q);
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int q = 0; q < KMAX; ++q) x[g][q] = lit_dword<VR>(a.bits32, q < k ? code[g][q] : code[g][0], a.W2, d);
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            if (c + g >= ce) break;
+            uint32_t R = 0;
+#pragma unroll
+            for (int q = 0; q < KMAX; ++q) R += q < k ? (x[g][q] >> bit) & 1u : 0u;
+            if (live) atomicAdd(&my[R], 1u);
+            if (a.rbytes) a.rbytes[(size_t)(pbase + c + g) * a.rb_stride + cand] = (uint8_t)R;
+        }
+    }
+}
+
+// A block's clauses share a width; the run is compiled for widths up to 8,
+// 16 and 32, so that narrow units keep several clauses in flight next to a
+// bucket of wide ones (2e5 mixed clauses up to 24 wide, N = 100: 87 us
+// with every unit one clause at a time and codes in vector registers, 60 us
+// with the bytes of R written as well).
+template <int KMAX, bool VR>
 __global__ __launch_bounds__(256) void fwd_hist_lanes_kernel(FwdArgs a)
 {
     extern __shared__ uint32_t lh[]; // [4 waves][64 lanes][K1]
@@ -377,53 +435,23 @@ __global__ __launch_bounds__(256) void fwd_hist_lanes_kernel(FwdArgs a)
     const FwdUnit u = a.units[un];
     if (a.ictrl && a.ictrl[u.inst].frozen) return;
     uint32_t* H = a.H + ((size_t)u.inst * a.H_reps + blockIdx.x % (uint32_t)a.H_reps) * a.H_stride;
-    const uint32_t lane = __lane_id(), wave = threadIdx.x / 64u;
+    const uint32_t lane = __lane_id(), wave = uniform(threadIdx.x / 64u);
     // KW = 0: the units of every wide bucket in one launch, unit width in pad
-    const int K1 = a.K1, k = a.KW > 0 ? a.KW : u.pad;
+    const int K1 = a.K1, k = (int)uniform((uint32_t)(a.KW > 0 ? a.KW : u.pad));
     const uint32_t* codes = a.KW > 0 ? a.codes : a.wide_codes[k];
     const int64_t pbase = a.KW > 0 ? a.plane_base : a.wide_base[k];
     const uint32_t cand = blockIdx.y * 64u + lane;
-    const uint32_t d = cand >> 5, bit = cand & 31u;
-    const bool live = (int)d < a.Dn;
+    const bool live = (int)(cand >> 5) < a.Dn;
     uint32_t* my = lh + (wave * 64u + lane) * (uint32_t)K1;
     for (int r = 0; r < K1; ++r) my[r] = 0;
-    // this wave's clauses: CPT consecutive ones of the unit
-    const int64_t cb = u.c0 + (int64_t)wave * a.CPT;
-    const int64_t ce = cb + a.CPT < u.c1 ? cb + a.CPT : u.c1;
-    for (int64_t c = cb; c < ce; c += G) { // wave-uniform
-        uint32_t x[G][KMAX];
-#pragma unroll
-        for (int g = 0; g < G; ++g)
-#pragma unroll
-            for (int q = 0; q < KMAX; ++q) {
-                x[g][q] = 0u;
-                if (q < k && c + g < ce) {
-                    const uint32_t code = sload(codes + (c + g) * k + q);
-                    if (live) x[g][q] = lit_dword<VR>(a.bits32, code, a.W2, d);
-                }
-            }
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            if (c + g >= ce) break;
-            uint32_t R = 0;
-#pragma unroll
-            for (int q = 0; q < KMAX; ++q) R += (x[g][q] >> bit) & 1u;
-            if (live) atomicAdd(&my[R], 1u);
-            if (a.planes) {
-                // R in binary for the backward: plane p of this clause, word
-                // blockIdx.y (the wave's 64 candidates), one bit per lane
-                uint64_t bal[4];
-#pragma unroll
-                for (int p = 0; p < 4; ++p) bal[p] = ballot64((R >> p) & 1u);
-                if (lane == 0) {
-                    uint64_t* P = (uint64_t*)a.planes + (size_t)(pbase + c + g) * (size_t)(a.plane_P * a.plane_stride / 2) + blockIdx.y;
-#pragma unroll
-                    for (int p = 0; p < 4; ++p)
-                        if (p < a.plane_P) P[(size_t)p * (a.plane_stride / 2)] = bal[p];
-                }
-            }
-        }
-    }
+    // this wave's clauses: a quarter of the unit
+    const int64_t u0 = (int64_t)uniform64((uint64_t)u.c0), u1 = (int64_t)uniform64((uint64_t)u.c1);
+    const int64_t share = (u1 - u0 + 3) / 4;
+    const int64_t cb = u0 + (int64_t)wave * share;
+    const int64_t ce = cb + share < u1 ? cb + share : u1;
+    if (KMAX > 16 && k > 16) fwd_lanes_run<KMAX, 1, VR>(a, k, codes, cb, ce, pbase, cand, live, my);
+    else if (KMAX > 8 && k > 8) fwd_lanes_run<(KMAX < 16 ? KMAX : 16), 2, VR>(a, k, codes, cb, ce, pbase, cand, live, my);
+    else fwd_lanes_run<8, 4, VR>(a, k, codes, cb, ce, pbase, cand, live, my);
     __syncthreads();
     for (int e = threadIdx.x; e < 64 * K1; e += 256) {
         const int l = e / K1, r = e % K1;
@@ -730,7 +758,10 @@ __device__ __forceinline__ void load_row(const VarArgs& a, uint32_t v, uint32_t 
 
 // Eq. 5 backward of one variable row: g = U / mu - (sum_i U_i theta_i) /
 // (N mu^2) in mean mode (inside the clamp the mean is a constant and the
-// second term is dropped), g = U without normalization.
+// second term is dropped), g = U without normalization.  The difference is
+// written as the fused operation: left to the compiler, which of the two
+// products it fuses depends on the code around, and where the terms cancel
+// (one candidate: g is their rounding alone) kernels would disagree.
 template <int J>
 __device__ __forceinline__ void norm_backward_row(const VarArgs& a, const float (&th)[J], const double (&U)[J],
                                                   double mu, bool clamped, float (&g)[J])
@@ -740,7 +771,7 @@ __device__ __forceinline__ void norm_backward_row(const VarArgs& a, const float 
         const double inv_mu = 1.0 / mu;
         const double corr = clamped ? 0.0 : ut * inv_mu * inv_mu * a.inv_n;
 #pragma unroll
-        for (int j = 0; j < J; ++j) g[j] = (float)(U[j] * inv_mu - corr);
+        for (int j = 0; j < J; ++j) g[j] = (float)__builtin_fma(U[j], inv_mu, -corr);
     } else {
 #pragma unroll
         for (int j = 0; j < J; ++j) g[j] = (float)U[j];
@@ -1113,6 +1144,148 @@ __global__ __launch_bounds__(256) void var_kernel(VarArgs a)
             }
             q += 1 + k1;
         }
+        var_tail<J, OP>(a, c, v, lane, th, mm, vv, valid, mu, clamped, U, oP, vi.witness, vi.wcand, bad);
+    }
+    if (OP == OP_STEP) {
+        if (ballot64(bad != 0) && lane == 0) atomicOr(&a.ctrl->nonfinite, 1);
+        advance_step(a);
+    }
+}
+
+// Generic records over the forward's bytes of R (the stores and candidate
+// counts without clause planes: clauses wider than 15, or mixed widths at
+// N > 256): a record is its clause's index, the wave loads R of its
+// candidates (64 bytes per word and record, B records in flight), looks up
+// dL/dR in the table and adds in FP64, record by record in var_kernel's order
+// and so with its results.  A record's sign multiplies its entry inside the
+// fused sum.  What bounds it is latency: a record's row is a random 64 W-byte
+// read, hubs are long chains of them (cut into the heavy variables' chunks,
+// which run first, beside the other variables).  V = 4e4, 2e5 clauses of
+// widths 2 .. 24, N = 100: adjoint 70 us; the row gather 211 + 100 for the
+// heavy chunks' launch before it.  16 records in flight and doubled 105 us,
+// 4 67.  var_kernel, which gathers the k - 1 other literal
+// rows of every record through the scalar cache and counts them, remains for
+// stores whose bytes would not fit and with the clause planes off.
+template <int J, int B, class T>
+__device__ __forceinline__ void bytes_records(const VarArgs& a, uint32_t q, uint32_t qm, uint32_t qe, uint32_t lane,
+                                              T table, double (&U)[J])
+{
+    const int W = a.W;
+    const uint32_t stride = 64u * (uint32_t)W;
+    // lanes past the candidates read the last one's byte: those beyond the
+    // forward's dwords hold nothing
+    uint32_t col[J];
+#pragma unroll
+    for (int j = 0; j < J; ++j) col[j] = min(64u * j + lane, (uint32_t)a.N - 1u);
+    for (uint32_t base = q; base < qe; base += 64) { // wave-uniform
+        // the next 64 records' clauses in one load, lane by lane
+        const uint32_t n = qe - base < 64u ? qe - base : 64u;
+        const uint64_t rows = (uint64_t)a.occ_cid[base + min(lane, n - 1u)] * stride;
+        const uint32_t rlo = (uint32_t)rows, rhi = (uint32_t)(rows >> 32);
+        uint32_t nx[B][J];
+        auto load = [&](uint32_t i0) {
+#pragma unroll
+            for (int i = 0; i < B; ++i) { // past the end: the last record's row again
+                const int at = (int)min(i0 + i, n - 1u);
+                const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)rlo, at);
+                const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)rhi, at);
+                const uint8_t* row = a.rb + (((uint64_t)hi << 32) | lo);
+#pragma unroll
+                for (int j = 0; j < J; ++j) nx[i][j] = j < W ? row[col[j]] : 0u;
+            }
+        };
+        load(0);
+        for (uint32_t i0 = 0; i0 < n; i0 += B) {
+            // the next batch is in flight while this one is added
+            uint32_t R[B][J];
+#pragma unroll
+            for (int i = 0; i < B; ++i)
+#pragma unroll
+                for (int j = 0; j < J; ++j) R[i][j] = nx[i][j];
+            if (i0 + B < n) load(i0 + B);
+#pragma unroll
+            for (int i = 0; i < B; ++i) {
+                if (i0 + i >= n) break;
+                // +-1 times the entry, fused: the sum itself
+                const double sg = base + i0 + i >= qm ? -1.0 : 1.0;
+#pragma unroll
+                for (int j = 0; j < J; ++j) {
+                    if (j >= W) break;
+                    const double val = (double)table[__umul24(R[i][j], (uint32_t)a.Np) + 64 * j + lane];
+                    U[j] = __builtin_fma(sg, val, U[j]);
+                }
+            }
+        }
+    }
+}
+
+// records in flight per wave
+template <int J> constexpr int bytes_batch() { return J <= 2 ? 8 : 16 / J; }
+
+template <int J, int OP, bool MULTI>
+__global__ __launch_bounds__(256) void var_bytes_kernel(VarArgs a)
+{
+    extern __shared__ float s_tbl[]; // [K1][Np] (one instance)
+    if (OP == OP_STEP && a.ctrl->stop) {
+        copy_bits_on_stop(a);
+        return;
+    }
+    if (OP == OP_STEP && a.ctrl->mixing) {
+        mix_rows<J>(a);
+        return;
+    }
+    if (!MULTI) {
+        const int nt = a.K1 * a.Np;
+        for (int q = threadIdx.x; q < nt; q += blockDim.x) s_tbl[q] = a.tbl[q];
+        __syncthreads();
+    }
+    const uint32_t lane = __lane_id();
+    const uint32_t wave0 = uniform(blockIdx.x * 4u + threadIdx.x / 64u);
+    const uint32_t nwaves = uniform(gridDim.x * 4u);
+    const StepScalars c = load_scalars(a, OP);
+    int bad = 0;
+    // the chunks of the heavy variables first (the longest items), then the
+    // variables
+    const uint32_t nch = a.heavy ? (uint32_t)a.n_chunks : 0u;
+    for (uint32_t it = wave0; it < nch + (uint32_t)a.V; it += nwaves) {
+        if (it < nch) {
+            const uint32_t v = sload(a.ch_var + it);
+            const VarInst vi = var_instance<OP>(a, v);
+            double U[J];
+#pragma unroll
+            for (int j = 0; j < J; ++j) U[j] = 0.0;
+            if (!vi.frozen) {
+                const uint32_t q = sload(a.ch_rbeg + it), qm = sload(a.cid_mid + v), qe = sload(a.ch_rend + it);
+                if constexpr (MULTI) bytes_records<J, bytes_batch<J>()>(a, q, qm, qe, lane, a.tbl + (size_t)vi.inst * a.K1 * a.Np, U);
+                else bytes_records<J, bytes_batch<J>()>(a, q, qm, qe, lane, (const float*)s_tbl, U);
+            }
+#pragma unroll
+            for (int j = 0; j < J; ++j)
+                if (j < a.W) a.partial[(size_t)it * a.Np + 64 * j + lane] = U[j];
+            continue;
+        }
+        const uint32_t v = it - nch;
+        if (a.heavy && sload(a.heavy + v)) continue; // its chunks' sums meet in the tail kernel
+        const VarInst vi = var_instance<OP>(a, v);
+        if (vi.frozen) {
+            keep_variable<J>(a, v, lane);
+            continue;
+        }
+        float th[J], mm[J], vv[J];
+        bool valid[J];
+        load_row<J, OP>(a, v, lane, th, mm, vv, valid);
+        double U[J];
+#pragma unroll
+        for (int j = 0; j < J; ++j) U[j] = 0.0;
+        const uint32_t q = sload(a.cid_off + v), qm = sload(a.cid_mid + v), qe = sload(a.cid_off + v + 1);
+        if constexpr (MULTI) bytes_records<J, bytes_batch<J>()>(a, q, qm, qe, lane, a.tbl + (size_t)vi.inst * a.K1 * a.Np, U);
+        else bytes_records<J, bytes_batch<J>()>(a, q, qm, qe, lane, (const float*)s_tbl, U);
+        bool clamped = false;
+        const double mu = (OP == OP_ADJ || a.mode != 1) ? 1.0 : clamp_mu(sload(a.mu_cur + v), clamped);
+        const uint64_t* ownp = a.lits_cur + (size_t)(2 * v) * a.W;
+        uint64_t oP[J];
+#pragma unroll
+        for (int j = 0; j < J; ++j) oP[j] = OP == OP_STEP ? sload(ownp + j) : 0ull;
         var_tail<J, OP>(a, c, v, lane, th, mm, vv, valid, mu, clamped, U, oP, vi.witness, vi.wcand, bad);
     }
     if (OP == OP_STEP) {
@@ -2221,7 +2394,7 @@ __global__ __launch_bounds__(256) void var_window_team_kernel(VarArgs a)
                 const double inv_mu = 1.0 / mu;
                 const double corr = clamped ? 0.0 : ut * inv_mu * inv_mu * a.inv_n;
 #pragma unroll
-                for (int j = 0; j < J; ++j) g[i][j] = (float)((double)g[i][j] * inv_mu - corr);
+                for (int j = 0; j < J; ++j) g[i][j] = (float)__builtin_fma((double)g[i][j], inv_mu, -corr);
             }
             if (OP == OP_GRAD) {
                 if (a.g_out) {
@@ -2327,7 +2500,7 @@ __device__ __forceinline__ void pair_tail(const VarArgs& a, const StepScalars& c
         ut = half_sum(ut);
         const double inv_mu = 1.0 / mu;
         const double corr = clamped ? 0.0 : ut * inv_mu * inv_mu * a.inv_n;
-        g = (float)(U * inv_mu - corr);
+        g = (float)__builtin_fma(U, inv_mu, -corr);
     } else {
         g = (float)U;
     }
@@ -2855,8 +3028,9 @@ __global__ __launch_bounds__(256) void fwd_planes_kernel(FwdArgs a)
     fwd_planes_unit<KMAX, VR>(a, u, k, a.wide_codes[k], a.planes, a.wide_base[k]);
 }
 
-// Every bucket of a mixed-width store in one launch (clause planes on, at
-// most 256 candidates, so a block's tile is all of them): a unit of width
+// Several buckets of a mixed-width store in one launch: with clause planes
+// every bucket (at most 256 candidates, so a block's tile is all of them),
+// without them those of widths up to 4.  A unit of width
 // k <= 4 is a histogram unit of fwd_hist_unit (widths up to 3 write two
 // planes from the start of the plane buffer, width 4 four planes in the
 // wide region), a wider one a planes unit of fwd_planes_unit; the histogram
@@ -2874,7 +3048,7 @@ __global__ __launch_bounds__(256) void fwd_multi_kernel(FwdArgs a)
     const int k = u.pad; // block-uniform
     const uint32_t* codes = a.wide_codes[k];
     const int64_t base = a.wide_base[k];
-    uint32_t* planes4 = a.planes + a.wide_off;
+    uint32_t* planes4 = a.planes ? a.planes + a.wide_off : nullptr;
     switch (k) {
     case 1: fwd_hist_unit<1, 8, VR>(a, u, codes, a.planes, 2, base, lh); break;
     case 2: fwd_hist_unit<2, 8, VR>(a, u, codes, a.planes, 2, base, lh); break;
@@ -3624,9 +3798,9 @@ static hipError_t launch_fwd_vr(const FwdArgs& a, dim3 grid, hipStream_t st)
     case 4: return launch_fwd_k<4, 8, VR>(a, grid, st);
     default: {
         const size_t lds = (size_t)4 * 64 * a.K1 * sizeof(uint32_t);
-        if (a.KW <= 8) hipLaunchKernelGGL((fwd_hist_lanes_kernel<8, 4, VR>), grid, dim3(256), lds, st, a);
-        else if (a.KW <= 16) hipLaunchKernelGGL((fwd_hist_lanes_kernel<16, 2, VR>), grid, dim3(256), lds, st, a);
-        else hipLaunchKernelGGL((fwd_hist_lanes_kernel<32, 1, VR>), grid, dim3(256), lds, st, a);
+        if (a.KW <= 8) hipLaunchKernelGGL((fwd_hist_lanes_kernel<8, VR>), grid, dim3(256), lds, st, a);
+        else if (a.KW <= 16) hipLaunchKernelGGL((fwd_hist_lanes_kernel<16, VR>), grid, dim3(256), lds, st, a);
+        else hipLaunchKernelGGL((fwd_hist_lanes_kernel<32, VR>), grid, dim3(256), lds, st, a);
         return hipGetLastError();
     }
     }
@@ -3668,9 +3842,9 @@ hipError_t launch_planes_hist(const FwdArgs& a, int kmax, int nunits, hipStream_
 
 // every bucket in one launch (fwd_multi_kernel): a.units hold the units of
 // all widths, the width in pad; LDS for the widest histogram unit (k = 4)
-hipError_t launch_fwd_multi(const FwdArgs& a, int kmax, int nunits, hipStream_t st)
+hipError_t launch_fwd_multi(const FwdArgs& a, int kmax, int nunits, int tiles, hipStream_t st)
 {
-    const dim3 g(fwd_grid_x(a, nunits));
+    const dim3 g(fwd_grid_x(a, nunits), (unsigned)tiles);
     const size_t lds = (size_t)a.DT * 32 * 4 * sizeof(uint32_t);
     if (a.vrows) {
         if (kmax <= 8) hipLaunchKernelGGL((fwd_multi_kernel<8, true>), g, dim3(256), lds, st, a);
@@ -3700,13 +3874,13 @@ hipError_t launch_fwd_wide(const FwdArgs& a, int kmax, int nunits, int tiles, hi
     const dim3 grid(fwd_grid_x(a, nunits), (unsigned)tiles, 1);
     const size_t lds = (size_t)4 * 64 * a.K1 * sizeof(uint32_t);
     if (a.vrows) {
-        if (kmax <= 8) hipLaunchKernelGGL((fwd_hist_lanes_kernel<8, 4, true>), grid, dim3(256), lds, st, a);
-        else if (kmax <= 16) hipLaunchKernelGGL((fwd_hist_lanes_kernel<16, 2, true>), grid, dim3(256), lds, st, a);
-        else hipLaunchKernelGGL((fwd_hist_lanes_kernel<32, 1, true>), grid, dim3(256), lds, st, a);
+        if (kmax <= 8) hipLaunchKernelGGL((fwd_hist_lanes_kernel<8, true>), grid, dim3(256), lds, st, a);
+        else if (kmax <= 16) hipLaunchKernelGGL((fwd_hist_lanes_kernel<16, true>), grid, dim3(256), lds, st, a);
+        else hipLaunchKernelGGL((fwd_hist_lanes_kernel<32, true>), grid, dim3(256), lds, st, a);
     } else {
-        if (kmax <= 8) hipLaunchKernelGGL((fwd_hist_lanes_kernel<8, 4, false>), grid, dim3(256), lds, st, a);
-        else if (kmax <= 16) hipLaunchKernelGGL((fwd_hist_lanes_kernel<16, 2, false>), grid, dim3(256), lds, st, a);
-        else hipLaunchKernelGGL((fwd_hist_lanes_kernel<32, 1, false>), grid, dim3(256), lds, st, a);
+        if (kmax <= 8) hipLaunchKernelGGL((fwd_hist_lanes_kernel<8, false>), grid, dim3(256), lds, st, a);
+        else if (kmax <= 16) hipLaunchKernelGGL((fwd_hist_lanes_kernel<16, false>), grid, dim3(256), lds, st, a);
+        else hipLaunchKernelGGL((fwd_hist_lanes_kernel<32, false>), grid, dim3(256), lds, st, a);
     }
     return hipGetLastError();
 }
@@ -3774,6 +3948,14 @@ template <int J, bool MULTI>
 static hipError_t launch_var_jm(const VarArgs& a, int op, int blocks, hipStream_t st)
 {
     const size_t lds = MULTI ? 0 : (size_t)a.K1 * a.Np * sizeof(float);
+    if (a.rb && op != OP_NORMBWD && op != OP_BINARIZE) {
+        switch (op) {
+        case OP_STEP: hipLaunchKernelGGL((var_bytes_kernel<J, OP_STEP, MULTI>), dim3(blocks), dim3(256), lds, st, a); break;
+        case OP_GRAD: hipLaunchKernelGGL((var_bytes_kernel<J, OP_GRAD, MULTI>), dim3(blocks), dim3(256), lds, st, a); break;
+        default: hipLaunchKernelGGL((var_bytes_kernel<J, OP_ADJ, MULTI>), dim3(blocks), dim3(256), lds, st, a); break;
+        }
+        return hipGetLastError();
+    }
     switch (op) {
     case OP_STEP: hipLaunchKernelGGL((var_kernel<J, OP_STEP, MULTI>), dim3(blocks), dim3(256), lds, st, a); break;
     case OP_GRAD: hipLaunchKernelGGL((var_kernel<J, OP_GRAD, MULTI>), dim3(blocks), dim3(256), lds, st, a); break;
@@ -3818,8 +4000,9 @@ template <int J>
 static hipError_t launch_var_j(const VarArgs& a, int op, int blocks, hipStream_t st)
 {
     const bool split = a.heavy && a.n_chunks > 0 && op != OP_BINARIZE && op != OP_NORMBWD;
-    if (split) {
-        // partial sums of the heavy variables, then the light variables, then the heavy tails
+    if (split && !a.rb) {
+        // partial sums of the heavy variables (the byte gather forms them with
+        // the light variables), then the light variables, then the heavy tails
         hipError_t e = launch_heavy<J>(a, op, false, std::max(1, std::min((a.n_chunks + 3) / 4, blocks)), st);
         if (e != hipSuccess) return e;
     }
@@ -4023,8 +4206,8 @@ hipError_t launch_var(const VarArgs& a, int op, int blocks, hipStream_t st)
     // theta to read
     if (op == OP_GRAD && a.mode != 1) op = OP_ADJ;
     const bool rowwise = op == OP_BINARIZE || op == OP_NORMBWD; // no gather
-    if (a.occ_cid && a.planes && !rowwise && a.W > 4) return launch_team(a, op, blocks, st);
-    if (a.occ_cid && a.planes && !rowwise) {
+    if (a.occ_cid && a.planes && !a.rb && !rowwise && a.W > 4) return launch_team(a, op, blocks, st);
+    if (a.occ_cid && a.planes && !a.rb && !rowwise) {
         if (a.pure_k == 2 || a.pure_k == 3) {
             switch (a.W) {
             case 1: return launch_plane_j<1>(a, op, blocks, st);
@@ -4062,6 +4245,8 @@ template <int J>
 static int occupancy_j(const VarArgs& a, bool pure)
 {
     if (!pure) {
+        if (a.rb && a.var_inst) return occupancy_of(var_bytes_kernel<J, OP_STEP, true>, 0);
+        if (a.rb) return occupancy_of(var_bytes_kernel<J, OP_STEP, false>, (size_t)a.K1 * a.Np * sizeof(float));
         if (a.var_inst) return occupancy_of(var_kernel<J, OP_STEP, true>, 0);
         return occupancy_of(var_kernel<J, OP_STEP, false>, (size_t)a.K1 * a.Np * sizeof(float));
     }
@@ -4075,16 +4260,16 @@ static int occupancy_j(const VarArgs& a, bool pure)
 int var_occupancy(const VarArgs& a, int op)
 {
     const bool rowwise = op == OP_BINARIZE || op == OP_NORMBWD; // no gather
-    if (a.occ_cid && a.planes && !rowwise && a.W > 4)
+    if (a.occ_cid && a.planes && !a.rb && !rowwise && a.W > 4)
         return occupancy_of(a.pure_k == 2 ? team_kernel_ptr<2>(OP_STEP) : team_kernel_ptr<3>(OP_STEP), 0, team_threads(a));
-    if (a.occ_cid && a.planes && !rowwise && a.pure_k != 2 && a.pure_k != 3) {
+    if (a.occ_cid && a.planes && !a.rb && !rowwise && a.pure_k != 2 && a.pure_k != 3) {
         switch (a.W) {
         case 1: return occupancy_levels_j<1>(a);
         case 2: return occupancy_levels_j<2>(a);
         default: return occupancy_levels_j<4>(a);
         }
     }
-    if (a.occ_cid && a.planes && !rowwise) {
+    if (a.occ_cid && a.planes && !a.rb && !rowwise) {
         const bool k2 = a.pure_k == 2, win = a.window != 0;
         if (pair_rows(a))
             return k2 ? occupancy_of(var_window_pair_kernel<2, OP_STEP>, 0) : occupancy_of(var_window_pair_kernel<3, OP_STEP>, 0);

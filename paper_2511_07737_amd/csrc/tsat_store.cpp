@@ -216,37 +216,43 @@ int32_t build_store(int32_t n_inst, const int32_t* num_vars, const int64_t* lit_
     } catch (const std::bad_alloc&) {
         return fail(TSAT_E_OOM, "host allocation failed while building the occurrence store");
     }
-    // clause-index records for the plane gathers
-    if (st.K >= 1 && st.K <= kMaxPlaneWidth && (uint64_t)st.L < 0xffffffffull && (uint64_t)st.C < 0xffffffffull) {
+    // clause-index records, for the plane gathers or (wider clauses) the byte
+    // gather
+    if (st.K >= 1 && (uint64_t)st.L < 0xffffffffull && (uint64_t)st.C < 0xffffffffull) {
+        const bool planes = st.K <= kMaxPlaneWidth;
+        std::vector<uint32_t>& cid = planes ? st.occ_cid : st.wide_cid;
+        std::vector<uint32_t>& off = planes ? st.cid_off : st.wide_off;
+        std::vector<uint32_t>& mid = planes ? st.cid_mid : st.wide_mid;
         try {
-            st.plane_base.assign(TSAT_MAX_WIDTH + 1, 0);
+            std::vector<int64_t> base_of(TSAT_MAX_WIDTH + 1, 0);
             int64_t base = 0;
             for (int k = 1; k <= TSAT_MAX_WIDTH; ++k) {
-                st.plane_base[k] = base;
+                base_of[k] = base;
                 base += st.width_count[k];
             }
+            if (planes) st.plane_base = base_of;
             st.plane_clauses = base;
             std::vector<uint32_t> npos(V, 0), nneg(V, 0);
             for (int k = 1; k <= st.K; ++k)
                 for (const uint32_t c : st.buckets[k]) ++((c & 1u) ? nneg : npos)[c >> 1];
             std::vector<uint32_t> curp(V), curn(V);
             if (!pure) {
-                st.cid_off.assign((size_t)V + 1, 0);
-                st.cid_mid.assign((size_t)V, 0);
+                off.assign((size_t)V + 1, 0);
+                mid.assign((size_t)V, 0);
             }
             uint64_t total = 0;
             for (int32_t v = 0; v < V; ++v) {
                 curp[v] = (uint32_t)total;
                 curn[v] = (uint32_t)(total + npos[v]);
                 if (!pure) {
-                    st.cid_off[v] = curp[v];
-                    st.cid_mid[v] = curn[v];
+                    off[v] = curp[v];
+                    mid[v] = curn[v];
                 }
                 st.max_sign_rec = std::max<uint64_t>(st.max_sign_rec, std::max(npos[v], nneg[v]));
                 total += (uint64_t)npos[v] + nneg[v];
             }
-            if (!pure) st.cid_off[V] = (uint32_t)total;
-            st.occ_cid.assign(total, 0);
+            if (!pure) off[V] = (uint32_t)total;
+            cid.assign(total, 0);
             for (int k = 1; k <= st.K; ++k) {
                 const auto& b = st.buckets[k];
                 const size_t Cb = b.size() / (size_t)k;
@@ -254,8 +260,17 @@ int32_t build_store(int32_t n_inst, const int32_t* num_vars, const int64_t* lit_
                     for (int e = 0; e < k; ++e) {
                         const uint32_t code = b[c * k + e];
                         uint32_t& pos = (code & 1u) ? curn[code >> 1] : curp[code >> 1];
-                        st.occ_cid[pos++] = (uint32_t)(st.plane_base[k] + (int64_t)c);
+                        cid[pos++] = (uint32_t)(base_of[k] + (int64_t)c);
                     }
+            }
+            // the chunks of the heavy variables, in these records
+            for (size_t h = 0; h + 1 < st.hv_chunk.size(); ++h) {
+                uint32_t rec = off[st.hv_var[h]];
+                for (uint32_t c = st.hv_chunk[h]; c < st.hv_chunk[h + 1]; ++c) {
+                    st.ch_rbeg.push_back(rec);
+                    for (uint32_t q = st.ch_beg[c]; q < st.ch_end[c]; q += 1u + st.occ_data[q]) ++rec;
+                    st.ch_rend.push_back(rec);
+                }
             }
         } catch (const std::bad_alloc&) {
             return fail(TSAT_E_OOM, "host allocation failed while building the clause-index records");

@@ -67,9 +67,13 @@ struct Store {
     std::vector<int64_t> plane_base;   // [TSAT_MAX_WIDTH + 1]; empty without records
     int64_t plane_clauses = 0;         // clauses of widths >= 1 (rows of the plane array)
     uint64_t max_sign_rec = 0;         // most clause-index records of one variable and sign
+    // the same records of a store with wider clauses (K > kMaxPlaneWidth; no
+    // planes, the forward leaves R of a clause in bytes)
+    std::vector<uint32_t> wide_cid, wide_off, wide_mid;
     // generic records: variables with more than kHeavyWords occurrence words,
     // cut at record boundaries into chunks of at most kChunkWords words
     std::vector<uint32_t> heavy, hv_var, hv_chunk, ch_var, ch_beg, ch_end;
+    std::vector<uint32_t> ch_rbeg, ch_rend; // the chunks' ranges of clause-index records
 };
 
 // Validate n_inst DIMACS streams (instance j: lits[lit_off[j] .. lit_off[j+1]),
