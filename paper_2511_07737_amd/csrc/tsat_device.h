@@ -134,6 +134,7 @@ struct VarArgs {
                               // forward's two planes of a clause in one 8-byte word (plane 0 in
                               // the low dword, plane 1 in the high one)
     int32_t xcd;              // XCD-aware order of the variable chunks
+    uint32_t chunk;           // uniform widths, window gather: variables per work item
     const uint32_t* occ_off;  // [V+1] offsets into occ_data (words, or records if pure)
     const uint32_t* occ_mid;  // [V] first record of negative occurrences
     const uint32_t* occ_data; // records: [k-1,] the other k-1 literal indices
@@ -168,7 +169,7 @@ struct VarArgs {
     uint32_t narrow_end;      // clauses below this global index hold 2 planes, the rest 4 (after them)
     const uint32_t* cid_off;  // [V+1] record offsets of occ_cid
     const uint32_t* cid_mid;  // [V] first record of negative occurrences
-    const uint32_t* vchunk;   // null, or [n_vchunk + 1] first variables of the mixed-width
+    const uint32_t* vchunk;   // null, or [n_vchunk][2] first and end variable of the mixed-width
                               // window gather's work items (at most 8 variables and
                               // 64 records each, or one variable)
     int32_t n_vchunk;

@@ -2150,7 +2150,7 @@ __global__ __launch_bounds__(256) void var_window_kernel(VarArgs a)
         return;
     }
     constexpr int K1 = KW + 1;     // R in 0..KW
-    constexpr uint32_t kChunk = 4; // variables per wave work item (measured best of 2, 4, 8, 16)
+    const uint32_t kChunk = a.chunk; // variables per wave work item
     const uint32_t lane = __lane_id();
     const uint32_t wave0 = uniform(blockIdx.x * 4u + threadIdx.x / 64u);
     const uint32_t V = (uint32_t)a.V;
@@ -2832,8 +2832,8 @@ __global__ __launch_bounds__(256) void var_window_levels_kernel(VarArgs a)
     for (uint32_t ch = cr.first; ch < cr.end; ch += cr.stride) {
         uint32_t vb, ve;
         if (a.vchunk) {
-            vb = sload(a.vchunk + ch);
-            ve = sload(a.vchunk + ch + 1);
+            vb = sload(a.vchunk + 2 * (size_t)ch);
+            ve = sload(a.vchunk + 2 * (size_t)ch + 1);
         } else {
             vb = ch * kChunk;
             ve = vb + kChunk < V ? vb + kChunk : V;

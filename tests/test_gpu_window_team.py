@@ -66,3 +66,12 @@ def test_team_gradient_vs_oracle(N):
     aU = abs_adjoint(oc, b, table)
     assert (np.abs(U - orc.adjoint(oc, b, table)) <= TOL_GRAD * aU + 1e-30).all()
     assert (np.abs(g - ref["g"]) <= TOL_GRAD * grad_bound(aU, th, mu, ref["g"]) + 1e-30).all()
+
+
+@pytest.mark.parametrize("V", [2048, 2049, 8193])
+def test_variables_per_wave(V):
+    """One, two and four variables per wave by the store's size (the last item
+    cut short)."""
+    cnf = gen.planted_ksat(V, 4 * V, 3, seed=V)
+    p = tsat.default_params()
+    assert_same(run([cnf], 65, 1, 3, params=p), run([cnf], 65, 0, 3, params=p))
