@@ -41,6 +41,7 @@ struct MlpDev {
     float* grad;       // [kNumParams] last gradient
     uint2* w1op;       // [8][64] BF16x4 operands of layer 1 (rounded W1)
     uint2* w2op;       // [8][8][64] BF16x4 operands of layer 2 (rounded W2)
+    uint2* w2t;        // [8][8][64] the same for the transposed product
     float* w3q;        // [128] rounded w3 as FP32
     float* partial;    // [blocks][kPartialStride]
     float* loss;       // [1]

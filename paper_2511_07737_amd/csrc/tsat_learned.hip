@@ -182,6 +182,34 @@ __device__ __forceinline__ int w2_slot(int k, int c)
     return (((k >> 4) * 8 + (c >> 4)) * 64 + (c & 15) + 16 * ((k & 15) >> 2)) * 4 + (k & 3);
 }
 
+// BF16 slot of W2[k][c] among the operands of the transposed product
+// (da2 W2^T): c-step c/16, column tile k/16, lane k%16 + 16*((c%16)/4),
+// element c%4
+__device__ __forceinline__ int w2t_slot(int k, int c)
+{
+    return (((c >> 4) * 8 + (k >> 4)) * 64 + (k & 15) + 16 * ((c & 15) >> 2)) * 4 + (c & 3);
+}
+
+// Four FP32 values as three BF16 operands each, x = s[0] + s[1] + s[2]: each
+// part is the rounded rest of the ones before it, 8 significant bits a part,
+// so the sum is x itself (values above 2^-110; below, the rest underflows).
+// Products with BF16 operands are then exact in the FP32 accumulation, as
+// FP32 operands would be, at the BF16 matrix rate.
+__device__ __forceinline__ void split_bf16(const float (&x)[4], uint2 (&s)[3])
+{
+    float r[4] = {x[0], x[1], x[2], x[3]};
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+        uint32_t h[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            h[e] = bf16_bits(r[e]);
+            r[e] -= bf16_value(h[e]);
+        }
+        s[p] = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+    }
+}
+
 __device__ __forceinline__ void write_operand(const MlpDev& d, int e, float p)
 {
     if (e < kOffB1) {
@@ -189,6 +217,7 @@ __device__ __forceinline__ void write_operand(const MlpDev& d, int e, float p)
     } else if (e >= kOffW2 && e < kOffB2) {
         const int k = (e - kOffW2) / kHid, c = (e - kOffW2) % kHid;
         reinterpret_cast<uint16_t*>(d.w2op)[w2_slot(k, c)] = (uint16_t)bf16_bits(p);
+        reinterpret_cast<uint16_t*>(d.w2t)[w2t_slot(k, c)] = (uint16_t)bf16_bits(p);
     } else if (e >= kOffW3 && e < kOffB3) {
         d.w3q[e - kOffW3] = bf16_value(bf16_bits(p));
     }
@@ -214,11 +243,21 @@ constexpr int kRed = 3 * kHid + 2;
 // into the A layout of layer 2 (8 K-steps x 8 column tiles against the W2
 // operands held in LDS); layer 3 is a dot product per row.  With TRAIN, the
 // block then forms dLoss/da2 per row and accumulates, over all its rows,
-//   dW2 = h1q^T da2   (each wave 2 of the 8 row tiles of dW2, FP32 MFMA),
+//   dW2 = h1q^T da2   (each wave 2 of the 8 row tiles of dW2),
 //   dh1 = da2 W2q^T   (each wave its own 16 rows),
-//   dW1 = xq^T da1    (each wave 2 of the 8 column tiles),
+//   dW1 = xq^T da1    (each wave 2 of the 8 column tiles, FP32 MFMA),
 // and the bias / w3 gradients, in a fixed order; its sums go to one slot of
 // the partial buffer, which mlp_reduce_kernel adds up in block order.
+// In dW2 and dh1 one factor is BF16 already (h1q, W2q) and da2 is split into
+// three BF16 parts, so they run at the BF16 rate with nothing rounded (error
+// of the gradient against FP64, four seeds: B = 16384 1.3e-7 .. 2.1e-6,
+// FP32 operands 2.8e-7 .. 2.1e-6; B = 60000 1.6e-7 .. 1.0e-6 and 2.9e-7 ..
+// 1.1e-6; the upper ends are rounding decisions of h1 that FP32 and FP64 take
+// differently).  The
+// accumulator layout of the forward is the operand layout of dW2 (lane r + 16 q
+// holds rows 4 q .. 4 q + 3 of column r), so each wave hands its h1 and da2
+// parts over in lane order, without a transpose.  B = 16384, one block per CU:
+// 35.4 us with FP32 operands read element by element from LDS, 28.6 us.
 template <bool TRAIN>
 __global__ __launch_bounds__(256) void mlp_kernel(MlpDev d, const float* __restrict__ X, const float* __restrict__ y,
                                                   const float* __restrict__ wt, int64_t B,
@@ -229,6 +268,8 @@ __global__ __launch_bounds__(256) void mlp_kernel(MlpDev d, const float* __restr
     __shared__ __align__(16) float s_da[TRAIN ? 4 : 1][TRAIN ? 16 * kDS : 1];
     __shared__ __align__(16) float s_xq[TRAIN ? 64 * kXS : 1];
     __shared__ float s_red[TRAIN ? 4 * kRed : 1];
+    __shared__ uint2 s_opA[TRAIN ? 4 : 1][TRAIN ? 8 * 64 : 1];     // h1 of a wave's rows, [tile][lane]
+    __shared__ uint2 s_opB[TRAIN ? 4 : 1][TRAIN ? 3 * 8 * 64 : 1]; // da2 parts, [part][tile][lane]
 
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, r = lane & 15, q = lane >> 4;
     for (int e = tid; e < 8 * 8 * 64; e += 256) s_w2[e] = d.w2op[e];
@@ -272,9 +313,13 @@ __global__ __launch_bounds__(256) void mlp_kernel(MlpDev d, const float* __restr
 #pragma unroll
         for (int n = 0; n < 8; ++n) {
             const v4f c = mfma_bf16(ax, w1[n], zero);
+            uint32_t hb[4];
 #pragma unroll
-            for (int rr = 0; rr < 4; ++rr)
-                h1[(4 * q + rr) * kH1S + 16 * n + r] = (uint16_t)bf16_bits(fmaxf(c[rr] + b1c[n], 0.f));
+            for (int rr = 0; rr < 4; ++rr) {
+                hb[rr] = bf16_bits(fmaxf(c[rr] + b1c[n], 0.f));
+                h1[(4 * q + rr) * kH1S + 16 * n + r] = (uint16_t)hb[rr];
+            }
+            if (TRAIN) s_opA[TRAIN ? wv : 0][TRAIN ? n * 64 + lane : 0] = make_uint2(hb[0] | (hb[1] << 16), hb[2] | (hb[3] << 16));
         }
         __syncthreads();
         v4f acc[8];
@@ -327,38 +372,53 @@ __global__ __launch_bounds__(256) void mlp_kernel(MlpDev d, const float* __restr
         }
         if (r == 0) gb3 += (dout[0] + dout[1]) + (dout[2] + dout[3]);
 #pragma unroll
-        for (int n = 0; n < 8; ++n)
+        for (int n = 0; n < 8; ++n) {
+            float g4[4];
 #pragma unroll
             for (int rr = 0; rr < 4; ++rr) {
                 const float a2 = acc[n][rr] + b2c[n];
                 const float g = a2 > 0.f ? dout[rr] * w3c[n] : 0.f;
+                g4[rr] = g;
                 da[(4 * q + rr) * kDS + 16 * n + r] = g;
                 gb2[n] += g;
                 gw3[n] += fmaxf(a2, 0.f) * dout[rr];
             }
-        __syncthreads();
-        // dW2 row tiles 2*wv and 2*wv+1 over the 64 rows
-        for (int t = 0; t < 16; ++t) {
-            const int rw = 4 * t + q, sw = rw >> 4, lr = rw & 15;
-            const float ha0 = bf16_value(s_h1[sw][lr * kH1S + 16 * (2 * wv) + r]);
-            const float ha1 = bf16_value(s_h1[sw][lr * kH1S + 16 * (2 * wv + 1) + r]);
+            uint2 part[3];
+            split_bf16(g4, part);
 #pragma unroll
-            for (int n = 0; n < 8; ++n) {
-                const float db = s_da[TRAIN ? sw : 0][lr * kDS + 16 * n + r];
-                gW2[0][n] = mfma_f32(ha0, db, gW2[0][n]);
-                gW2[1][n] = mfma_f32(ha1, db, gW2[1][n]);
-            }
+            for (int p = 0; p < 3; ++p) s_opB[TRAIN ? wv : 0][TRAIN ? (p * 8 + n) * 64 + lane : 0] = part[p];
+        }
+        __syncthreads();
+        // dW2 row tiles 2*wv and 2*wv+1 over the four waves' rows, smallest
+        // parts first
+        for (int sw = 0; sw < 4; ++sw) {
+            const uint2 a0 = s_opA[TRAIN ? sw : 0][TRAIN ? (2 * wv) * 64 + lane : 0];
+            const uint2 a1 = s_opA[TRAIN ? sw : 0][TRAIN ? (2 * wv + 1) * 64 + lane : 0];
+#pragma unroll
+            for (int n = 0; n < 8; ++n)
+#pragma unroll
+                for (int p = 2; p >= 0; --p) {
+                    const uint2 b = s_opB[TRAIN ? sw : 0][TRAIN ? (p * 8 + n) * 64 + lane : 0];
+                    gW2[0][n] = mfma_bf16(a0, b, gW2[0][n]);
+                    gW2[1][n] = mfma_bf16(a1, b, gW2[1][n]);
+                }
         }
         // dh1 of this wave's rows: sum over columns of da2 * W2q
         v4f dh[8];
 #pragma unroll
         for (int m = 0; m < 8; ++m) dh[m] = zero;
-        const uint16_t* w2e = reinterpret_cast<const uint16_t*>(s_w2);
-        for (int t = 0; t < 32; ++t) {
-            const int col = 4 * t + q;
-            const float aa = da[r * kDS + col];
+#pragma unroll 2
+        for (int st = 0; st < 8; ++st) {
+            const float4 f = *reinterpret_cast<const float4*>(&da[r * kDS + 16 * st + 4 * q]);
+            const float x4[4] = {f.x, f.y, f.z, f.w};
+            uint2 part[3];
+            split_bf16(x4, part);
 #pragma unroll
-            for (int m = 0; m < 8; ++m) dh[m] = mfma_f32(aa, bf16_value(w2e[w2_slot(16 * m + r, col)]), dh[m]);
+            for (int m = 0; m < 8; ++m) {
+                const uint2 b = d.w2t[(st * 8 + m) * 64 + lane];
+#pragma unroll
+                for (int p = 2; p >= 0; --p) dh[m] = mfma_bf16(part[p], b, dh[m]);
+            }
         }
         __syncthreads(); // every wave is done with the da2 tiles
 #pragma unroll

@@ -21,7 +21,7 @@ constexpr double kBeta1 = 0.9, kBeta2 = 0.999, kEps = 1e-8;
 
 struct tsat_mlp {
     int32_t device = 0;
-    DBuf params, m, v, grad, w1op, w2op, w3q, partial, loss;
+    DBuf params, m, v, grad, w1op, w2op, w2t, w3q, partial, loss;
     int64_t t = 0;
     bool have_grad = false;
     MlpDev view() const
@@ -33,6 +33,7 @@ struct tsat_mlp {
         d.grad = grad.as<float>();
         d.w1op = w1op.as<uint2>();
         d.w2op = w2op.as<uint2>();
+        d.w2t = w2t.as<uint2>();
         d.w3q = w3q.as<float>();
         d.partial = partial.as<float>();
         d.loss = loss.as<float>();
@@ -102,6 +103,7 @@ int32_t tsat_mlp_create(int32_t device, const float* params, tsat_mlp** out)
     if (rc == TSAT_OK) rc = m->grad.alloc(np, "network gradient");
     if (rc == TSAT_OK) rc = m->w1op.alloc(8 * 64 * sizeof(uint2), "layer-1 operands");
     if (rc == TSAT_OK) rc = m->w2op.alloc(8 * 8 * 64 * sizeof(uint2), "layer-2 operands");
+    if (rc == TSAT_OK) rc = m->w2t.alloc(8 * 8 * 64 * sizeof(uint2), "transposed layer-2 operands");
     if (rc == TSAT_OK) rc = m->w3q.alloc(kHid * sizeof(float), "layer-3 operands");
     if (rc == TSAT_OK) rc = m->partial.alloc((size_t)kMaxTrainBlocks * kPartialStride * sizeof(float), "gradient partials");
     if (rc == TSAT_OK) rc = m->loss.alloc(sizeof(float), "loss");
