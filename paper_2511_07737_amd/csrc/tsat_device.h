@@ -219,7 +219,7 @@ hipError_t noalloc_scratch_address(int device, void** out);
 hipError_t launch_var(const VarArgs& a, int op, int blocks, hipStream_t st);
 int var_occupancy(const VarArgs& a, int op); // resident 256-thread blocks per CU of the step kernel
 hipError_t launch_expand(const uint64_t* bits, int64_t V, int W, int N, uint64_t* lits, hipStream_t st);
-hipError_t launch_pack(const float* assign, int V, int N, int W, uint64_t* out, int lit_rows, hipStream_t st);
+hipError_t launch_pack(const float* assign, int V, int N, int W, uint64_t* bits, hipStream_t st);
 hipError_t launch_init_normal(float* theta, int64_t n, uint64_t seed, hipStream_t st);
 hipError_t launch_fill_u32(uint32_t* p, int64_t n, uint32_t val, hipStream_t st);
 hipError_t launch_copy16(void* dst, const void* src, int64_t n16, int blocks, hipStream_t st);

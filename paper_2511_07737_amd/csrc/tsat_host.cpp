@@ -1953,7 +1953,7 @@ int32_t tsat_pack_dev(tsat_solver* s, const float* assign, int32_t N, uint64_t* 
     if (N < 1 || !assign || !bits) return fail(TSAT_E_ARG, "invalid arguments");
     RET(set_dev(s));
     hipStream_t st = (hipStream_t)stream; // NULL: the null (default) stream
-    HIPCHK(launch_pack(assign, s->st.V, N, (N + 63) / 64, bits, 0, st));
+    HIPCHK(launch_pack(assign, s->st.V, N, (N + 63) / 64, bits, st));
     return TSAT_OK;
 }
 

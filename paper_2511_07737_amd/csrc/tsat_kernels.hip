@@ -3275,28 +3275,35 @@ __global__ void expand_kernel(const uint64_t* __restrict__ bits, int64_t V, int 
     lits[(2 * v + 1) * W + j] = ~x & vm;
 }
 
-// Float assignment [V][N] (value > 0.5 = True) -> literal rows [2V][W]
-// (lit_rows = 1) or variable bits [V][W] (lit_rows = 0).
-__global__ void pack_kernel(const float* __restrict__ assign, int V, int N, int W, uint64_t* __restrict__ lits,
-                            int lit_rows)
+// Float assignment [V][N] (value > 0.5 = True) -> variable bits [V][W].
+// Bound by latency with one word per wave: a wave takes R consecutive words,
+// all their loads in flight, and lane q stores word q, so that the words
+// leave in one store (V = 1e5, N = 100, 40 MB: 23.7 us with a word per wave,
+// 16.0 at R = 4, 16.6 at 8, 16.8 at 16).
+template <int R>
+__global__ __launch_bounds__(256) void pack_kernel(const float* __restrict__ assign, int V, int N, int W,
+                                                   uint64_t* __restrict__ bits)
 {
     const uint32_t lane = __lane_id();
-    const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / 64;
-    if (wave >= (int64_t)V * W) return;
-    const int64_t v = wave / W;
-    const int j = (int)(wave % W);
-    const int i = 64 * j + (int)lane;
-    const bool valid = i < N;
-    const bool p = valid && assign[v * N + i] > 0.5f;
-    const uint64_t bal = ballot64(p), vm = ballot64(valid);
-    if (lane == 0) {
-        if (lit_rows) {
-            lits[(2 * v) * W + j] = bal;
-            lits[(2 * v + 1) * W + j] = ~bal & vm;
-        } else {
-            lits[v * W + j] = bal;
-        }
+    const int64_t words = (int64_t)V * W;
+    const int64_t w0 = ((int64_t)blockIdx.x * 4 + uniform(threadIdx.x / 64u)) * R;
+    if (w0 >= words) return;
+    int64_t v = w0 / W;
+    int j = (int)(w0 - v * W);
+    float x[R];
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+        const int i = 64 * j + (int)lane;
+        x[q] = w0 + q < words && i < N ? assign[v * N + i] : 0.f; // 0: False past N
+        if (++j == W) j = 0, ++v;
     }
+    uint64_t word = 0;
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+        const uint64_t bal = ballot64(x[q] > 0.5f);
+        if (lane == (uint32_t)q) word = bal;
+    }
+    if (lane < (uint32_t)R && w0 + lane < words) bits[w0 + lane] = word;
 }
 
 // Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC'11) + Box-Muller.
@@ -4297,11 +4304,13 @@ hipError_t launch_expand(const uint64_t* bits, int64_t V, int W, int N, uint64_t
     return hipGetLastError();
 }
 
-hipError_t launch_pack(const float* assign, int V, int N, int W, uint64_t* out, int lit_rows, hipStream_t st)
+hipError_t launch_pack(const float* assign, int V, int N, int W, uint64_t* bits, hipStream_t st)
 {
-    const int64_t waves = (int64_t)V * W;
-    if (waves == 0) return hipSuccess;
-    hipLaunchKernelGGL(pack_kernel, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st, assign, V, N, W, out, lit_rows);
+    const int64_t words = (int64_t)V * W;
+    if (words == 0) return hipSuccess;
+    constexpr int R = 4;
+    hipLaunchKernelGGL(pack_kernel<R>, dim3((unsigned)((words + 4 * R - 1) / (4 * R))), dim3(256), 0, st, assign, V, N,
+                       W, bits);
     return hipGetLastError();
 }
 
