@@ -192,9 +192,10 @@ __device__ __forceinline__ int w2t_slot(int k, int c)
 
 // Four FP32 values as three BF16 operands each, x = s[0] + s[1] + s[2]: each
 // part is the rounded rest of the ones before it, 8 significant bits a part,
-// so the sum is x itself (values above 2^-110; below, the rest underflows).
-// Products with BF16 operands are then exact in the FP32 accumulation, as
-// FP32 operands would be, at the BF16 matrix rate.
+// so the sum is x itself for magnitudes of 2^-102 (below, the last part leaves
+// the normal numbers) up to 2^127 (above, the first may round to infinity).
+// An infinity has no rest.  Products with BF16 operands are then exact in the
+// FP32 accumulation, as FP32 operands would be, at the BF16 matrix rate.
 __device__ __forceinline__ void split_bf16(const float (&x)[4], uint2 (&s)[3])
 {
     float r[4] = {x[0], x[1], x[2], x[3]};
@@ -204,7 +205,8 @@ __device__ __forceinline__ void split_bf16(const float (&x)[4], uint2 (&s)[3])
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             h[e] = bf16_bits(r[e]);
-            r[e] -= bf16_value(h[e]);
+            const float rest = r[e] - bf16_value(h[e]);
+            r[e] = p > 0 || fabsf(r[e]) < __builtin_inff() ? rest : 0.f;
         }
         s[p] = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
     }
@@ -249,7 +251,10 @@ constexpr int kRed = 3 * kHid + 2;
 // and the bias / w3 gradients, in a fixed order; its sums go to one slot of
 // the partial buffer, which mlp_reduce_kernel adds up in block order.
 // In dW2 and dh1 one factor is BF16 already (h1q, W2q) and da2 is split into
-// three BF16 parts, so they run at the BF16 rate with nothing rounded (error
+// three BF16 parts, so they run at the BF16 rate with nothing rounded: da2 and
+// what follows from it are held at 2^24 times their size, so that the parts of
+// small ones stay normal numbers, or at 2^-24 where the block's row weights
+// and labels allow a da2 past 2^76 or are not finite (error
 // of the gradient against FP64, four seeds: B = 16384 1.3e-7 .. 2.1e-6,
 // FP32 operands 2.8e-7 .. 2.1e-6; B = 60000 1.6e-7 .. 1.0e-6 and 2.9e-7 ..
 // 1.1e-6; the upper ends are rounding decisions of h1 that FP32 and FP64 take
@@ -257,7 +262,8 @@ constexpr int kRed = 3 * kHid + 2;
 // accumulator layout of the forward is the operand layout of dW2 (lane r + 16 q
 // holds rows 4 q .. 4 q + 3 of column r), so each wave hands its h1 and da2
 // parts over in lane order, without a transpose.  B = 16384, one block per CU:
-// 35.4 us with FP32 operands read element by element from LDS, 28.6 us.
+// 35.4 us with FP32 operands read element by element from LDS, 29.4 us (0.8 of
+// it for the scale).
 template <bool TRAIN>
 __global__ __launch_bounds__(256) void mlp_kernel(MlpDev d, const float* __restrict__ X, const float* __restrict__ y,
                                                   const float* __restrict__ wt, int64_t B,
@@ -270,8 +276,18 @@ __global__ __launch_bounds__(256) void mlp_kernel(MlpDev d, const float* __restr
     __shared__ float s_red[TRAIN ? 4 * kRed : 1];
     __shared__ uint2 s_opA[TRAIN ? 4 : 1][TRAIN ? 8 * 64 : 1];     // h1 of a wave's rows, [tile][lane]
     __shared__ uint2 s_opB[TRAIN ? 4 : 1][TRAIN ? 3 * 8 * 64 : 1]; // da2 parts, [part][tile][lane]
+    __shared__ int s_large;                                        // a da2 may pass 2^76
 
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, r = lane & 15, q = lane >> 4;
+    // |dLoss/dout| <= |weight| (1 + |label|) / B; a NaN stays
+    float reach = 0.f;
+    if (TRAIN) {
+        if (tid == 0) s_large = 0;
+        for (int64_t i = ((int64_t)wv * gridDim.x + blockIdx.x) * 64 + lane; i < B; i += (int64_t)gridDim.x * 256) {
+            const float x = (wt ? fabsf(wt[i]) : 1.f) * (1.f + fabsf(y[i]));
+            reach = x <= reach ? reach : x;
+        }
+    }
     for (int e = tid; e < 8 * 8 * 64; e += 256) s_w2[e] = d.w2op[e];
     uint2 w1[8];
     float b1c[8], b2c[8], w3c[8];
@@ -283,7 +299,19 @@ __global__ __launch_bounds__(256) void mlp_kernel(MlpDev d, const float* __restr
         w3c[n] = d.w3q[16 * n + r];
     }
     const float b3 = d.params[kOffB3];
+    const float invB = 1.f / (float)B;
+    float scale = 0x1p24f;
+    if (TRAIN) {
+        float w3top = 0x1p-24f;
+#pragma unroll
+        for (int n = 0; n < 8; ++n) w3top = fmaxf(w3top, fabsf(w3c[n]));
+#pragma unroll
+        for (int m = 1; m < 16; m <<= 1) w3top = fmaxf(w3top, __shfl_xor(w3top, m));
+        __syncthreads(); // s_large is cleared
+        if (!(reach * invB * w3top < 0x1p76f)) s_large = 1;
+    }
     __syncthreads();
+    if (TRAIN && s_large) scale = 0x1p-24f;
 
     const v4f zero = {0.f, 0.f, 0.f, 0.f};
     v4f gW2[2][8], gW1[2];
@@ -295,7 +323,6 @@ __global__ __launch_bounds__(256) void mlp_kernel(MlpDev d, const float* __restr
         gb1[n] = gb2[n] = gw3[n] = 0.f;
     }
     gW1[0] = gW1[1] = zero;
-    const float invB = 1.f / (float)B;
     const int64_t nsuper = (B + 63) / 64;
     uint16_t* h1 = s_h1[wv];
     float* da = s_da[TRAIN ? wv : 0];
@@ -370,6 +397,9 @@ __global__ __launch_bounds__(256) void mlp_kernel(MlpDev d, const float* __restr
                 if (r == 0) gloss += ww * (fmaxf(z, 0.f) + log1pf(expf(-fabsf(z))) - yy * z) * invB;
             }
         }
+        float ds[4]; // scaled; a NaN as the one whose upper half is a NaN
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr) ds[rr] = dout[rr] == dout[rr] ? dout[rr] * scale : __builtin_nanf("");
         if (r == 0) gb3 += (dout[0] + dout[1]) + (dout[2] + dout[3]);
 #pragma unroll
         for (int n = 0; n < 8; ++n) {
@@ -377,7 +407,7 @@ __global__ __launch_bounds__(256) void mlp_kernel(MlpDev d, const float* __restr
 #pragma unroll
             for (int rr = 0; rr < 4; ++rr) {
                 const float a2 = acc[n][rr] + b2c[n];
-                const float g = a2 > 0.f ? dout[rr] * w3c[n] : 0.f;
+                const float g = a2 > 0.f ? ds[rr] * w3c[n] : 0.f;
                 g4[rr] = g;
                 da[(4 * q + rr) * kDS + 16 * n + r] = g;
                 gb2[n] += g;
@@ -443,6 +473,7 @@ __global__ __launch_bounds__(256) void mlp_kernel(MlpDev d, const float* __restr
     }
     if (!TRAIN) return;
 
+    const float unscale = 1.f / scale;
     float* P = d.partial + (int64_t)blockIdx.x * kPartialStride;
 #pragma unroll
     for (int mm = 0; mm < 2; ++mm) {
@@ -450,9 +481,9 @@ __global__ __launch_bounds__(256) void mlp_kernel(MlpDev d, const float* __restr
         for (int n = 0; n < 8; ++n)
 #pragma unroll
             for (int rr = 0; rr < 4; ++rr)
-                P[kOffW2 + (16 * (2 * wv + mm) + 4 * q + rr) * kHid + 16 * n + r] = gW2[mm][n][rr];
+                P[kOffW2 + (16 * (2 * wv + mm) + 4 * q + rr) * kHid + 16 * n + r] = gW2[mm][n][rr] * unscale;
 #pragma unroll
-        for (int rr = 0; rr < 4; ++rr) P[kOffW1 + (4 * q + rr) * kHid + 16 * (2 * wv + mm) + r] = gW1[mm][rr];
+        for (int rr = 0; rr < 4; ++rr) P[kOffW1 + (4 * q + rr) * kHid + 16 * (2 * wv + mm) + r] = gW1[mm][rr] * unscale;
     }
 #pragma unroll
     for (int n = 0; n < 8; ++n) {
@@ -470,8 +501,8 @@ __global__ __launch_bounds__(256) void mlp_kernel(MlpDev d, const float* __restr
     if (q == 0) {
 #pragma unroll
         for (int n = 0; n < 8; ++n) {
-            s_red[wv * kRed + 16 * n + r] = gb1[n];
-            s_red[wv * kRed + kHid + 16 * n + r] = gb2[n];
+            s_red[wv * kRed + 16 * n + r] = gb1[n] * unscale;
+            s_red[wv * kRed + kHid + 16 * n + r] = gb2[n] * unscale;
             s_red[wv * kRed + 2 * kHid + 16 * n + r] = gw3[n];
         }
     }
