@@ -530,7 +530,10 @@ __global__ __launch_bounds__(256) void smin_kernel(SminArgs a)
     double loss = 0.0;
     int64_t best = -1;
     int32_t bidx = 0x7fffffff, satc = 0x7fffffff;
-    for (int i0 = blockIdx.y * 256; i0 < a.Np; i0 += gridDim.y * 256) {
+    // passes of 256 candidates, counted in passes: Np may be close to 2^31
+    const int passes = (a.Np - 1) / 256 + 1;
+    for (int pass = blockIdx.y; pass < passes; pass += gridDim.y) {
+        const int i0 = pass * 256;
         // this pass's histogram rows: the replicas' sum, cleared on the way
         const int rows = min(256, a.Np - i0);
         for (int g = tid; g < rows * K1 / 4; g += 256) { // 16 bytes: rows is a multiple of 64
@@ -3945,7 +3948,7 @@ hipError_t launch_smin(const SminArgs& a, hipStream_t st)
     // the candidates of an evaluation without a loss or bookkeeping are
     // independent: as many blocks as they fill (a brute-force check has
     // millions)
-    const unsigned tiles = (a.ictrl || a.loss_out) ? 1u : (unsigned)std::min(4096, (a.Np + 255) / 256);
+    const unsigned tiles = (a.ictrl || a.loss_out) ? 1u : (unsigned)std::min(4096, (a.Np - 1) / 256 + 1);
     const size_t lds = (size_t)256 * (a.K1 | 1) * sizeof(uint32_t);
     hipLaunchKernelGGL(smin_kernel, dim3((unsigned)a.n_inst, tiles), dim3(256), lds, st, a);
     return hipGetLastError();
