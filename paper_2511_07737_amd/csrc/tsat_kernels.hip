@@ -1766,6 +1766,11 @@ __device__ __forceinline__ void var_pure_body(const VarArgs& a)
     }
 }
 
+// A half of a window's 64-bit word.  The words were stored as such by the same
+// lane: without the attribute the compiler may move the loads of halves ahead
+// of the stores, as types that cannot alias.
+typedef uint32_t __attribute__((may_alias)) half_word;
+
 // Counts of the window gathers.  cnt[r - 1][j] collects, for candidate
 // 64 j + lane and level r, (positive - negative records whose clause has
 // R >= r) + (negative records): with the positive records' window bits in mp
@@ -1801,7 +1806,7 @@ __device__ __forceinline__ void count_window(const uint64_t* win, uint32_t lane,
     if ((uint32_t)(m >> 32) == 0u || (uint32_t)m == 0u) { // wave-uniform
         // they lie in one 32-bit half (most do): count on its dwords only
         const uint32_t hf = (uint32_t)m == 0u ? 1u : 0u;
-        const uint32_t* win32 = reinterpret_cast<const uint32_t*>(win);
+        const half_word* win32 = reinterpret_cast<const half_word*>(win);
         uint32_t b0[J], b1[J];
 #pragma unroll
         for (int j = 0; j < J; ++j) {
@@ -2881,7 +2886,7 @@ __global__ __launch_bounds__(256) void var_window_levels_kernel(VarArgs a)
                     // the variable's records in this window lie in one 32-bit
                     // half (most do): count on that half's dwords only
                     const uint32_t hf = (uint32_t)m == 0u ? 1u : 0u;
-                    const uint32_t* win32 = reinterpret_cast<const uint32_t*>(my_win);
+                    const half_word* win32 = reinterpret_cast<const half_word*>(my_win);
                     const uint32_t mp32 = (uint32_t)(mp >> (32u * hf)), mn32 = (uint32_t)(mn >> (32u * hf));
 #pragma unroll
                     for (int j = 0; j < J; ++j) {
