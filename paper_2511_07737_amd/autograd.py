@@ -16,7 +16,9 @@ passes their pointers and torch's current stream, and wires the backward.
 
 The layer and the loss keep the forward's histogram, row means and clause
 planes in a saved tensor, so that the backward does not form the forward
-again; without a gradient to compute nothing is kept.
+again; without a gradient to compute nothing is kept.  Inside ``forward`` autograd
+is off and ``needs_input_grad`` only says that the input asks for a gradient,
+so the wrappers pass on whether autograd was recording.
 """
 from __future__ import annotations
 
@@ -56,7 +58,7 @@ def _upstream(t: torch.Tensor) -> torch.Tensor:
 
 class SmoothMinSat(torch.autograd.Function):
     @staticmethod
-    def forward(ctx, assign: torch.Tensor, solver: tsat.Solver, tau: float):
+    def forward(ctx, assign: torch.Tensor, solver: tsat.Solver, tau: float, grad: bool = True):
         assign = _logits(assign, solver)
         V, N = assign.shape
         W = (N + 63) // 64
@@ -64,7 +66,7 @@ class SmoothMinSat(torch.autograd.Function):
         bits = torch.empty((V, W), dtype=torch.int64, device=assign.device)
         solver.pack_dev(assign.data_ptr(), N, bits.data_ptr(), stream)
         S = torch.empty(N, dtype=torch.float32, device=assign.device)
-        saved = _saved_buffer(solver, N, assign.device) if ctx.needs_input_grad[0] else None
+        saved = _saved_buffer(solver, N, assign.device) if grad and ctx.needs_input_grad[0] else None
         if saved is None:
             solver.fwd_dev(bits.data_ptr(), N, tau, S.data_ptr(), None, stream)
             ctx.save_for_backward(bits)
@@ -88,12 +90,12 @@ class SmoothMinSat(torch.autograd.Function):
                                      saved[0].numel(), ctx.key, _stream(bits))
         else:
             ctx.solver.bwd_dev(bits.data_ptr(), N, ctx.tau, dS.data_ptr(), U.data_ptr(), _stream(bits))
-        return U, None, None
+        return U, None, None, None
 
 
 def smoothmin_sat(assign: torch.Tensor, solver: tsat.Solver, tau: float = 1.0) -> torch.Tensor:
     """S[N] of the binary assignment ``assign`` [V][N] (differentiable via the STE adjoint)."""
-    return SmoothMinSat.apply(assign, solver, float(tau))
+    return SmoothMinSat.apply(assign, solver, float(tau), torch.is_grad_enabled())
 
 
 class Binarize(torch.autograd.Function):
@@ -125,11 +127,11 @@ def binarize(theta: torch.Tensor, solver: tsat.Solver, mode: int = tsat.MODE_MEA
 
 class LogitLoss(torch.autograd.Function):
     @staticmethod
-    def forward(ctx, theta: torch.Tensor, solver: tsat.Solver, tau: float, mode: int):
+    def forward(ctx, theta: torch.Tensor, solver: tsat.Solver, tau: float, mode: int, grad: bool = True):
         theta = _logits(theta, solver)
         loss = torch.empty((), dtype=torch.float32, device=theta.device)
         N, stream = theta.shape[1], _stream(theta)
-        saved = _saved_buffer(solver, N, theta.device) if ctx.needs_input_grad[0] else None
+        saved = _saved_buffer(solver, N, theta.device) if grad and ctx.needs_input_grad[0] else None
         if saved is None:
             solver.loss_dev(theta.data_ptr(), N, tau, mode, loss.data_ptr(), None, None, stream)
             ctx.save_for_backward(theta)
@@ -152,9 +154,10 @@ class LogitLoss(torch.autograd.Function):
             ctx.solver.loss_backward_saved_dev(*args, saved[0].data_ptr(), saved[0].numel(), ctx.key, _stream(theta))
         else:
             ctx.solver.loss_backward_dev(*args, _stream(theta))
-        return g, None, None, None
+        return g, None, None, None, None
 
 
 def loss_of(theta: torch.Tensor, solver: tsat.Solver, tau: float = 1.0, normalize: bool = True) -> torch.Tensor:
     """L = -sum_i S_i (Eq. 3) of the logits theta [V][N], as a 0-d tensor."""
-    return LogitLoss.apply(theta, solver, float(tau), tsat.MODE_MEAN if normalize else tsat.MODE_NONE)
+    mode = tsat.MODE_MEAN if normalize else tsat.MODE_NONE
+    return LogitLoss.apply(theta, solver, float(tau), mode, torch.is_grad_enabled())
