@@ -50,6 +50,12 @@ def _saved_buffer(solver: tsat.Solver, n: int, device) -> torch.Tensor | None:
         return None
 
 
+def _readable(saved: list) -> bool:
+    """Whether a backward has a saved state it can read: saved-tensor hooks may
+    hand back a copy at any offset or stride (the plain call then runs)."""
+    return bool(saved) and saved[0].is_cuda and saved[0].is_contiguous() and saved[0].data_ptr() % 256 == 0
+
+
 def _upstream(t: torch.Tensor) -> torch.Tensor:
     if t.dtype != torch.float32:
         raise ValueError(f"upstream gradient must be float32 (got {t.dtype})")
@@ -85,7 +91,7 @@ class SmoothMinSat(torch.autograd.Function):
         V, N = ctx.shape
         dS = _upstream(dS)
         U = torch.empty((V, N), dtype=torch.float32, device=bits.device)
-        if saved:
+        if _readable(saved):
             ctx.solver.bwd_saved_dev(bits.data_ptr(), N, ctx.tau, dS.data_ptr(), U.data_ptr(), saved[0].data_ptr(),
                                      saved[0].numel(), ctx.key, _stream(bits))
         else:
@@ -150,7 +156,7 @@ class LogitLoss(torch.autograd.Function):
         dloss = _upstream(dloss)
         g = torch.empty_like(theta)
         args = (theta.data_ptr(), theta.shape[1], ctx.tau, ctx.mode, dloss.data_ptr(), g.data_ptr(), None)
-        if saved:
+        if _readable(saved):
             ctx.solver.loss_backward_saved_dev(*args, saved[0].data_ptr(), saved[0].numel(), ctx.key, _stream(theta))
         else:
             ctx.solver.loss_backward_dev(*args, _stream(theta))

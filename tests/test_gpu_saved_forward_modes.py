@@ -1,5 +1,6 @@
 """When a forward is saved for its backward, and what happens to the saved
-memory in between: nothing is saved without autograd."""
+memory in between: nothing is saved without autograd, and a saved-tensor hook
+may hand the memory back at any offset."""
 import pytest
 
 from paper_2511_07737_amd import gen, tsat
@@ -32,3 +33,31 @@ def test_nothing_saved_without_autograd(env, monkeypatch, guard):
     assert all(torch.equal(x, y) for x, y in zip(got, want))
     with pytest.raises(AssertionError):
         ag.loss_of(T, s)
+
+
+def test_hooks_may_move_the_saved_state(env):
+    torch, s, ag = env
+    cnf = CNFS["3sat"]()
+    s.load(cnf)
+    T, A = inputs(torch, cnf, 40, 4)
+    dS = torch.linspace(-1, 2, 40, device="cuda")
+
+    def grads():
+        return torch.autograd.grad(ag.loss_of(T, s), T) + torch.autograd.grad(ag.smoothmin_sat(A, s), A, dS)
+
+    want = grads()
+    spaced = lambda t: torch.stack([t, t], -1)[..., 0] if t.dtype == torch.uint8 else t  # noqa: E731
+    for off in (1, 8, 64):
+        def pack(t):
+            # one arena for all tensors, offsets as they come (each type's own alignment kept)
+            arena = torch.empty(off + 256 + t.numel() * t.element_size(), dtype=torch.uint8, device="cuda")
+            at = off if t.dtype == torch.uint8 else 8
+            part = arena[at:at + t.numel() * t.element_size()]
+            part.copy_(t.reshape(-1).view(torch.uint8))
+            return part, t.dtype, t.shape
+
+        with torch.autograd.graph.saved_tensors_hooks(pack, lambda p: p[0].view(p[1]).view(p[2])):
+            got = grads()
+        assert all(torch.equal(x, y) for x, y in zip(got, want)), off
+    with torch.autograd.graph.saved_tensors_hooks(lambda t: t, spaced):
+        assert all(torch.equal(x, y) for x, y in zip(grads(), want))
