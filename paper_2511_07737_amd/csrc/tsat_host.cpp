@@ -56,10 +56,10 @@ struct tsat_solver {
     DBuf occ_cid;            // clause-index records (widths up to kMaxPlaneWidth)
     DBuf cid_off, cid_mid;   // their record offsets (stores with generic occurrence records)
     DBuf wide_cid, wide_off, wide_mid; // the same of a store with clauses past kMaxPlaneWidth
-    bool bytes_off = false;  // the forward's bytes of R did not fit: row gather
     DBuf vchunk;             // work items of the mixed-width window gather: first variables
     int32_t n_vchunk = 0;
-    DBuf planes, planes_scr; // R of every clause in binary, for the step / for evaluations
+    DBuf planes, planes_scr; // R of every clause (binary or bytes), for the step / for evaluations
+    size_t planes_refused = 0, scr_refused = 0; // bytes of each that did not fit: row gather
     DBuf heavy, hv_var, hv_chunk, ch_var, ch_beg, ch_end, ch_rbeg, ch_rend; // chunked heavy variables (generic stores)
     DBuf partial, partial_scr; // FP64 partial sums of the chunks, for the step / for evaluations
 
@@ -335,7 +335,7 @@ static size_t rbytes_bytes(const tsat_solver* s, int32_t N)
 
 static bool bytes_path(const tsat_solver* s, int32_t N)
 {
-    return s->clause_planes && !s->bytes_off && s->st.pure_k == 0 && (s->wide_cid.p || s->occ_cid.p) &&
+    return s->clause_planes && s->st.pure_k == 0 && (s->wide_cid.p || s->occ_cid.p) &&
            s->rows_per_var == 1 && N <= TSAT_MAX_STEP_N && !plane_path(s, N) &&
            rbytes_bytes(s, N) <= ((size_t)8 << 30);
 }
@@ -366,19 +366,34 @@ static size_t planes_bytes(const tsat_solver* s, int32_t N)
     return std::max<size_t>(16, words * 8 * (size_t)row_words((N + 63) / 64));
 }
 
-static int32_t ensure_planes(tsat_solver* s, DBuf& buf, int32_t N, hipStream_t st)
+// Room for them in `buf`.  Past 256 candidates, and as bytes, they are a
+// convenience: where the memory does not fit (`refused`: the size that last
+// did not), the buffer stays without and the rows are gathered.
+static int32_t ensure_planes(tsat_solver* s, DBuf& buf, size_t& refused, int32_t N, hipStream_t st)
 {
-    const size_t bytes = planes_bytes(s, N);
-    if (buf.p && buf.bytes >= bytes) return TSAT_OK;
-    if (bytes_path(s, N)) {
-        // a convenience: without the memory the row gather stays
-        s->bytes_off = buf.alloc(bytes, "bytes of R") != TSAT_OK;
-        if (s->bytes_off) g_err.clear();
+    const bool bytes = bytes_path(s, N);
+    if (!bytes && !plane_path(s, N)) return TSAT_OK;
+    const size_t need = planes_bytes(s, N);
+    if (buf.p && buf.bytes >= need) return TSAT_OK;
+    const bool optional = bytes || N > 256;
+    if (optional && refused && need >= refused) return TSAT_OK;
+    const int32_t rc = buf.alloc(need, bytes ? "bytes of R" : "clause planes");
+    if (rc != TSAT_OK && optional) {
+        refused = need;
+        g_err.clear();
         return TSAT_OK;
     }
-    RET(buf.alloc(bytes, "clause planes"));
-    HIPCHK(launch_fill_u32(buf.as<uint32_t>(), (int64_t)(bytes / 4), 0u, st));
+    RET(rc);
+    if (!bytes) HIPCHK(launch_fill_u32(buf.as<uint32_t>(), (int64_t)(need / 4), 0u, st));
     return TSAT_OK;
+}
+
+// `buf` as the planes (or bytes) of N candidates; null where the forward
+// writes none or they do not fit it.
+static uint32_t* planes_in(const tsat_solver* s, const DBuf& buf, int32_t N)
+{
+    const bool any = plane_path(s, N) || bytes_path(s, N);
+    return any && buf.p && buf.bytes >= planes_bytes(s, N) ? buf.as<uint32_t>() : nullptr;
 }
 
 // Work units of every wide bucket (width > 4) for one launch of the
@@ -675,7 +690,9 @@ static int var_blocks(const tsat_solver* s, int32_t V, int occ = 0)
     return (int)std::max<int64_t>(1, std::min<int64_t>(want, (int64_t)s->cus * per_cu));
 }
 
-static VarArgs var_args(tsat_solver* s, const tsat_params& p, int32_t N, int32_t W, int32_t Np)
+// `planes`: the forward's planes or bytes of R for a gather over them; null:
+// the other literals' rows are gathered (or nothing at all).
+static VarArgs var_args(tsat_solver* s, const tsat_params& p, int32_t N, int32_t W, int32_t Np, uint32_t* planes)
 {
     VarArgs a{};
     a.V = s->st.V;
@@ -705,17 +722,15 @@ static VarArgs var_args(tsat_solver* s, const tsat_params& p, int32_t N, int32_t
     a.one_minus_beta1 = (float)(1.0 - p.beta1);
     a.one_minus_beta2 = (float)(1.0 - p.beta2);
     a.eps = (float)p.eps;
-    // clause-plane gather: evaluations write their planes to planes_scr, the
-    // step overrides this with its own buffer
-    a.occ_cid = plane_path(s, N) ? s->occ_cid.as<uint32_t>() : nullptr;
+    a.occ_cid = planes && plane_path(s, N) ? s->occ_cid.as<uint32_t>() : nullptr;
     a.narrow_end = s->loaded && s->occ_cid.p ? (uint32_t)narrow_end(s) : 0u;
     a.cid_off = s->cid_off.p ? s->cid_off.as<uint32_t>() : a.occ_off;
     a.cid_mid = s->cid_mid.p ? s->cid_mid.as<uint32_t>() : a.occ_mid;
     a.vchunk = s->vchunk.p ? s->vchunk.as<uint32_t>() : nullptr;
     a.n_vchunk = s->n_vchunk;
-    a.planes = s->planes_scr.as<uint32_t>();
-    if (bytes_path(s, N)) { // likewise
-        a.rb = s->planes_scr.as<uint8_t>();
+    a.planes = planes;
+    if (planes && bytes_path(s, N)) {
+        a.rb = reinterpret_cast<const uint8_t*>(planes);
         a.occ_cid = s->wide_cid.p ? s->wide_cid.as<uint32_t>() : s->occ_cid.as<uint32_t>();
         if (s->wide_cid.p) {
             a.cid_off = s->wide_off.as<uint32_t>();
@@ -812,7 +827,7 @@ static int32_t binarize_current(tsat_solver* s, int32_t mode)
 {
     tsat_params p = s->params;
     p.norm_mode = mode;
-    VarArgs a = var_args(s, p, s->N, s->W, s->Np);
+    VarArgs a = var_args(s, p, s->N, s->W, s->Np, nullptr);
     a.lits_next = s->lits[s->cur].as<uint64_t>();
     a.mu_next = s->mu[s->cur].as<double>();
     a.theta = s->theta.as<float>();
@@ -996,7 +1011,7 @@ static int32_t load_store(tsat_solver* s, Store&& st)
     s->wide_cid.release();
     s->wide_off.release();
     s->wide_mid.release();
-    s->bytes_off = false;
+    s->planes_refused = s->scr_refused = 0;
     if (!s->st.wide_cid.empty()) {
         // 64 words of padding, as above
         const size_t nr = s->st.wide_cid.size();
@@ -1161,8 +1176,8 @@ static int32_t alloc_batch(tsat_solver* s, int32_t N)
     HIPCHK(launch_fill_u32(s->H.as<uint32_t>(), (int64_t)hw, 0u, s->stream));
     HIPCHK(launch_fill_u32(s->m.as<uint32_t>(), (int64_t)VN, 0u, s->stream));
     HIPCHK(launch_fill_u32(s->v.as<uint32_t>(), (int64_t)VN, 0u, s->stream));
-    s->bytes_off = false;
-    if (plane_path(s, N) || bytes_path(s, N)) RET(ensure_planes(s, s->planes, N, s->stream));
+    s->planes_refused = s->scr_refused = 0;
+    RET(ensure_planes(s, s->planes, s->planes_refused, N, s->stream));
     RET(ensure_partial(s, s->partial, N));
     s->N = N;
     s->W = W;
@@ -1317,7 +1332,7 @@ static int32_t enqueue_iteration(tsat_solver* s, const SminArgs& sa, VarArgs va,
     Ctrl* ctrl = s->ctrl.as<Ctrl>();
     InstCtrl* ictrl = s->ictrl.as<InstCtrl>();
     RET(enqueue_fwd(s, s->lits[cur].as<uint64_t>(), s->N, s->H.as<uint32_t>(), ctrl, ictrl, s->stream,
-                    plane_path(s, s->N) || bytes_path(s, s->N) ? s->planes.as<uint32_t>() : nullptr));
+                    planes_in(s, s->planes, s->N)));
     if (timing) HIPCHK(hipEventRecord(s->events[3 * it + 1], s->stream));
     HIPCHK(launch_smin(sa, s->stream));
     if (timing) HIPCHK(hipEventRecord(s->events[3 * it + 2], s->stream));
@@ -1392,9 +1407,7 @@ int32_t tsat_step(tsat_solver* s, int32_t max_steps, const tsat_params* params, 
     sa.ctrl = ctrl;
     sa.ictrl = s->ictrl.as<InstCtrl>();
     sa.update = 1;
-    VarArgs va = var_args(s, p, s->N, s->W, s->Np);
-    va.planes = s->planes.as<uint32_t>();
-    if (bytes_path(s, s->N)) va.rb = s->planes.as<uint8_t>();
+    VarArgs va = var_args(s, p, s->N, s->W, s->Np, planes_in(s, s->planes, s->N));
     if (va.heavy) va.partial = s->partial.as<double>();
     va.tbl = s->table.as<float>();
     va.theta = s->theta.as<float>();
@@ -1586,8 +1599,8 @@ static int32_t eval_rows(tsat_solver* s, const tsat_params& p, const uint64_t* l
     if (saved) {
         planes = saved->planes;
     } else if ((plane_path(s, N) && (table || s->st.K > 4 || multi_path(s, N))) || (table && bytes_path(s, N))) {
-        RET(ensure_planes(s, s->planes_scr, N, st));
-        planes = s->planes_scr.as<uint32_t>();
+        RET(ensure_planes(s, s->planes_scr, s->scr_refused, N, st));
+        planes = planes_in(s, s->planes_scr, N);
     }
     if (table) RET(ensure_partial(s, s->partial_scr, N));
     RET(enqueue_fwd(s, lits, N, s->H_scr.as<uint32_t>(), nullptr, nullptr, st, planes));
@@ -1847,7 +1860,7 @@ int32_t tsat_get_grad(tsat_solver* s, const tsat_params* params, float* U, float
     RET(s->tmp.reserve(VN * 8, "gradient copies"));
     RET(eval_rows(s, p, s->lits[s->cur].as<uint64_t>(), s->N, nullptr, nullptr, nullptr, nullptr, nullptr,
                   s->table_scr.as<float>(), s->stream));
-    VarArgs va = var_args(s, p, s->N, s->W, s->Np);
+    VarArgs va = var_args(s, p, s->N, s->W, s->Np, planes_in(s, s->planes_scr, s->N));
     va.tbl = s->table_scr.as<float>();
     va.theta = s->theta.as<float>();
     va.lits_cur = s->lits[s->cur].as<uint64_t>();
@@ -1912,7 +1925,7 @@ int32_t tsat_extract_partial(tsat_solver* s, int32_t max_cands, int32_t k, int32
     RET(eval_rows(s, s->params, s->lits[s->cur].as<uint64_t>(), s->N, nullptr, nullptr, nullptr, nullptr,
                   s->sat_scr.as<int64_t>(), s->table_scr.as<float>(), s->stream));
     HIPCHK(launch_rank(s->sat_scr.as<int64_t>(), s->N, max_cands, order, slot, s->stream));
-    VarArgs va = var_args(s, s->params, s->N, s->W, s->Np);
+    VarArgs va = var_args(s, s->params, s->N, s->W, s->Np, planes_in(s, s->planes_scr, s->N));
     va.tbl = s->table_scr.as<float>();
     va.theta = s->theta.as<float>();
     va.lits_cur = s->lits[s->cur].as<uint64_t>();
@@ -1995,7 +2008,7 @@ int32_t tsat_bwd_dev(tsat_solver* s, const uint64_t* bits, int32_t N, float tau,
     tsat_params p = s->params;
     p.tau = tau;
     RET(eval_rows(s, p, s->lits_scr.as<uint64_t>(), N, dS, nullptr, nullptr, nullptr, nullptr, s->table_scr.as<float>(), st));
-    VarArgs va = var_args(s, p, N, W, Np);
+    VarArgs va = var_args(s, p, N, W, Np, planes_in(s, s->planes_scr, N));
     va.tbl = s->table_scr.as<float>();
     va.lits_cur = s->lits_scr.as<uint64_t>();
     va.U_out = U;
@@ -2105,7 +2118,7 @@ static int32_t dev_binarize(tsat_solver* s, const float* theta, int32_t N, int32
     const int32_t W = (N + 63) / 64;
     tsat_params p = s->params;
     p.norm_mode = mode;
-    VarArgs a = var_args(s, p, N, W, 64 * W);
+    VarArgs a = var_args(s, p, N, W, 64 * W, nullptr);
     a.theta = const_cast<float*>(theta); // read only by the binarize op
     a.lits_next = lits ? lits : s->lits_scr.as<uint64_t>();
     a.mu_next = mu ? mu : s->mu_scr.as<double>();
@@ -2145,7 +2158,7 @@ int32_t tsat_norm_backward_dev(tsat_solver* s, const float* theta, const float* 
     const int32_t W = (N + 63) / 64;
     tsat_params p = s->params;
     p.norm_mode = mode;
-    VarArgs a = var_args(s, p, N, W, 64 * W);
+    VarArgs a = var_args(s, p, N, W, 64 * W, nullptr);
     a.theta = const_cast<float*>(theta); // read only by this op
     a.dA_in = dA;
     a.g_out = g;
@@ -2184,7 +2197,7 @@ int32_t tsat_loss_backward_dev(tsat_solver* s, const float* theta, int32_t N, fl
     p.norm_mode = mode;
     RET(eval_rows(s, p, s->lits_scr.as<uint64_t>(), N, nullptr, nullptr, nullptr, nullptr, nullptr,
                   s->table_scr.as<float>(), st, nullptr, dloss));
-    VarArgs va = var_args(s, p, N, W, Np);
+    VarArgs va = var_args(s, p, N, W, Np, planes_in(s, s->planes_scr, N));
     va.tbl = s->table_scr.as<float>();
     va.theta = const_cast<float*>(theta); // read only by the gradient op
     va.lits_cur = s->lits_scr.as<uint64_t>();
@@ -2247,11 +2260,9 @@ static int32_t saved_backward(tsat_solver* s, const tsat_params& p, int32_t N, c
     a.dloss = dloss;
     a.update = 0;
     HIPCHK(launch_smin(a, st));
-    VarArgs va = var_args(s, p, N, W, Np);
+    VarArgs va = var_args(s, p, N, W, Np, v.planes);
     va.tbl = s->table_scr.as<float>();
     va.theta = const_cast<float*>(theta); // read only by the gradient op
-    va.planes = v.planes;
-    if (bytes_path(s, N)) va.rb = reinterpret_cast<const uint8_t*>(v.planes);
     va.lits_cur = v.lits ? v.lits : s->lits_scr.as<uint64_t>(); // the plane gathers of these ops use no rows
     va.mu_cur = v.mu;
     va.U_out = U;
@@ -2395,7 +2406,8 @@ int32_t tsat_set_launch_config(tsat_solver* s, const tsat_launch_config* cfg)
     s->pure_group = cfg->pure_group;
     s->clause_planes = cfg->clause_planes;
     s->window_gather = cfg->window_gather;
-    if (s->N > 0 && (plane_path(s, s->N) || bytes_path(s, s->N))) RET(ensure_planes(s, s->planes, s->N, s->stream));
+    s->planes_refused = s->scr_refused = 0;
+    if (s->N > 0) RET(ensure_planes(s, s->planes, s->planes_refused, s->N, s->stream));
     return TSAT_OK;
 }
 

@@ -15,9 +15,12 @@
 namespace tsat_host {
 
 // allocation-failure injection for tests of the OOM path: the environment
-// variable TSAT_FAIL_ALLOC_AFTER=n makes the (n+1)-th device allocation fail
-inline bool inject_alloc_failure()
+// variable TSAT_FAIL_ALLOC_AFTER=n makes the (n+1)-th device allocation and
+// all later ones fail, TSAT_FAIL_ALLOC_OVER=n those of more than n bytes
+inline bool inject_alloc_failure(size_t bytes)
 {
+    static const char* over = getenv("TSAT_FAIL_ALLOC_OVER");
+    if (over && bytes > (size_t)atoll(over)) return true;
     static int64_t countdown = -2;
     if (countdown == -2) {
         const char* e = getenv("TSAT_FAIL_ALLOC_AFTER");
@@ -54,7 +57,7 @@ struct DBuf {
         if (n == bytes && p) return TSAT_OK;
         release();
         if (n == 0) return TSAT_OK;
-        if (inject_alloc_failure()) return fail(TSAT_E_OOM, "device allocation of %zu bytes for %s failed (injected)", n, what);
+        if (inject_alloc_failure(n)) return fail(TSAT_E_OOM, "device allocation of %zu bytes for %s failed (injected)", n, what);
         if (hipMalloc(&p, n) != hipSuccess) {
             (void)hipGetLastError();
             p = nullptr;
