@@ -440,8 +440,9 @@ int32_t tsat_loss_backward_saved_dev(tsat_solver* s, const float* theta, int32_t
  * time on one GPU (any solver, any stream) race and must be ordered by the
  * caller.  Each call clears what it needs.  1 <= N <= TSAT_MAX_STEP_N;
  * E_ARG when the accumulator ((64 ceil(N/64)) x (max width + 1) x 4 bytes)
- * plus the work units (24 bytes per unit, about C / 8000 units per width
- * bucket at N = 256) exceed the array; E_STATE as tsat_fwd_dev. */
+ * plus the work units (24 bytes per unit; where the launch shape's do not
+ * fit, coarser ones, down to about C / 8000 units per width bucket at N = 256)
+ * exceed the array; E_STATE as tsat_fwd_dev. */
 int32_t tsat_fwd_dev_noalloc(tsat_solver* s, const uint64_t* bits, int32_t N, float tau, float* S, uint32_t* hist,
                              void* stream);
 

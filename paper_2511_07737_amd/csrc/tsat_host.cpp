@@ -168,7 +168,7 @@ struct FwdGeom {
     int DT, S, CPT, tiles, Dn;
 };
 
-static FwdGeom fwd_geometry(int32_t N, int32_t K1, int64_t Cb, int32_t KW, int32_t target_blocks)
+static FwdGeom fwd_geometry(int32_t N, int32_t K1, int64_t Cb, int32_t KW, int32_t target_blocks, int32_t min_cpt = 4)
 {
     FwdGeom g;
     g.Dn = (N + 31) / 32;
@@ -191,12 +191,12 @@ static FwdGeom fwd_geometry(int32_t N, int32_t K1, int64_t Cb, int32_t KW, int32
     target_blocks = std::max(1, target_blocks);
     const int64_t target_x = std::max<int64_t>(1, (target_blocks + g.tiles - 1) / g.tiles);
     int64_t cpt = (Cb + (int64_t)g.S * target_x - 1) / ((int64_t)g.S * target_x);
-    // at least 4 clauses per thread: below that the read-out of a block's
+    // at least 4 clauses per thread (min_cpt): below that the read-out of a block's
     // counters outweighs its clauses (32 ragged instances, N = 32: forward
     // 30.1 us at 16, 26.6 at 8 and 4; 32 instances of 800 clauses, N = 64:
     // 11.6 at 16, 10.5 at 4, 9.9 at 2; 2e5 mixed clauses, N = 100, the three
     // narrow buckets: 43.4 at 16, 31.9 at 4, 34.5 at 2)
-    g.CPT = (int)std::max<int64_t>(4, std::min<int64_t>(255, cpt));
+    g.CPT = (int)std::max<int64_t>(min_cpt, std::min<int64_t>(255, cpt));
     return g;
 }
 
@@ -2057,12 +2057,18 @@ int32_t tsat_fwd_dev_noalloc(tsat_solver* s, const uint64_t* bits, int32_t N, fl
     // layout: histogram accumulator [Np][K1] u32, then each bucket's units
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
     const size_t h_bytes = up((size_t)Np * K1 * 4);
-    size_t need = h_bytes;
-    for (auto* b : s->buckets) {
-        if (b->count == 0 || b->k == 0) continue;
-        const FwdGeom g = fwd_geometry(N, K1, b->count, b->k, s->fwd_target_blocks);
-        const int64_t per = (int64_t)g.S * g.CPT;
-        need += up((size_t)((b->count + per - 1) / per) * sizeof(FwdUnit));
+    // tables that would not fit take more clauses per thread, up to the most
+    int32_t min_cpt = 4;
+    size_t need;
+    for (;; min_cpt = std::min(255, 4 * min_cpt)) {
+        need = h_bytes;
+        for (auto* b : s->buckets) {
+            if (b->count == 0 || b->k == 0) continue;
+            const FwdGeom g = fwd_geometry(N, K1, b->count, b->k, s->fwd_target_blocks, min_cpt);
+            const int64_t per = (int64_t)g.S * g.CPT;
+            need += up((size_t)((b->count + per - 1) / per) * sizeof(FwdUnit));
+        }
+        if (need <= TSAT_NOALLOC_SCRATCH_BYTES || min_cpt == 255) break;
     }
     if (need > TSAT_NOALLOC_SCRATCH_BYTES)
         return fail(TSAT_E_ARG, "needs %zu bytes of scratch, the fixed array holds %u", need, TSAT_NOALLOC_SCRATCH_BYTES);
@@ -2072,7 +2078,7 @@ int32_t tsat_fwd_dev_noalloc(tsat_solver* s, const uint64_t* bits, int32_t N, fl
     size_t off = h_bytes;
     for (auto* b : s->buckets) {
         if (b->count == 0 || b->k == 0) continue;
-        const FwdGeom g = fwd_geometry(N, K1, b->count, b->k, s->fwd_target_blocks);
+        const FwdGeom g = fwd_geometry(N, K1, b->count, b->k, s->fwd_target_blocks, min_cpt);
         const int64_t per = (int64_t)g.S * g.CPT;
         const int64_t nunits = (b->count + per - 1) / per;
         FwdUnit* units = reinterpret_cast<FwdUnit*>(base + off);
