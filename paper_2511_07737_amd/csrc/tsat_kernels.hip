@@ -1485,8 +1485,20 @@ __device__ __forceinline__ void cum_masks(const uint64_t (&w)[KO], uint64_t (&ge
 template <int J, int KO, int G, int OP, bool FULL>
 __device__ __forceinline__ void var_pure_body(const VarArgs& a);
 
-// Uniform-width update kernel.  The batched gather needs its scalar
-// registers; the grouped one fits eight waves per SIMD.
+// Uniform-width update kernels.  The batched gather needs its scalar
+// registers; the grouped one fits eight waves per SIMD with rows of up to
+// four words.  Longer rows hold more than the 64 registers that leaves: at
+// eight waves they spill (850 to 900 registers of the step's 16-word rows), so
+// they get the registers of four waves (8 words), three, or two for the step
+// (16 words).  V = 1e5, 3-SAT, N = 1000: update 5.96 ms at eight waves, 2.02
+// at four, 1.76 at three, 1.29 at two; adjoint 0.80, 0.50, 0.51, 0.64;
+// N = 300: update 0.88, 0.69 at six, 0.64 at five, 0.36 at four.
+template <int J, int OP>
+constexpr int pure_waves()
+{
+    return J <= 4 ? 8 : (J <= 8 ? 4 : (OP == OP_STEP ? 2 : 3));
+}
+
 template <int J, int KO, int G, int OP, bool FULL>
 __global__ __launch_bounds__(256) void var_pure_kernel(VarArgs a)
 {
@@ -1494,7 +1506,8 @@ __global__ __launch_bounds__(256) void var_pure_kernel(VarArgs a)
 }
 
 template <int J, int KO, int G, int OP, bool FULL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) void var_pure8_kernel(VarArgs a)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(pure_waves<J, OP>(), 8))) void var_pure8_kernel(
+    VarArgs a)
 {
     var_pure_body<J, KO, G, OP, FULL>(a);
 }
@@ -4038,7 +4051,7 @@ static int occupancy_of(K kernel, size_t lds, int threads = 256)
     return n;
 }
 
-// the batched gather keeps its scalar registers; the others run eight waves per SIMD
+// the batched gather keeps its scalar registers
 template <int J, int KO, int G, int OP, bool FULL>
 static auto pure_kernel_ptr()
 {
