@@ -682,13 +682,17 @@ static SminArgs smin_args(tsat_solver* s, const tsat_params& p, int32_t N, int32
 // resident round: waves that finish early pick up the remaining blocks); 16
 // per CU for the gradient and adjoint passes (V = 4e5, N = 256 gradient
 // 311 us, 328 at 32; V = 1e5 mixed adjoint 110 and 113; V = 2e5, N = 128
-// adjoint 64 and 63).
-static int var_blocks(const tsat_solver* s, int32_t V, int occ = 0)
+// adjoint 64 and 63), 32 for the row-wise passes, binarization and Eq. 5
+// backward, which wait for nothing but their streams (V = 1e5, N = 1000: Eq. 5
+// backward 388 us, 418 at 16; binarization 240 and 249).
+static int var_blocks(const tsat_solver* s, int32_t V, int occ = 0, int other = 16)
 {
-    const int per_cu = s->var_per_cu > 0 ? s->var_per_cu : (occ > 0 ? 4 * occ : 16);
+    const int per_cu = s->var_per_cu > 0 ? s->var_per_cu : (occ > 0 ? 4 * occ : other);
     const int64_t want = ((int64_t)V + 3) / 4;
     return (int)std::max<int64_t>(1, std::min<int64_t>(want, (int64_t)s->cus * per_cu));
 }
+
+static int row_blocks(const tsat_solver* s, int32_t V) { return var_blocks(s, V, 0, 32); }
 
 // `planes`: the forward's planes or bytes of R for a gather over them; null:
 // the other literals' rows are gathered (or nothing at all).
@@ -833,7 +837,7 @@ static int32_t binarize_current(tsat_solver* s, int32_t mode)
     a.theta = s->theta.as<float>();
     a.ctrl = s->ctrl.as<Ctrl>();
     batch_rows(s, a);
-    HIPCHK(launch_var(a, VOP_BINARIZE, var_blocks(s, a.V), s->stream));
+    HIPCHK(launch_var(a, VOP_BINARIZE, row_blocks(s, a.V), s->stream));
     s->bits_mode = mode;
     return TSAT_OK;
 }
@@ -2130,7 +2134,7 @@ static int32_t dev_binarize(tsat_solver* s, const float* theta, int32_t N, int32
     a.mu_next = mu ? mu : s->mu_scr.as<double>();
     a.vbits_out = vbits;
     a.assign_out = assign;
-    HIPCHK(launch_var(a, VOP_BINARIZE, var_blocks(s, s->st.V), st));
+    HIPCHK(launch_var(a, VOP_BINARIZE, row_blocks(s, s->st.V), st));
     return TSAT_OK;
 }
 
@@ -2168,7 +2172,7 @@ int32_t tsat_norm_backward_dev(tsat_solver* s, const float* theta, const float* 
     a.theta = const_cast<float*>(theta); // read only by this op
     a.dA_in = dA;
     a.g_out = g;
-    HIPCHK(launch_var(a, VOP_NORMBWD, var_blocks(s, s->st.V), (hipStream_t)stream));
+    HIPCHK(launch_var(a, VOP_NORMBWD, row_blocks(s, s->st.V), (hipStream_t)stream));
     return TSAT_OK;
 }
 
