@@ -2090,7 +2090,7 @@ int32_t tsat_fwd_dev_noalloc(tsat_solver* s, const uint64_t* bits, int32_t N, fl
         HIPCHK(launch_fwd_units(units, nunits, per, b->count, st));
         FwdArgs a{};
         a.units = units;
-        a.codes = b->codes.as<uint32_t>();
+        a.codes = a.wide_codes[b->k] = b->codes.as<uint32_t>();
         a.KW = b->k;
         a.K1 = K1;
         a.bits32 = reinterpret_cast<const uint32_t*>(bits);

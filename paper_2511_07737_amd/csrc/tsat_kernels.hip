@@ -438,8 +438,11 @@ __global__ __launch_bounds__(256) void fwd_hist_lanes_kernel(FwdArgs a)
     const uint32_t lane = __lane_id(), wave = uniform(threadIdx.x / 64u);
     // KW = 0: the units of every wide bucket in one launch, unit width in pad
     const int K1 = a.K1, k = (int)uniform((uint32_t)(a.KW > 0 ? a.KW : u.pad));
-    const uint32_t* codes = a.KW > 0 ? a.codes : a.wide_codes[k];
-    const int64_t pbase = a.KW > 0 ? a.plane_base : a.wide_base[k];
+    // from the tables by width in either form: a choice between them and the
+    // single bucket's fields becomes one of two addresses, for which every lane
+    // copies the arguments to scratch memory (672 bytes)
+    const uint32_t* codes = a.wide_codes[k];
+    const int64_t pbase = a.wide_base[k];
     const uint32_t cand = blockIdx.y * 64u + lane;
     const bool live = (int)(cand >> 5) < a.Dn;
     uint32_t* my = lh + (wave * 64u + lane) * (uint32_t)K1;
