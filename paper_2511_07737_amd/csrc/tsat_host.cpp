@@ -2058,13 +2058,14 @@ int32_t tsat_fwd_dev_noalloc(tsat_solver* s, const uint64_t* bits, int32_t N, fl
     RET(set_dev(s));
     hipStream_t st = (hipStream_t)stream; // NULL: the null (default) stream
     const int32_t W = (N + 63) / 64, Np = 64 * W, K1 = K1_of(s);
-    // layout: histogram accumulator [Np][K1] u32, then each bucket's units
+    // layout: histogram accumulator [reps][Np][K1] u32, then each bucket's
+    // units.  What would not fit takes one replica, then more clauses per
+    // thread, up to the most
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
-    const size_t h_bytes = up((size_t)Np * K1 * 4);
-    // tables that would not fit take more clauses per thread, up to the most
-    int32_t min_cpt = 4;
-    size_t need;
-    for (;; min_cpt = std::min(255, 4 * min_cpt)) {
+    int32_t reps = hist_reps(s, Np), min_cpt = 4;
+    size_t h_bytes, need;
+    for (;;) {
+        h_bytes = up((size_t)reps * Np * K1 * 4);
         need = h_bytes;
         for (auto* b : s->buckets) {
             if (b->count == 0 || b->k == 0) continue;
@@ -2073,12 +2074,14 @@ int32_t tsat_fwd_dev_noalloc(tsat_solver* s, const uint64_t* bits, int32_t N, fl
             need += up((size_t)((b->count + per - 1) / per) * sizeof(FwdUnit));
         }
         if (need <= TSAT_NOALLOC_SCRATCH_BYTES || min_cpt == 255) break;
+        if (reps > 1) reps = 1;
+        else min_cpt = std::min(255, 4 * min_cpt);
     }
     if (need > TSAT_NOALLOC_SCRATCH_BYTES)
         return fail(TSAT_E_ARG, "needs %zu bytes of scratch, the fixed array holds %u", need, TSAT_NOALLOC_SCRATCH_BYTES);
     uint8_t* base = static_cast<uint8_t*>(s->noalloc_scratch);
     uint32_t* H = reinterpret_cast<uint32_t*>(base);
-    HIPCHK(launch_fill_u32(H, (int64_t)Np * K1, 0u, st));
+    HIPCHK(launch_fill_u32(H, (int64_t)reps * Np * K1, 0u, st));
     size_t off = h_bytes;
     for (auto* b : s->buckets) {
         if (b->count == 0 || b->k == 0) continue;
@@ -2101,7 +2104,7 @@ int32_t tsat_fwd_dev_noalloc(tsat_solver* s, const uint64_t* bits, int32_t N, fl
         a.CPT = g.CPT;
         a.H = H;
         a.H_stride = (int64_t)Np * K1;
-        a.H_reps = 1; // the fixed scratch array holds one accumulator
+        a.H_reps = reps;
         a.nunits = (int32_t)nunits;
         HIPCHK(launch_fwd(a, (int)nunits, g.tiles, st));
     }
@@ -2109,7 +2112,7 @@ int32_t tsat_fwd_dev_noalloc(tsat_solver* s, const uint64_t* bits, int32_t N, fl
     p.tau = tau;
     SminArgs a = smin_args(s, p, N, Np);
     a.H = H;
-    a.H_reps = 1;
+    a.H_reps = reps;
     a.H_last = hist;
     a.S_out = S;
     a.update = 0;
