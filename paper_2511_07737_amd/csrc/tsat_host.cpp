@@ -1902,8 +1902,8 @@ int32_t tsat_extract_partial(tsat_solver* s, int32_t max_cands, int32_t k, int32
     sa.W = s->W;
     sa.S = max_cands;
     sa.k = k;
-    sa.kpow2 = 1;
-    while (sa.kpow2 < k) sa.kpow2 <<= 1;
+    sa.kpow2 = 1; // sorted: at most one entry per variable
+    while (sa.kpow2 < std::min(k, sa.V)) sa.kpow2 <<= 1;
     sa.chunk = (int32_t)std::max<size_t>(256, (V + 511) / 512);
     sa.nchunks = (int32_t)((V + sa.chunk - 1) / sa.chunk);
     size_t need = 0;
