@@ -194,8 +194,9 @@ __device__ __forceinline__ int w2t_slot(int k, int c)
 // part is the rounded rest of the ones before it, 8 significant bits a part,
 // so the sum is x itself for magnitudes of 2^-102 (below, the last part leaves
 // the normal numbers) up to 2^127 (above, the first may round to infinity).
-// An infinity has no rest.  Products with BF16 operands are then exact in the
-// FP32 accumulation, as FP32 operands would be, at the BF16 matrix rate.
+// An infinity's rest, and a NaN's, is some finite number, which changes nothing
+// beside them.  Products with BF16 operands are then exact in the FP32
+// accumulation, as FP32 operands would be, at the BF16 matrix rate.
 __device__ __forceinline__ void split_bf16(const float (&x)[4], uint2 (&s)[3])
 {
     float r[4] = {x[0], x[1], x[2], x[3]};
@@ -205,8 +206,8 @@ __device__ __forceinline__ void split_bf16(const float (&x)[4], uint2 (&s)[3])
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             h[e] = bf16_bits(r[e]);
-            const float rest = r[e] - bf16_value(h[e]);
-            r[e] = p > 0 || fabsf(r[e]) < __builtin_inff() ? rest : 0.f;
+            r[e] -= bf16_value(h[e]);
+            if (p == 0) r[e] = fmaxf(r[e], -0x1p120f);
         }
         s[p] = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
     }
@@ -262,8 +263,8 @@ constexpr int kRed = 3 * kHid + 2;
 // accumulator layout of the forward is the operand layout of dW2 (lane r + 16 q
 // holds rows 4 q .. 4 q + 3 of column r), so each wave hands its h1 and da2
 // parts over in lane order, without a transpose.  B = 16384, one block per CU:
-// 35.4 us with FP32 operands read element by element from LDS, 29.4 us (0.8 of
-// it for the scale).
+// 35.4 us with FP32 operands read element by element from LDS, 28.6 us so, 30.2
+// with the scale.
 template <bool TRAIN>
 __global__ __launch_bounds__(256) void mlp_kernel(MlpDev d, const float* __restrict__ X, const float* __restrict__ y,
                                                   const float* __restrict__ wt, int64_t B,
@@ -276,13 +277,12 @@ __global__ __launch_bounds__(256) void mlp_kernel(MlpDev d, const float* __restr
     __shared__ float s_red[TRAIN ? 4 * kRed : 1];
     __shared__ uint2 s_opA[TRAIN ? 4 : 1][TRAIN ? 8 * 64 : 1];     // h1 of a wave's rows, [tile][lane]
     __shared__ uint2 s_opB[TRAIN ? 4 : 1][TRAIN ? 3 * 8 * 64 : 1]; // da2 parts, [part][tile][lane]
-    __shared__ int s_large;                                        // a da2 may pass 2^76
+    __shared__ int s_large[4];                                     // a da2 may pass 2^76, by wave
 
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, r = lane & 15, q = lane >> 4;
     // |dLoss/dout| <= |weight| (1 + |label|) / B; a NaN stays
     float reach = 0.f;
     if (TRAIN) {
-        if (tid == 0) s_large = 0;
         for (int64_t i = ((int64_t)wv * gridDim.x + blockIdx.x) * 64 + lane; i < B; i += (int64_t)gridDim.x * 256) {
             const float x = (wt ? fabsf(wt[i]) : 1.f) * (1.f + fabsf(y[i]));
             reach = x <= reach ? reach : x;
@@ -302,16 +302,14 @@ __global__ __launch_bounds__(256) void mlp_kernel(MlpDev d, const float* __restr
     const float invB = 1.f / (float)B;
     float scale = 0x1p24f;
     if (TRAIN) {
-        float w3top = 0x1p-24f;
+        float w3top = 0.f;
 #pragma unroll
         for (int n = 0; n < 8; ++n) w3top = fmaxf(w3top, fabsf(w3c[n]));
-#pragma unroll
-        for (int m = 1; m < 16; m <<= 1) w3top = fmaxf(w3top, __shfl_xor(w3top, m));
-        __syncthreads(); // s_large is cleared
-        if (!(reach * invB * w3top < 0x1p76f)) s_large = 1;
+        const uint64_t large = __ballot(!(reach * invB < 0x1p50f && w3top < 0x1p26f));
+        if (lane == 0) s_large[wv] = large != 0;
     }
     __syncthreads();
-    if (TRAIN && s_large) scale = 0x1p-24f;
+    if (TRAIN && (s_large[0] | s_large[1] | s_large[2] | s_large[3])) scale = 0x1p-24f;
 
     const v4f zero = {0.f, 0.f, 0.f, 0.f};
     v4f gW2[2][8], gW1[2];
