@@ -549,8 +549,10 @@ typedef struct {
                                   gather): 1 = the forward stores R of every
                                   clause in binary and the update gathers it (one record per
                                   occurrence), 0 = the update gathers the other literals' rows.
-                                  Other stores of mixed or wide clauses: 1 = the forward stores R
-                                  in bytes (up to 8 GiB) */
+                                  Uniform widths 2, 3 past 256 candidates with the window gather: the
+                                  same.  Other stores of mixed or wide clauses: 1 = the forward
+                                  stores R in bytes (up to 8 GiB).  Past 256 candidates, and as
+                                  bytes, only where the memory is there */
     int32_t window_gather;     /* with clause planes: 1 = the update loads the planes of 64 consecutive
                                   occurrence records per vector load and transposes their bits across
                                   the wavefront (up to 32 candidates: two variables per wavefront),

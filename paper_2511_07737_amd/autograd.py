@@ -15,10 +15,13 @@ passes their pointers and torch's current stream, and wires the backward.
   backward in one fused pass (adjoint, Eq. 5 backward).
 
 The layer and the loss keep the forward's histogram, row means and clause
-planes in a saved tensor, so that the backward does not form the forward
-again; without a gradient to compute nothing is kept.  Inside ``forward`` autograd
-is off and ``needs_input_grad`` only says that the input asks for a gradient,
-so the wrappers pass on whether autograd was recording.
+planes (or bytes of R, or literal rows) in a saved tensor, so that the backward
+does not form the forward again.  Each node holds its own until it is freed:
+two to four bits per clause and candidate, or a byte where clauses pass 15
+literals and for mixed widths past 256 candidates (up to 8 GiB).  Without a
+gradient to compute nothing is kept: inside ``forward`` autograd is off and
+``needs_input_grad`` only says that the input asks for a gradient, so the
+wrappers pass on whether autograd was recording.
 """
 from __future__ import annotations
 
@@ -100,7 +103,8 @@ class SmoothMinSat(torch.autograd.Function):
 
 
 def smoothmin_sat(assign: torch.Tensor, solver: tsat.Solver, tau: float = 1.0) -> torch.Tensor:
-    """S[N] of the binary assignment ``assign`` [V][N] (differentiable via the STE adjoint)."""
+    """S[N] of the binary assignment ``assign`` [V][N] (differentiable via the STE adjoint).
+    With a gradient to compute, the node keeps ``solver.saved_bytes(N)`` bytes of GPU memory."""
     return SmoothMinSat.apply(assign, solver, float(tau), torch.is_grad_enabled())
 
 
@@ -164,6 +168,7 @@ class LogitLoss(torch.autograd.Function):
 
 
 def loss_of(theta: torch.Tensor, solver: tsat.Solver, tau: float = 1.0, normalize: bool = True) -> torch.Tensor:
-    """L = -sum_i S_i (Eq. 3) of the logits theta [V][N], as a 0-d tensor."""
+    """L = -sum_i S_i (Eq. 3) of the logits theta [V][N], as a 0-d tensor.
+    With a gradient to compute, the node keeps ``solver.saved_bytes(N)`` bytes of GPU memory."""
     mode = tsat.MODE_MEAN if normalize else tsat.MODE_NONE
     return LogitLoss.apply(theta, solver, float(tau), mode, torch.is_grad_enabled())

@@ -311,11 +311,13 @@ static size_t levels_lds_bytes(const tsat_solver* s, int32_t J)
 
 // The clause-plane update applies: clause-index records exist (widths up to
 // kMaxPlaneWidth) and, beyond uniform widths 2 and 3 at N <= 256 (which also
-// have a record-by-record plane gather), the window gather is on and its
-// 16-bit counts hold; mixed widths up to 256 candidates and within the
-// kernel's LDS budget, uniform widths 2 and 3 up to TSAT_MAX_STEP_N (the row
-// gather took 2.35 ms per launch at V = 5e4, C = 2.05e5, N = 1000 where the
-// teams of waves take 0.36).
+// have a record-by-record plane gather), the window gather is on and no
+// variable has 65536 records of one sign; mixed widths up to 256 candidates
+// and within the kernel's LDS budget, uniform widths 2 and 3 up to
+// TSAT_MAX_STEP_N (V = 5e4, C = 2.05e5, N = 1000: 0.66 ms per launch for the
+// row gather, 0.34 for the teams of waves).  The line at 65536 records was
+// drawn for counts in 16-bit halves; they are whole words now, whose sums are
+// exact in FP32 below 2^24, but no store past the line has been run.
 static bool plane_path(const tsat_solver* s, int32_t N)
 {
     const int32_t W = (N + 63) / 64;
@@ -327,10 +329,12 @@ static bool plane_path(const tsat_solver* s, int32_t N)
 }
 
 // R of every clause and candidate in bytes, for the stores and candidate
-// counts past the planes (clauses wider than kMaxPlaneWidth; mixed widths at
-// N > 256) with generic records: an update then loads one byte per record
-// and candidate where the row gather loads k - 1 literal rows and counts.
-// Held to 8 GiB, and to the clause planes' switch.
+// counts past the planes (clauses wider than kMaxPlaneWidth; mixed widths, and
+// uniform ones other than 2, 3 and 4, at N > 256 or with the window gather
+// off) with generic records: an update then loads one byte per record and
+// candidate where the row gather loads k - 1 literal rows and counts.  Width 4
+// alone, whose records have no header, takes the row gather past 256
+// candidates.  Held to 8 GiB, and to the clause planes' switch.
 static size_t rbytes_bytes(const tsat_solver* s, int32_t N)
 {
     return std::max<size_t>(16, (size_t)s->st.plane_clauses * 64 * (size_t)((N + 63) / 64));
@@ -711,14 +715,15 @@ static VarArgs var_args(tsat_solver* s, const tsat_params& p, int32_t N, int32_t
     a.mode = p.norm_mode;
     a.pure_k = s->st.pure_k;
     a.group = s->pure_group;
-    // the window gather keeps its counts in 16-bit halves
+    // the same line as in plane_path
     a.window = s->window_gather && s->st.max_sign_rec < 65536;
     a.packed = packed_planes(s, N);
     a.xcd = s->xcd_update;
     // four variables share a window (measured best of 2, 4, 8 and 16); few
-    // variables go one or two per wave, so that their rows run side by side
-    // (V = 200, N = 64 gradient: 4.8 us at 1, 5.6 at 2, 6.7 at 4; 32 x 200
-    // variables update: 7.6, 7.2 and 7.9)
+    // variables go one or two per wave, so that their rows run side by side:
+    // one as long as that makes at most two waves for each of the chip's 1024
+    // SIMDs, two up to four (V = 200, N = 64 gradient: 4.8 us at 1, 5.6 at 2,
+    // 6.7 at 4; 32 x 200 variables update: 7.6, 7.2 and 7.9)
     a.chunk = s->st.V <= 2048 ? 1 : (s->st.V <= 8192 ? 2 : 4);
     a.occ_off = s->occ_off.as<uint32_t>();
     a.occ_mid = s->occ_mid.as<uint32_t>();

@@ -423,7 +423,7 @@ __device__ __forceinline__ void fwd_lanes_run(const FwdArgs& a, int k, const uin
 // A block's clauses share a width; the run is compiled for widths up to 8,
 // 16 and 32, so that narrow units keep several clauses in flight next to a
 // bucket of wide ones (2e5 mixed clauses up to 24 wide, N = 100: 87 us
-// with every unit one clause at a time and codes in vector registers, 60 us
+// with every unit one clause at a time and codes in vector registers, 24 us
 // with the bytes of R written as well).
 template <int KMAX, bool VR>
 __global__ __launch_bounds__(256) void fwd_hist_lanes_kernel(FwdArgs a)
@@ -2257,9 +2257,9 @@ __global__ __launch_bounds__(256) void var_window_kernel(VarArgs a)
 //
 // What bounds it: the theta, m, v streams and a plane row per record (V =
 // 5e4, C = 2.05e5, N = 1000: 1.2 GB and 0.16 GB a launch, 345 us = 3.9 TB/s,
-// a copy of 5.1).  The row gather of var_pure_kernel, which these sizes took
-// before, reads two literal rows of 128 bytes per record through the scalar
-// cache, one wave per variable: 2346 us.
+// a copy of 5.1).  The row gather of var_pure_kernel, which these sizes take
+// without the planes, reads two literal rows of 128 bytes per record through
+// the scalar cache, one wave per variable: 660 us.
 // ---------------------------------------------------------------------------
 
 // Planes of records [w, w + 64) as load_window<4>, of the four words from
@@ -2712,7 +2712,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void v
 // every word is transposed across the wave into the wave's LDS window, and
 // a variable counts, per level r = 1 .. KT and candidate, its positive and
 // negative records whose clause has R >= r (the comparison of the P-bit R
-// with the constant r, bit-sliced over 64 records, then two popcounts).
+// with the constant r, bit-sliced over 64 records, then one popcount).
 // U_vi = sum over r of (positive - negative records with R = r) dL/dR_i[r]
 // (Sec. III-B: P^T dL/dR with the straight-through estimator), formed from
 // these exact counts in the order of r; the tail is the one shared with the
