@@ -252,10 +252,10 @@ constexpr int kRed = 3 * kHid + 2;
 // and the bias / w3 gradients, in a fixed order; its sums go to one slot of
 // the partial buffer, which mlp_reduce_kernel adds up in block order.
 // In dW2 and dh1 one factor is BF16 already (h1q, W2q) and da2 is split into
-// three BF16 parts, so they run at the BF16 rate with nothing rounded: da2 and
-// what follows from it are held at 2^24 times their size, so that the parts of
-// small ones stay normal numbers, or at 2^-24 where the block's row weights
-// and labels allow a da2 past 2^76 or are not finite (error
+// three BF16 parts, so they run at the BF16 rate with nothing rounded: dLoss/dout
+// and what follows from it are held at 2^24 times their size, so that the parts
+// of small ones stay normal numbers, or at 2^-24 where the block's row weights,
+// labels or w3 allow a da2 past 2^76 or are not finite (error
 // of the gradient against FP64, four seeds: B = 16384 1.3e-7 .. 2.1e-6,
 // FP32 operands 2.8e-7 .. 2.1e-6; B = 60000 1.6e-7 .. 1.0e-6 and 2.9e-7 ..
 // 1.1e-6; the upper ends are rounding decisions of h1 that FP32 and FP64 take
@@ -263,7 +263,7 @@ constexpr int kRed = 3 * kHid + 2;
 // accumulator layout of the forward is the operand layout of dW2 (lane r + 16 q
 // holds rows 4 q .. 4 q + 3 of column r), so each wave hands its h1 and da2
 // parts over in lane order, without a transpose.  B = 16384, one block per CU:
-// 35.4 us with FP32 operands read element by element from LDS, 28.6 us so, 30.2
+// 35.4 us with FP32 operands read element by element from LDS, 28.6 us so, 29.0
 // with the scale.
 template <bool TRAIN>
 __global__ __launch_bounds__(256) void mlp_kernel(MlpDev d, const float* __restrict__ X, const float* __restrict__ y,
@@ -309,6 +309,7 @@ __global__ __launch_bounds__(256) void mlp_kernel(MlpDev d, const float* __restr
         if (lane == 0) s_large[wv] = large != 0;
     }
     __syncthreads();
+    // everything from dLoss/dout on carries the scale
     if (TRAIN && (s_large[0] | s_large[1] | s_large[2] | s_large[3])) scale = 0x1p-24f;
 
     const v4f zero = {0.f, 0.f, 0.f, 0.f};
@@ -353,8 +354,15 @@ __global__ __launch_bounds__(256) void mlp_kernel(MlpDev d, const float* __restr
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
             const uint2 ah = *reinterpret_cast<const uint2*>(&h1[r * kH1S + 16 * s + 4 * q]);
+            uint2 b2[8];
 #pragma unroll
-            for (int n = 0; n < 8; ++n) acc[n] = mfma_bf16(ah, s_w2[(s * 8 + n) * 64 + lane], acc[n]);
+            for (int n = 0; n < 8; ++n) b2[n] = s_w2[(s * 8 + n) * 64 + lane];
+#pragma unroll
+            for (int n = 0; n < 8; ++n) acc[n] = mfma_bf16(ah, b2[n], acc[n]);
+            // five LDS reads, then eight products: left to itself the scheduler
+            // waits for each pair of operands (3e5 rows: 238 us a step, 224)
+            __builtin_amdgcn_sched_group_barrier(0x100, 5, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
         }
         float out[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -395,9 +403,9 @@ __global__ __launch_bounds__(256) void mlp_kernel(MlpDev d, const float* __restr
                 if (r == 0) gloss += ww * (fmaxf(z, 0.f) + log1pf(expf(-fabsf(z))) - yy * z) * invB;
             }
         }
-        float ds[4]; // scaled; a NaN as the one whose upper half is a NaN
+        // a NaN as the one whose upper half is a NaN
 #pragma unroll
-        for (int rr = 0; rr < 4; ++rr) ds[rr] = dout[rr] == dout[rr] ? dout[rr] * scale : __builtin_nanf("");
+        for (int rr = 0; rr < 4; ++rr) dout[rr] = dout[rr] == dout[rr] ? dout[rr] * scale : __builtin_nanf("");
         if (r == 0) gb3 += (dout[0] + dout[1]) + (dout[2] + dout[3]);
 #pragma unroll
         for (int n = 0; n < 8; ++n) {
@@ -405,7 +413,7 @@ __global__ __launch_bounds__(256) void mlp_kernel(MlpDev d, const float* __restr
 #pragma unroll
             for (int rr = 0; rr < 4; ++rr) {
                 const float a2 = acc[n][rr] + b2c[n];
-                const float g = a2 > 0.f ? ds[rr] * w3c[n] : 0.f;
+                const float g = a2 > 0.f ? dout[rr] * w3c[n] : 0.f;
                 g4[rr] = g;
                 da[(4 * q + rr) * kDS + 16 * n + r] = g;
                 gb2[n] += g;
@@ -501,11 +509,11 @@ __global__ __launch_bounds__(256) void mlp_kernel(MlpDev d, const float* __restr
         for (int n = 0; n < 8; ++n) {
             s_red[wv * kRed + 16 * n + r] = gb1[n] * unscale;
             s_red[wv * kRed + kHid + 16 * n + r] = gb2[n] * unscale;
-            s_red[wv * kRed + 2 * kHid + 16 * n + r] = gw3[n];
+            s_red[wv * kRed + 2 * kHid + 16 * n + r] = gw3[n] * unscale;
         }
     }
     if (lane == 0) {
-        s_red[wv * kRed + 3 * kHid] = gb3;
+        s_red[wv * kRed + 3 * kHid] = gb3 * unscale;
         s_red[wv * kRed + 3 * kHid + 1] = gloss;
     }
     __syncthreads();
